@@ -2,12 +2,12 @@
 // on the device, plus the ea_* entry points of the C ABI.
 //
 // One workgroup per lightcurve runs a whole generation of its population:
-// the old population and its fitness are staged in LDS, rows are ranked by a
-// counting rank (stable, NaN last), one thread per reproductive pairing
-// draws its tournament, crossover mode and weights, builds both children and
-// applies creep then jump mutation to them, writing the next population in
-// place; thread 0 keeps the per-lightcurve record (best-ever individual,
-// best-chi^2 history, jump probability, stagnation flags, restarts).
+// the old population and its fitness are staged in LDS, rows are ranked
+// (stable, NaN last), the tournaments and crossover weights of all pairings
+// are drawn one Philox block per thread, then one thread per (offspring, two
+// genes) crosses and mutates them, writing the next population in place;
+// thread 0 keeps the per-lightcurve record (best-ever individual, best-chi^2
+// history, jump probability, stagnation flags, restarts).
 //
 // Random numbers: Philox4x64-10 (Salmon et al. 2011), key (seed, lc),
 // counter (generation, purpose, row, j/4), word j%4, so every draw is a pure
@@ -81,17 +81,23 @@ struct EaParams {
 
 // Sec. A.1: rows i < pop/2 uniform, row i + pop/2 = 1 - row i, odd last row
 // uniform; draws keyed by generation `gen`.  Writes rows of P for
-// lightcurve lc with the threads of one block.
+// lightcurve lc with the threads of one block, one Philox block (four genes,
+// then two) per thread and pass.
 __device__ void init_rows(const EaParams& p, double* P, int64_t lc,
                           int64_t gen) {
-  const Stream rs = {p.seed, (uint64_t)lc, (uint64_t)gen};
-  const int half = p.pop / 2;
+  const int half = p.pop / 2, drawn = half + (p.pop & 1);
   const int64_t base = lc * p.pop;
-  for (int i = threadIdx.x; i < half + (p.pop & 1); i += blockDim.x) {
+  for (int e = threadIdx.x; e < 2 * drawn; e += blockDim.x) {
+    const int q = e >= drawn ? 1 : 0, i = e - q * drawn;
     const bool odd_last = (i == half);
     const int row = odd_last ? p.pop - 1 : i;
-    for (int g = 0; g < SBLM_NPAR; ++g) {
-      const double x = u01(rs.draw(P_INIT, (uint64_t)row, (uint64_t)g));
+    const u64x4 w = philox4x64_10((uint64_t)gen, P_INIT, (uint64_t)row, (uint64_t)q, p.seed,
+                                  (uint64_t)lc);
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const int g = 4 * q + m;
+      if (g >= SBLM_NPAR) break;
+      const double x = u01(w.v[m]);
       P[g * p.n_ind + base + row] = x;
       if (!odd_last) P[g * p.n_ind + base + i + half] = 1.0 - x;
     }
@@ -170,8 +176,10 @@ __device__ void seed_mixture(const float* o, const Stream& rs, int row, double* 
   x[MLP_PERIODIC] -= floor(x[MLP_PERIODIC]);
 }
 
-__device__ void seed_row(const EaParams& p, double* P, const Proposals& pr,
-                         int64_t lc, int row, int64_t gen) {
+// (Out of line: its exponentials and cosines would cost the generation kernel,
+// which calls it at restarts only, its registers.)
+__device__ __noinline__ void seed_row(const EaParams& p, double* P, const Proposals& pr,
+                                      int64_t lc, int row, int64_t gen) {
   const int64_t k = lc / p.n_isl;  // the lightcurve of this island
   const int64_t o0 = pr.off[k], o1 = pr.off[k + 1];
   if (o1 <= o0) return;
@@ -210,16 +218,88 @@ __global__ void ea_seed_kernel(EaParams p, double* P, const EaLc* lcs, Proposals
   seed_row(p, P, pr, lc, (int)(idx % pr.n_seed), lcs[lc].gen);
 }
 
-// One generation (Sec. A.3-A.7) for lightcurve blockIdx.x.
-__global__ void ea_generation_kernel(EaParams p, double* P, EaLc* lcs,
-                                     const double* chi2, const double* Fs,
-                                     const double* Fb, int32_t* parents_out,
-                                     Proposals pr) {
+// Populations up to this size are ranked by counting, larger ones sorted.
+#define EA_COUNT_RANK 256
+
+// Entries of the ranking's arrays: N, or the next power of two for the sort.
+__host__ __device__ inline int rank_room(int N) {
+  if (N <= EA_COUNT_RANK) return N;
+  int M = 2 * EA_COUNT_RANK;
+  while (M < N) M *= 2;
+  return M;
+}
+
+// Ranks of the keys (ascending, equal keys in row order) into perm[rank] =
+// row; key[0] is then the lowest key if they were sorted.  Counting needs N^2 compares spread over the block and no barrier, the
+// bitonic sort log^2 N barriers of N/2 exchanges: at N = 256 about 1 us
+// against 4, at N = 1000 about 13 us against 6.  The sort needs room for
+// the next power of two.
+__device__ void rank_rows(double* key, int* perm, int N) {
+  if (N <= EA_COUNT_RANK) {
+    for (int i = threadIdx.x; i < N; i += blockDim.x) {
+      const double ki = key[i];
+      int r = 0;
+#pragma unroll 4
+      for (int j = 0; j < N; ++j) {
+        const double kj = key[j];
+        r += (kj < ki || (kj == ki && j < i)) ? 1 : 0;
+      }
+      perm[r] = i;
+    }
+    __syncthreads();
+    return;
+  }
+  const int M = rank_room(N);
+  for (int i = threadIdx.x; i < M; i += blockDim.x) {
+    perm[i] = i;
+    if (i >= N) key[i] = INFINITY;  // (after every row: higher index)
+  }
+  __syncthreads();
+  for (int k = 2; k <= M; k <<= 1) {
+    for (int s = k >> 1; s > 0; s >>= 1) {
+      for (int e = threadIdx.x; e < M / 2; e += blockDim.x) {
+        const int i = 2 * e - (e & (s - 1)), j = i + s;  // i has bit s clear
+        const double a = key[i], b = key[j];
+        const int ia = perm[i], ib = perm[j];
+        const bool gt = a > b || (a == b && ia > ib);
+        if (gt == ((i & k) == 0)) {
+          key[i] = b;
+          key[j] = a;
+          perm[i] = ib;
+          perm[j] = ia;
+        }
+      }
+      // exchanges at a distance of at most 64 stay within the 128 entries of
+      // one wave; wider ones cross waves (the next distance after 1 is k)
+      if (s > 64 || (s == 1 && k > 64))
+        __syncthreads();
+      else
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+  }
+}
+
+// One generation (Sec. A.3-A.7) for lightcurve blockIdx.x.  Bound by the
+// Philox blocks (ten rounds of two 64-bit products, quarter-rate integer
+// multiplies) and, for small populations, by the length of the chain
+// load - rank - draw - mutate.  Every block of four words is computed once:
+// the tournament words of a pairing one block per thread (their minimum by
+// an LDS atomic), its crossover weights in LDS for both children, the creep
+// and jump words of two genes by the thread that mutates them.  256
+// lightcurves x pop 1000: 252 -> 67 us a call; a fit of one lightcurve, pop
+// 48: 72 -> 54 us a generation, fitness included (before: one thread per
+// pairing and a Philox block for every word).
+__global__ __launch_bounds__(1024) void ea_generation_kernel(
+    EaParams p, double* P, EaLc* lcs, const double* chi2, const double* Fs, const double* Fb,
+    int32_t* parents_out, Proposals pr) {
   extern __shared__ double smem[];
-  const int N = p.pop;
-  double* sP = smem;                         // [6][N] old population
-  double* key = sP + SBLM_NPAR * N;          // [N]
-  int* perm = (int*)(key + N);               // [N] rank -> row
+  const int N = p.pop, npair = N / 2, nt = p.n_tourn;
+  const int Nr = rank_room(N);
+  double* sP = smem;                            // [6][N] old population
+  double* key = sP + SBLM_NPAR * N;             // [Nr]
+  double* wgt = key + Nr;                       // [6][npair] crossover weights
+  int* perm = (int*)(wgt + SBLM_NPAR * npair);  // [Nr] rank -> row
+  int* par = perm + Nr;                         // [2][npair] parent ranks
   __shared__ double s_pmut;
   __shared__ int s_restart;
 
@@ -228,58 +308,92 @@ __global__ void ea_generation_kernel(EaParams p, double* P, EaLc* lcs,
   const int64_t base = lc * N;
   EaLc& st = lcs[lc];
   const int64_t gen = st.gen;
-  const Stream rs = {p.seed, (uint64_t)lc, (uint64_t)gen};
+  const uint64_t ulc = (uint64_t)lc, ugen = (uint64_t)gen;
+  // the record's fields that thread 0 needs after the ranking (loads in
+  // flight meanwhile)
+  const int W = p.window;
+  double r_best = 0.0, r_old = 0.0, r_pmut = 0.0;
+  int64_t r_gen0 = 0;
+  int r_stag = 0;
+  if (threadIdx.x == 0) {
+    r_best = st.best_chi2;
+    r_pmut = st.p_mut;
+    r_gen0 = st.gen_restart;
+    r_stag = st.stag_count;
+    r_old = st.hist[(gen + 1) % (W + 1)];  // generation gen - W
+  }
 
-  for (int i = threadIdx.x; i < N; i += blockDim.x) {
-    key[i] = rank_key(chi2[base + i]);
+  for (int i = threadIdx.x; i < N; i += blockDim.x) key[i] = rank_key(chi2[base + i]);
+  for (int i = threadIdx.x; i < N; i += blockDim.x)
+#pragma unroll
     for (int g = 0; g < SBLM_NPAR; ++g) sP[g * N + i] = P[g * p.n_ind + base + i];
-  }
+  for (int i = threadIdx.x; i < 2 * npair; i += blockDim.x) par[i] = N;
   __syncthreads();
-  // (A.3) stable counting rank
-  for (int i = threadIdx.x; i < N; i += blockDim.x) {
-    const double ki = key[i];
-    int r = 0;
-    for (int j = 0; j < N; ++j) {
-      const double kj = key[j];
-      r += (kj < ki || (kj == ki && j < i)) ? 1 : 0;
+  // (A.4) tournaments: parent rank = min of nt draws from {0..N-1}; words 0
+  // .. nt-1 choose the first parent, nt .. 2 nt - 1 the second
+  const int nq = (2 * nt + 3) / 4;
+  for (int e = threadIdx.x; e < npair * nq; e += blockDim.x) {
+    const int q = e / npair, k = e - q * npair;
+    const u64x4 w = philox4x64_10(ugen, P_TOURN, (uint64_t)k, (uint64_t)q, p.seed, ulc);
+    int ra = N, rb = N;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const int j = 4 * q + m, x = (int)below(w.v[m], (uint32_t)N);
+      if (j < nt)
+        ra = x < ra ? x : ra;
+      else if (j < 2 * nt)
+        rb = x < rb ? x : rb;
     }
-    perm[r] = i;
+    if (ra < N) atomicMin(&par[k], ra);
+    if (rb < N) atomicMin(&par[npair + k], rb);
   }
-  __syncthreads();
+  // (A.5) weighting mode of every pairing: U(0,1), Bin(1,1/2) or ones
+  for (int k = blockDim.x - 1 - threadIdx.x; k < npair; k += blockDim.x) {
+    const u64x4 mb0 = philox4x64_10(ugen, P_MODE, (uint64_t)k, 0, p.seed, ulc);
+    const u64x4 mb1 = philox4x64_10(ugen, P_MODE, (uint64_t)k, 1, p.seed, ulc);
+    const int mode = (int)below(mb0.v[0], 3u);
+#pragma unroll
+    for (int g = 0; g < SBLM_NPAR; ++g) {
+      const uint64_t x = (g < 3) ? mb0.v[1 + g] : mb1.v[g - 3];
+      wgt[g * npair + k] = (mode == 0) ? u01(x) : (mode == 1 ? ((x >> 63) ? 1.0 : 0.0) : 1.0);
+    }
+  }
+  // (A.3) stable rank
+  rank_rows(key, perm, N);
 
   if (threadIdx.x == 0) {
     const int top = perm[0];
-    const double b = key[top];
-    s_pmut = st.p_mut;  // mutation of this generation uses the current value
-    if (b < st.best_chi2) {
+    const double b = key[N <= EA_COUNT_RANK ? top : 0];
+    s_pmut = r_pmut;  // mutation of this generation uses the current value
+    if (b < r_best) {
       st.best_chi2 = b;
       st.best_Fs = Fs[base + top];
       st.best_Fb = Fb[base + top];
       for (int g = 0; g < SBLM_NPAR; ++g) st.best_p[g] = sP[g * N + top];
       st.best_gen = gen;
     }
-    const int W = p.window;
     st.hist[gen % (W + 1)] = b;
     // (A.7) stagnation test on the best chi^2 of `window` generations ago
     int restart = 0;
-    if (gen - st.gen_restart >= W) {
-      const double old = st.hist[(gen - W) % (W + 1)];
+    if (gen - r_gen0 >= W) {
       const bool improved =
-          isinf(old) ? (b < old) : ((old - b) > p.stag_frac * old);
+          isinf(r_old) ? (b < r_old) : ((r_old - b) > p.stag_frac * r_old);
       if (improved) {
-        st.p_mut = fmax(0.5 * st.p_mut, p.p_mut_min);
-        st.stag_count = 0;
+        r_pmut = fmax(0.5 * r_pmut, p.p_mut_min);
+        r_stag = 0;
       } else {
-        st.p_mut = fmin(1.5 * st.p_mut, p.p_mut_max);
-        st.stag_count += 1;
+        r_pmut = fmin(1.5 * r_pmut, p.p_mut_max);
+        r_stag += 1;
       }
-      if (st.stag_count >= p.restart_after) {
+      if (r_stag >= p.restart_after) {
         restart = 1;
-        st.p_mut = p.p_mut0;
-        st.stag_count = 0;
+        r_pmut = p.p_mut0;
+        r_stag = 0;
         st.gen_restart = gen + 1;
         st.n_restarts += 1;
       }
+      st.p_mut = r_pmut;
+      st.stag_count = r_stag;
     }
     st.gen = gen + 1;
     s_restart = restart;
@@ -295,58 +409,37 @@ __global__ void ea_generation_kernel(EaParams p, double* P, EaLc* lcs,
     return;
   }
   const double pm = s_pmut;
-  if (threadIdx.x == 0) {  // (A.5) elitism: row 0 keeps the fittest
-    for (int g = 0; g < SBLM_NPAR; ++g)
-      P[g * p.n_ind + base] = sP[g * N + perm[0]];
+  if (threadIdx.x < SBLM_NPAR) {  // (A.5) elitism: row 0 keeps the fittest
+    const int g = threadIdx.x;
+    P[g * p.n_ind + base] = sP[g * N + perm[0]];
   }
-  const int npair = N / 2;
-  const int nt = p.n_tourn;
-  for (int k = threadIdx.x; k < npair; k += blockDim.x) {
-    // (A.4) tournaments: parent rank = min of nt draws from {0..N-1}
-    int ra = N, rb = N;
-    for (int m = 0; m < nt; ++m) {
-      const int x = (int)below(rs.draw(P_TOURN, (uint64_t)k, (uint64_t)m), (uint32_t)N);
-      const int y =
-          (int)below(rs.draw(P_TOURN, (uint64_t)k, (uint64_t)(nt + m)), (uint32_t)N);
-      ra = x < ra ? x : ra;
-      rb = y < rb ? y : rb;
+  if (parents_out)
+    for (int k = threadIdx.x; k < npair; k += blockDim.x) {
+      parents_out[lc * 2 * npair + 2 * k] = par[k];
+      parents_out[lc * 2 * npair + 2 * k + 1] = par[npair + k];
     }
-    if (parents_out) {
-      parents_out[lc * 2 * npair + 2 * k] = ra;
-      parents_out[lc * 2 * npair + 2 * k + 1] = rb;
-    }
-    const int ia = perm[ra], ib = perm[rb];
-    // (A.5) weighting mode for this pairing: U(0,1), Bin(1,1/2) or ones
-    const u64x4 mb0 = philox4x64_10(gen, P_MODE, (uint64_t)k, 0, p.seed, (uint64_t)lc);
-    const u64x4 mb1 = philox4x64_10(gen, P_MODE, (uint64_t)k, 1, p.seed, (uint64_t)lc);
-    const int mode = (int)below(mb0.v[0], 3u);
-    const int s1 = 2 * k + 1, s2 = 2 * k + 2;
-    for (int g = 0; g < SBLM_NPAR; ++g) {
-      const int j = 1 + g;
-      const uint64_t x = (j < 4) ? mb0.v[j] : mb1.v[j - 4];
-      const double f = (mode == 0) ? u01(x) : (mode == 1 ? ((x >> 63) ? 1.0 : 0.0) : 1.0);
-      const double omf = 1.0 - f;
-      const double pa = sP[g * N + ia], pb = sP[g * N + ib];
-      double child[2];
-      child[0] = clamp01(fma(f, pa, omf * pb));
-      child[1] = clamp01(fma(f, pb, omf * pa));
-      for (int c = 0; c < 2; ++c) {
-        const int slot = c ? s2 : s1;
-        if (slot >= N) continue;
-        // (A.6) creep: p -> p + (1-p) X or p - p X, ln X ~ U(ln 2^-52, 0)
-        double v = child[c];
-        const u64x4 cb = philox4x64_10(gen, P_CREEP, (uint64_t)slot,
-                                       (uint64_t)((2 * g) >> 2), p.seed, (uint64_t)lc);
-        const uint64_t xs = cb.v[(2 * g) & 3], xu = cb.v[(2 * g + 1) & 3];
-        const double X = exp2_neg(52.0 * u01(xu));
-        v = (xs >> 63) ? fma(1.0 - v, X, v) : fma(-v, X, v);
-        v = clamp01(v);
-        // (A.6) jump: with probability p_mut replace by a fresh uniform
-        const u64x4 jb = philox4x64_10(gen, P_JUMP, (uint64_t)slot,
-                                       (uint64_t)((2 * g) >> 2), p.seed, (uint64_t)lc);
-        if (u01(jb.v[(2 * g) & 3]) < pm) v = u01(jb.v[(2 * g + 1) & 3]);
-        P[g * p.n_ind + base + slot] = v;
-      }
+  // offspring 2k+1, 2k+2 of pairing k, genes 2h and 2h+1 per thread
+  const int n_off = 2 * npair < N - 1 ? 2 * npair : N - 1;
+  for (int e = threadIdx.x; e < 3 * n_off; e += blockDim.x) {
+    const int h = e / n_off, slot = 1 + e - h * n_off;
+    const int k = (slot - 1) >> 1;
+    const bool second = ((slot - 1) & 1) != 0;
+    const int ia = perm[par[k]], ib = perm[par[npair + k]];
+    const u64x4 cb = philox4x64_10(ugen, P_CREEP, (uint64_t)slot, (uint64_t)h, p.seed, ulc);
+    const u64x4 jb = philox4x64_10(ugen, P_JUMP, (uint64_t)slot, (uint64_t)h, p.seed, ulc);
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+      const int g = 2 * h + m;
+      const double f = wgt[g * npair + k], omf = 1.0 - f;
+      const double pa = sP[g * N + (second ? ib : ia)], pb = sP[g * N + (second ? ia : ib)];
+      double v = clamp01(fma(f, pa, omf * pb));
+      // (A.6) creep: p -> p + (1-p) X or p - p X, ln X ~ U(ln 2^-52, 0)
+      const double X = exp2_neg(52.0 * u01(cb.v[2 * m + 1]));
+      v = (cb.v[2 * m] >> 63) ? fma(1.0 - v, X, v) : fma(-v, X, v);
+      v = clamp01(v);
+      // (A.6) jump: with probability p_mut replace by a fresh uniform
+      if (u01(jb.v[2 * m]) < pm) v = u01(jb.v[2 * m + 1]);
+      P[g * p.n_ind + base + slot] = v;
     }
   }
 }
@@ -523,12 +616,19 @@ __global__ void queue_reset_kernel(unsigned int* q) {
 }
 
 static size_t gen_smem(int pop) {
-  return (size_t)pop * (SBLM_NPAR * sizeof(double) + sizeof(double) + sizeof(int));
+  const size_t half = pop / 2, room = rank_room(pop);
+  return SBLM_NPAR * (pop + half) * sizeof(double) + room * (sizeof(double) + sizeof(int)) +
+         2 * half * sizeof(int);
 }
 
+// Threads of a generation's block: one per (offspring, two genes) task up to
+// 256, where several blocks share a compute unit; 512 and 1024 for the
+// populations whose LDS (45 KB at 512, 90 KB at 1024) leaves room for two
+// blocks or one.
 static int gen_block(int pop) {
   int b = 64;
-  while (b < pop / 2 && b < 256) b *= 2;
+  while (b < 3 * pop && b < 256) b *= 2;
+  while (b < pop && b < 1024) b *= 2;
   return b;
 }
 
@@ -737,6 +837,16 @@ extern "C" int ea_create(const ea_config* cfg, const sblm_lcs* lcs, uint64_t see
   // the four waves of a block on the one-shot grid.
   s.lanes = default_lanes(p.n_ind);
   if (s.lanes > 64) s.persistent = 0;
+  if (gen_smem(p.pop) > (64u << 10)) {
+    rc = check_hip(hipFuncSetAttribute((const void*)ea_generation_kernel,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)gen_smem(p.pop)),
+                   "ea_create: LDS");
+    if (rc) {
+      ea_destroy(st);
+      return rc;
+    }
+  }
   const size_t nb = (size_t)p.n_ind * sizeof(double);
   // longest-processing-time order of the work items: lightcurves by length,
   // longest first (stable), the individuals of each lightcurve (all its

@@ -23,13 +23,14 @@ __device__ __forceinline__ u64x4 philox4x64_10(uint64_t c0, uint64_t c1,
   const uint64_t W0 = 0x9E3779B97F4A7C15ULL, W1 = 0xBB67AE8584CAA73BULL;
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
-    const uint64_t lo0 = M0 * c0, hi0 = __umul64hi(M0, c0);
-    const uint64_t lo1 = M1 * c2, hi1 = __umul64hi(M1, c2);
-    const uint64_t n0 = hi1 ^ c1 ^ k0, n2 = hi0 ^ c3 ^ k1;
+    // (one 128-bit product: the low and the high word share their partial
+    // products)
+    const unsigned __int128 p0 = (unsigned __int128)M0 * c0, p1 = (unsigned __int128)M1 * c2;
+    const uint64_t n0 = (uint64_t)(p1 >> 64) ^ c1 ^ k0, n2 = (uint64_t)(p0 >> 64) ^ c3 ^ k1;
     c0 = n0;
-    c1 = lo1;
+    c1 = (uint64_t)p1;
     c2 = n2;
-    c3 = lo0;
+    c3 = (uint64_t)p0;
     k0 += W0;
     k1 += W1;
   }

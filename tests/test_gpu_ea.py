@@ -97,6 +97,36 @@ def test_init_and_generations_bit_exact(hip, pop):
     assert all(ea.summary()["n_restarts"] >= 1 for ea in eas)
 
 
+@pytest.mark.parametrize("pop", [2, 3, 21, 85, 255, 256, 257, 511, 512, 513, 1000, 1023, 1024])
+def test_generation_bit_exact_at_size_edges(hip, pop):
+    # the smallest populations, both sides of the sizes at which the block
+    # grows and the counting rank gives way to the sort, and the largest:
+    # ties, NaN and inf among the keys, one generation of distinct keys, then
+    # (constant fitness) up to a restart
+    wl = csr_workload(5, [20, 30])
+    st, _, _ = _make_state(hip, wl, pop, seed=77)
+    eas = _oracle_eas(2, pop, 77)
+    rng = np.random.default_rng(pop)
+    for g in range(24):
+        chi2 = rng.uniform(10, 1000, 2 * pop)
+        if g == 1:
+            chi2 = np.floor(chi2 / 100)  # many ties
+        if g == 2:
+            chi2[rng.random(2 * pop) < 0.3] = np.nan
+            chi2[rng.random(2 * pop) < 0.3] = np.inf
+        if g > 2:
+            chi2 = np.full(2 * pop, 5.0)
+        Fs, Fb = rng.uniform(0.5, 1.5, 2 * pop), rng.uniform(0, 0.5, 2 * pop)
+        st.generation(_cuda(chi2), _cuda(Fs), _cuda(Fb))
+        for lc, ea in enumerate(eas):
+            ea.generation(chi2[lc * pop:(lc + 1) * pop], Fs[lc * pop:(lc + 1) * pop],
+                          Fb[lc * pop:(lc + 1) * pop])
+        if g in (0, 1, 2, 3, 23):
+            _compare(hip, st, eas, pop)
+    assert all(ea.summary()["n_restarts"] >= 1 for ea in eas)
+    st.close()
+
+
 def test_fit_graph_equals_stepping_and_oracle(hip):
     # ea_fit (graph replay of evaluate + generation) must equal stepping
     # generation by generation with sblm_chi2 on the decoded population, and
