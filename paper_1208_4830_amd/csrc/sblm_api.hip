@@ -25,19 +25,18 @@ int check_hip(hipError_t e, const char* what) {
   return set_error(SBLM_EDEVICE, "%s: %s", what, hipGetErrorString(e));
 }
 
-// Lanes per individual of the stateless calls: the rule of the EA states
-// (default_lanes), so that sblm_chi2 of a population equals the state's own
-// evaluation bit for bit.  Overridable with SBLM_LANES (8 ... 256) for tuning
-// runs.
-static int choose_group(int64_t n_ind) {
+// Lanes per individual of the stateless calls: for sblm_chi2 the rule of the
+// EA states (default_lanes), so that it equals the state's own evaluation bit
+// for bit, for sblm_magnify that of magnify_lanes.  Overridable with
+// SBLM_LANES (a power of two in [least, most]) for tuning runs.
+static int choose_group(int64_t by_rule, int least, int most) {
   const char* env = getenv("SBLM_LANES");
   if (env) {
     int g = atoi(env);
-    if (g == 8 || g == 16 || g == 32 || g == 64 || g == 128 || g == 256) return g;
+    if (g >= least && g <= most && (g & (g - 1)) == 0) return g;
   }
-  return default_lanes(n_ind);
+  return (int)by_rule;
 }
-
 
 // Epoch stepping of the stateless calls: lockstep unless SBLM_ASYNC=1 (the
 // asynchronous form measured slower on the MI355X for 200-5000-epoch
@@ -88,7 +87,7 @@ extern "C" int sblm_magnify(const double* theta, int64_t n, const double* t,
   a.A = A;
   a.n_img = n_img;
   a.stats = stats;
-  a.lanes_per_ind = choose_group(n);
+  a.lanes_per_ind = choose_group(magnify_lanes(n, n_t), 1, 1024);
   a.async = async_stepping() && a.lanes_per_ind <= 64;
   return check_hip(launch_fitness(a, mode, false, (hipStream_t)stream,
                                   block_waves(a.lanes_per_ind)),
@@ -122,7 +121,7 @@ extern "C" int sblm_chi2(const sblm_lcs* lcs, const double* theta, int32_t pop,
   a.Fs = Fs;
   a.Fb = Fb;
   a.stats = stats;
-  a.lanes_per_ind = choose_group(a.n_ind);
+  a.lanes_per_ind = choose_group(default_lanes(a.n_ind), 8, 256);
   a.async = async_stepping() && a.lanes_per_ind <= 64;
   return check_hip(launch_fitness(a, mode, true, (hipStream_t)stream,
                                   block_waves(a.lanes_per_ind)),

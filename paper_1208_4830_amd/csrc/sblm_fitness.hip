@@ -12,8 +12,8 @@
 // weighted linear least squares.
 //
 // Mapping onto CDNA4:
-//   * one group of G lanes (G = 64, 32 or 16) per individual, each lane
-//     owning a contiguous chunk of C = ceil(L/G) epochs; the individual's
+//   * one group of G lanes per individual (8 to 64, several waves up to 256;
+//     magnifications from 1 to as many as there are epochs), each lane owning a contiguous chunk of C = ceil(L/G) epochs; the individual's
 //     parameters are wave-uniform (scalar registers), epochs are read once;
 //   * all five roots are found together by the Ehrlich-Aberth simultaneous
 //     iteration -- branch-free and identical work per lane, so a wavefront
@@ -76,15 +76,82 @@ __device__ __forceinline__ float rcp_hw(float x) { return __builtin_amdgcn_rcpf(
 
 namespace sblm {
 
-// Starting points for a cold solve: five points on a circle about the root
+// Starting points for a cold solve from the limit of a light secondary
+// (float, all lanes the same work).  At q = 0 the lens polynomial factors:
+// the two images z+- of the primary alone, zeta (1 +- sqrt(1 + 4/|zeta|^2))/2,
+// the spurious root 1/(d - conj(zeta)) and a double root at z = d; to first
+// order in q the double root splits into z = d + q d u with
+//   B u^2 + C u + E = 0,  E = zeta - d,  a = 1 + d conj(zeta),  b = a - d^2,
+//   B = b (E a + d),  C = E (a + b) + d.
+// Each start is turned by 1e-4 about the origin: starts on a common symmetry
+// axis could otherwise leave it by rounding only.  Over the prior they take
+// the iteration 2.7 sweeps per solve (7.6 for the slowest of 64), the circle
+// of cold_start 7.8 (12.9); the roots reached are the same.  False when a
+// start is not finite or two of them (nearly) coincide: then the circle.
+__device__ __forceinline__ bool light_secondary_start(cx<double> zeta_, double d_, double q_,
+                                                      cx<float> z[5]) {
+  const float d = (float)d_, q = (float)q_;
+  const cx<float> zt = {(float)zeta_.re, (float)zeta_.im};
+  const float n = c_norm(zt);
+  const float h = 0.5f + 0.5f * __builtin_amdgcn_sqrtf(fmaf(4.0f, rcp_hw(n), 1.0f));
+  const float m = -rcp_hw(n * h);  // z- = -zeta/(|zeta|^2 h)
+  z[0] = {h * zt.re, h * zt.im};
+  z[1] = {m * zt.re, m * zt.im};
+  const cx<float> E = {zt.re - d, zt.im};
+  const float ie = rcp_hw(c_norm(E));  // d - conj(zeta) = -conj(E)
+  z[2] = {-E.re * ie, -E.im * ie};
+  const cx<float> a = {fmaf(d, zt.re, 1.0f), -d * zt.im};
+  const cx<float> b = {fmaf(-d, d, a.re), a.im};
+  const cx<float> Ea = c_mul(E, a);
+  const cx<float> B = c_mul(b, cx<float>{Ea.re + d, Ea.im});
+  const cx<float> Eab = c_fma(E, b, Ea);
+  const cx<float> C = {Eab.re + d, Eab.im};
+  // s = sqrt(C^2 - 4 B E), its sign such that C + s is the larger sum;
+  // u = w/B and E/w with w = -(C + s)/2
+  const cx<float> C2 = c_mul(C, C), BE = c_mul(B, E);
+  const cx<float> D = {fmaf(-4.0f, BE.re, C2.re), fmaf(-4.0f, BE.im, C2.im)};
+  const float r = __builtin_amdgcn_sqrtf(c_norm(D));
+  const float t = __builtin_amdgcn_sqrtf(0.5f * (r + fabsf(D.re)));
+  const float o = t > 0.0f ? 0.5f * D.im * rcp_hw(t) : 0.0f;
+  cx<float> s = D.re >= 0.0f ? cx<float>{t, o} : cx<float>{fabsf(o), copysignf(t, D.im)};
+  if (fmaf(C.re, s.re, C.im * s.im) < 0.0f) s = {-s.re, -s.im};
+  const cx<float> w = {-0.5f * (C.re + s.re), -0.5f * (C.im + s.im)};
+  const float qd = q * d;
+  const float fb = qd * rcp_hw(c_norm(B)), fw = qd * rcp_hw(c_norm(w));
+  z[3] = {fmaf(fb, fmaf(w.re, B.re, w.im * B.im), d), fb * fmaf(w.im, B.re, -w.re * B.im)};
+  z[4] = {fmaf(fw, fmaf(E.re, w.re, E.im * w.im), d), fw * fmaf(E.im, w.re, -E.re * w.im)};
+  const float turn[5] = {1e-4f, -0.7e-4f, 0.8e-4f, 1.3e-4f, -1.1e-4f};
+  float sum = 0.0f, dmin = INFINITY;
+#pragma unroll
+  for (int i = 0; i < 5; ++i) {
+    z[i] = {fmaf(-turn[i], z[i].im, z[i].re), fmaf(turn[i], z[i].re, z[i].im)};
+    sum += fabsf(z[i].re) + fabsf(z[i].im);
+#pragma unroll
+    for (int j = 0; j < i; ++j) dmin = vmin(c_norm(c_sub(z[i], z[j])), dmin);
+  }
+  return sum < 1e12f && dmin > 1e-12f;
+}
+
+// Starting points for a cold solve of the polynomial c of the source zeta and
+// the lens d, q: those of the light-secondary limit where they apply (q <= 2,
+// checked up to there), else five points on a circle about the root
 // centroid -c4/(5 c5) of radius (|c0|/|c5|)^(1/5) (geometric mean of the
 // root moduli); for a degree-4 polynomial four points and one root parked
 // far away, where it never moves; with a far root (far_root) the four near
 // roots start as for the degree-4 polynomial and the fifth at -c4/c5, which
 // it would otherwise take the iteration some 50-80 sweeps to walk out to.
 template <typename T>
-__device__ __forceinline__ void cold_start(const cx<T> c[6], bool deg4,
-                                           cx<T> z[5], bool far = false) {
+__device__ __forceinline__ void cold_start(const cx<T> c[6], cx<double> zeta, double d, double q,
+                                           bool deg4, cx<T> z[5], bool far = false) {
+  const bool four = deg4 || far;
+  if (!four && q <= 2.0) {
+    cx<float> zf[5];
+    if (light_secondary_start(zeta, d, q, zf)) {
+#pragma unroll
+      for (int i = 0; i < 5; ++i) z[i] = {(T)zf[i].re, (T)zf[i].im};
+      return;
+    }
+  }
   // cos/sin of 2 pi k/5 + 0.4 and 2 pi k/4 + 0.4
   const float c5a[5] = {0.92106099f, 0.06083749f, -0.88523008f, -0.62472004f,
                         0.52805164f};
@@ -92,7 +159,6 @@ __device__ __forceinline__ void cold_start(const cx<T> c[6], bool deg4,
                         -0.84920782f};
   const float c4a[4] = {0.92106099f, -0.38941834f, -0.92106099f, 0.38941834f};
   const float s4a[4] = {0.38941834f, 0.92106099f, -0.38941834f, -0.92106099f};
-  const bool four = deg4 || far;
   const int lead = four ? 4 : 5;
   const float n_lead = (float)c_norm(c[lead]);
   const float n_0 = (float)c_norm(c[0]);
@@ -199,14 +265,15 @@ struct LaneStats {
 // accepted images are refined on the lens equation anyway.
 #define SBLM_SETTLED_STEP2 1e-8
 
-// Solve one polynomial from the roots in z (warm) or from a cold start;
+// Solve one polynomial (of the source zeta and the lens d, q) from the roots
+// in z (warm) or from a cold start;
 // ok = converged to finite roots; settled = ok, or capped with finite roots
 // that no longer move (see SBLM_SETTLED_STEP2).  `retry` marks a second,
 // cold attempt at an epoch whose warm-started solve failed (not counted as
 // another solve).
 template <int MODE>
-__device__ __forceinline__ void solve_roots(const cx<double> c[6], bool deg4,
-                                            bool warm, bool active,
+__device__ __forceinline__ void solve_roots(const cx<double> c[6], cx<double> zeta, double d,
+                                            double q, bool deg4, bool warm, bool active,
                                             cx<double> z[5], LaneStats& st,
                                             bool& ok, bool& settled, bool retry = false) {
   constexpr int MAXIT64 = 60, MAXIT32 = 30;
@@ -214,7 +281,7 @@ __device__ __forceinline__ void solve_roots(const cx<double> c[6], bool deg4,
   const double tau64 = SBLM_ROOT_TAU;
   const float tau32 = SBLM_ROOT_TAU32;
   const bool far = !deg4 && far_root(c);
-  if (!warm && active) cold_start<double>(c, deg4, z, far);
+  if (!warm && active) cold_start<double>(c, zeta, d, q, deg4, z, far);
   unsigned int it_lane = 0, it32_lane = 0, it_wave = 0, newton_lane = 0;
   bool done = !active, fell_back = false;
   if (MODE == SBLM_MIXED) {
@@ -274,7 +341,7 @@ __device__ __forceinline__ void solve_roots(const cx<double> c[6], bool deg4,
       bool apart = true;
 #pragma unroll
       for (int i = 0; i < 5; ++i) apart = apart && (d2n[i] >= 0.25 * d2[i]);
-      if (!apart) cold_start<double>(c, deg4, z, far);
+      if (!apart) cold_start<double>(c, zeta, d, q, deg4, z, far);
       done = pol_done && apart;
       fell_back = !done;
     }
@@ -314,8 +381,9 @@ __device__ __forceinline__ void solve_roots(const cx<double> c[6], bool deg4,
 // warm start from the roots of another epoch or, in the simplex rounds, of
 // another point), called by the whole wave when any lane needs it; lanes
 // with active = 0 only follow along.  Kept out of line: a second inlined
-// copy of the iteration would cost the hot path registers.  Coefficients,
-// roots (in and out) and the lane's counters travel through memory.
+// copy of the iteration would cost the hot path registers.  Coefficients (then
+// the source position, d and q), roots (in and out) and the lane's counters
+// travel through memory.
 template <int MODE>
 __device__ __noinline__ void cold_retry(const double* cr, double* zr, int deg4, int active,
                                         unsigned int* counts) {
@@ -324,7 +392,8 @@ __device__ __noinline__ void cold_retry(const double* cr, double* zr, int deg4, 
   for (int i = 0; i < 5; ++i) z[i] = {zr[2 * i], zr[2 * i + 1]};
   LaneStats st = {};
   bool ok, settled;
-  solve_roots<MODE>(c, deg4 != 0, false, active != 0, z, st, ok, settled, true);
+  solve_roots<MODE>(c, {cr[12], cr[13]}, cr[14], cr[15], deg4 != 0, false, active != 0, z, st, ok,
+                    settled, true);
   for (int i = 0; i < 5; ++i) {
     zr[2 * i] = z[i].re;
     zr[2 * i + 1] = z[i].im;
@@ -336,10 +405,6 @@ __device__ __noinline__ void cold_retry(const double* cr, double* zr, int deg4, 
   counts[4] = st.fallback;
   counts[5] = (ok ? 1u : 0u) | (settled ? 2u : 0u);
 }
-
-#ifndef SBLM_MIN_WAVES_PER_EU
-#define SBLM_MIN_WAVES_PER_EU 1
-#endif
 
 // Per-lane context of one work item: the individual, its parameters and the
 // lane's chunk [k0, k1) of the lightcurve's epochs.
@@ -366,12 +431,21 @@ __device__ __noinline__ ItemTrig item_trig(double lq, double alpha, double tE) {
   return r;
 }
 
+// Value of G for magnifications spread over any number of waves.
+constexpr int WIDE = 1 << 20;
+
 template <int G>
 __device__ __forceinline__ Item item_setup(const FitArgs& a, int64_t wave_item) {
   Item x;
   const int lane = threadIdx.x & 63;
   int64_t item;
-  if constexpr (G > 64) {  // G / 64 waves per individual: wave item = (individual, part)
+  int64_t lanes = G;
+  if constexpr (G == WIDE) {  // as below, the number of waves set at run time
+    lanes = a.lanes_per_ind;
+    const int64_t parts = lanes / 64;
+    item = wave_item / parts;
+    x.gl = (int)(wave_item - item * parts) * 64 + lane;
+  } else if constexpr (G > 64) {  // G / 64 waves per individual: wave item = (individual, part)
     item = wave_item / (G / 64);
     x.gl = (int)(wave_item % (G / 64)) * 64 + lane;
   } else {
@@ -405,7 +479,7 @@ __device__ __forceinline__ Item item_setup(const FitArgs& a, int64_t wave_item) 
   if (!x.valid) e1 = e0;
   x.e0 = e0;
   const int64_t L = e1 - e0;
-  x.Cg = (L + G - 1) / G;
+  x.Cg = (L + lanes - 1) / lanes;
   x.C = x.Cg;
 #pragma unroll
   for (int o = G; o < 64; o <<= 1) {
@@ -608,20 +682,24 @@ __device__ __forceinline__ void fit_wave(const FitArgs& a, int64_t wave_item,
       }
     }
     bool ok, settled;
-    solve_roots<MODE>(c, deg4, warm, active, z, st, ok, settled);
+    solve_roots<MODE>(c, zeta, d, q, deg4, warm, active, z, st, ok, settled);
     {
       // a warm start that did not converge: solve again from the cold
       // start; roots that still have not settled poison the result (A and
       // with it chi^2 become NaN, which ranks last)
       const bool again = active && !ok && warm;
       if (__any(again)) {
-        double cr[12], zr[10];
+        double cr[16], zr[10];
         unsigned int cnt[6];
 #pragma unroll
         for (int j = 0; j < 6; ++j) {
           cr[2 * j] = c[j].re;
           cr[2 * j + 1] = c[j].im;
         }
+        cr[12] = zeta.re;
+        cr[13] = zeta.im;
+        cr[14] = d;
+        cr[15] = q;
 #pragma unroll
         for (int i = 0; i < 5; ++i) {
           zr[2 * i] = z[i].re;
@@ -749,7 +827,7 @@ __device__ __forceinline__ void fit_wave_async(const FitArgs& a, int64_t wave_it
           t3 = t2;
           t2 = t1;
         } else {
-          cold_start<double>(c, deg4, z, !deg4 && far_root(c));
+          cold_start<double>(c, zeta, x.d, x.q, deg4, z, !deg4 && far_root(c));
         }
         phase = (MODE == SBLM_MIXED) && !deg4 && !far_root(c) ? (warm ? 1 : 0) : 2;
         if (phase == 1) nearest2(z, d2);
@@ -792,7 +870,7 @@ __device__ __forceinline__ void fit_wave_async(const FitArgs& a, int64_t wave_it
           bool apart = true;
 #pragma unroll
           for (int i = 0; i < 5; ++i) apart = apart && (d2n[i] >= 0.25 * d2[i]);
-          if (!apart) cold_start<double>(c, deg4, z, false);
+          if (!apart) cold_start<double>(c, zeta, x.d, x.q, deg4, z, false);
           if (pol && apart) {
             conv = true;
             finished = true;
@@ -816,7 +894,7 @@ __device__ __forceinline__ void fit_wave_async(const FitArgs& a, int64_t wave_it
         if (!(conv && finite) && warm && !retried) {
           // the warm-started solve failed: again from the cold start (see
           // the lockstep form)
-          cold_start<double>(c, deg4, z, !deg4 && far_root(c));
+          cold_start<double>(c, zeta, x.d, x.q, deg4, z, !deg4 && far_root(c));
           warm = false;
           retried = true;
           phase = (MODE == SBLM_MIXED) && !deg4 && !far_root(c) ? 0 : 2;
@@ -875,11 +953,11 @@ __device__ __forceinline__ void fit_wave_async(const FitArgs& a, int64_t wave_it
 }
 
 // PERSIST = 0: one-shot grid.  PERSIST = 1: persistent grid fed by a work
-// counter; its loop keeps the kernel arguments live, so it is compiled for
-// two waves per SIMD (a few bytes of spill) instead of letting scalar-register
-// spills push it to one.
+// counter.  All forms are compiled for two waves per SIMD: left alone, the
+// mixed form takes 272 registers and runs one, where its dependent FP64
+// chains leave the SIMD idle half of the time.
 template <int MODE, bool CHI2, int G, int PERSIST, int ASYNC>
-__global__ __launch_bounds__(256, PERSIST ? 2 : SBLM_MIN_WAVES_PER_EU) void fitness_kernel(
+__global__ __launch_bounds__(256, 2) void fitness_kernel(
     FitArgs a) {
   // (blocks of at most 256 threads: launch_gg refuses larger ones)
   constexpr int GPW = G > 64 ? 1 : 64 / G;  // individuals per wave
@@ -971,10 +1049,10 @@ template <int MODE, bool CHI2, int G>
 static hipError_t launch_gg(const FitArgs& a, hipStream_t s, int wpb) {
   if (wpb < 1 || 64 * wpb > SBLM_FIT_MAX_THREADS) return hipErrorInvalidConfiguration;
   if constexpr (G > 64) {
-    // several waves per individual: one-shot grid, lockstep, whole
-    // individuals in every block (for chi^2 their waves meet at the merge)
-    constexpr int P = G / 64;
-    if (a.queue || a.async || wpb % P != 0) return hipErrorInvalidConfiguration;
+    // several waves per individual: one-shot grid, lockstep; for chi^2, where
+    // they meet at the merge, whole individuals in every block
+    const int P = (G == WIDE ? a.lanes_per_ind : G) / 64;
+    if (a.queue || a.async || (CHI2 && wpb % P != 0)) return hipErrorInvalidConfiguration;
     const size_t smem = ROOT_HIST_BYTES * 64 * wpb + 6 * sizeof(double) * wpb;
     const int64_t nblk = (a.n_ind * P + wpb - 1) / wpb;
     if (nblk <= 0) return hipSuccess;
@@ -986,9 +1064,11 @@ static hipError_t launch_gg(const FitArgs& a, hipStream_t s, int wpb) {
     const int64_t groups_per_block = (int64_t)wpb * (64 / G);
     int64_t nblk = (a.n_ind + groups_per_block - 1) / groups_per_block;
     if (nblk <= 0) return hipSuccess;
-    auto kern = a.async ? (a.queue ? fitness_kernel<MODE, CHI2, G, 1, 1>
+    if (!CHI2 && a.queue) return hipErrorInvalidConfiguration;
+    constexpr int PF = CHI2 ? 1 : 0;  // (magnifications: the one-shot grid only)
+    auto kern = a.async ? (a.queue ? fitness_kernel<MODE, CHI2, G, PF, 1>
                                    : fitness_kernel<MODE, CHI2, G, 0, 1>)
-                        : (a.queue ? fitness_kernel<MODE, CHI2, G, 1, 0>
+                        : (a.queue ? fitness_kernel<MODE, CHI2, G, PF, 0>
                                    : fitness_kernel<MODE, CHI2, G, 0, 0>);
     if (a.queue) {  // persistent grid: as many blocks as can be resident
       int dev = 0, ncu = 0, per_cu = 0;
@@ -1007,11 +1087,21 @@ static hipError_t launch_gg(const FitArgs& a, hipStream_t s, int wpb) {
 
 template <int MODE, bool CHI2>
 static hipError_t launch_g(const FitArgs& a, hipStream_t s, int wpb) {
-  if (a.lanes_per_ind == 256) return launch_gg<MODE, CHI2, 256>(a, s, wpb);
-  if (a.lanes_per_ind == 128) return launch_gg<MODE, CHI2, 128>(a, s, wpb);
+  if constexpr (CHI2) {
+    if (a.lanes_per_ind == 256) return launch_gg<MODE, CHI2, 256>(a, s, wpb);
+    if (a.lanes_per_ind == 128) return launch_gg<MODE, CHI2, 128>(a, s, wpb);
+  } else {
+    if (a.lanes_per_ind > 64 && a.lanes_per_ind % 64 == 0)
+      return launch_gg<MODE, CHI2, WIDE>(a, s, wpb);
+  }
   if (a.lanes_per_ind == 64) return launch_gg<MODE, CHI2, 64>(a, s, wpb);
   if (a.lanes_per_ind == 32) return launch_gg<MODE, CHI2, 32>(a, s, wpb);
   if (a.lanes_per_ind == 8) return launch_gg<MODE, CHI2, 8>(a, s, wpb);
+  if constexpr (!CHI2) {
+    if (a.lanes_per_ind == 4) return launch_gg<MODE, CHI2, 4>(a, s, wpb);
+    if (a.lanes_per_ind == 2) return launch_gg<MODE, CHI2, 2>(a, s, wpb);
+    if (a.lanes_per_ind == 1) return launch_gg<MODE, CHI2, 1>(a, s, wpb);
+  }
   return launch_gg<MODE, CHI2, 16>(a, s, wpb);
 }
 

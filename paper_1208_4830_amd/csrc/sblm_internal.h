@@ -3,6 +3,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 
 #include "../../include/sblm.h"
@@ -45,7 +46,8 @@ struct FitArgs {
   int64_t cold_per;
   int32_t lanes_per_ind;  // 64, 32, 16 or 8 (a power of two dividing 64), or
                           // 128 / 256: several waves per individual (one-shot
-                          // lockstep, wpb a multiple of G/64)
+                          // lockstep, wpb a multiple of G/64); magnifications
+                          // also 1, 2, 4 or any multiple of 64
   unsigned int* queue;    // nullable: persistent launch; one shared work
                           // counter, or with xcd_start one per XCD (8)
   const int64_t* xcd_start;  // nullable: [9] order positions; the items at
@@ -73,6 +75,35 @@ inline int default_lanes(int64_t n_ind) {
   for (int g = 8; g < 64; g *= 2)
     if (n_ind * g >= 8 * RESIDENT) return g;
   return 64;
+}
+
+// Lanes per individual for the magnifications of n individuals at n_t shared
+// epochs, where no sum over the epochs ties the lanes together: the number of
+// lowest modelled time, the fewest among equals.  A lane's chain of C epochs
+// costs 2.5 for the cold start and w for every warm one, w = 1 for dense
+// epochs, more (a poorer extrapolation) for few.  The n G lanes are r = n G /
+// 2^17 residencies of the chip; below one residency only the chain's length
+// counts (a little slower when waves share a SIMD), above it the work grows
+// with r and more, shorter waves even out what the slowest lane of each
+// holds up (the factor, fitted to 1 <= r <= 32 at 4096 x 1000).  In us at G
+// lanes against the rule's choice: 2^20 single epochs 1660 (8), 187 (1); one
+// curve of 1000 epochs 21 (256), 11 (1024); 16384 x 256 470 (8), 442 (32);
+// 4096 x 1000 405 (32), 347 (128); 10^5 x 4 135 (8), 85 (4); 16 x 5000 131
+// (256), 30 (8192); 65536 x 256 1601 (64), 1507 (16).
+inline int64_t magnify_lanes(int64_t n, int64_t n_t) {
+  const double w = 1.0 + fmin(1.5, 12.0 / (double)n_t);
+  int64_t best = 1;
+  double best_cost = 0.0;
+  for (int64_t g = 1;; g *= 2) {
+    const double r = (double)n * (double)g / (double)(2048 * 64);
+    const double chain = 2.5 + w * (double)((n_t + g - 1) / g - 1);
+    const double cost = chain * (r < 1.0 ? 1.3 + 0.8 * r : r + 1.1 * sqrt(r));
+    if (g == 1 || cost < best_cost) {
+      best = g;
+      best_cost = cost;
+    }
+    if (g >= n_t) return best;
+  }
 }
 
 hipError_t launch_fitness(const FitArgs& a, int mode, bool chi2,

@@ -68,6 +68,33 @@ def test_magnify_small_and_tail_shapes(hip, mode):
                                                                      device=DEV), A=A)
 
 
+@pytest.mark.parametrize("n,n_t", [(70001, 1), (70001, 2), (40000, 3), (20000, 9), (9001, 33),
+                                   (3001, 65), (301, 200), (7, 700), (1, 1000), (1, 1025)])
+def test_magnify_lanes_by_shape(hip, n, n_t):
+    # few epochs of many individuals (one to a few lanes each, partly empty
+    # last waves) up to many epochs of one (a lane per epoch, several waves):
+    # the magnification of a pair does not depend on the split
+    rng = np.random.default_rng(n_t)
+    theta = inputs.draw_theta(rng, n)
+    t = np.sort(rng.uniform(-150, 150, n_t))
+    _check_magnify(hip, theta, t, 0, 1e-10)
+
+
+def test_magnify_cold_starts_on_symmetry_axes(hip):
+    # sources on the lens axis and on the axis perpendicular to it (u0 = 0,
+    # alpha a multiple of pi/2), single epochs, so that every solve starts
+    # cold with starts on a symmetry axis of the polynomial's roots
+    rng = np.random.default_rng(105)
+    n = 3000
+    theta = inputs.draw_theta(rng, n)
+    theta[2] = 0.0
+    theta[3] = rng.choice([0.0, np.pi / 2, np.pi, 1.5 * np.pi], n)
+    theta[5] = -rng.uniform(-2, 2, n) * theta[4]
+    for mode, floor in ((0, 1e-10), (1, 1e-6)):
+        _, s = _check_magnify(hip, theta, np.zeros(1), mode, floor)
+        assert s["n_unsettled"] == 0
+
+
 def test_magnify_source_on_primary(hip):
     # u0 = 0 and t = t0: zeta = 0, the leading coefficient vanishes (degree 4)
     theta = np.array([[-1.0], [1.2], [0.0], [0.3], [20.0], [1.5]])
