@@ -88,6 +88,29 @@ def test_resample_matches_oracle(hip):
     assert torch.equal(xb.cpu(), torch.from_numpy(xf.astype(np.float32)).to(torch.bfloat16))
 
 
+def test_resample_chunks_and_gaps(hip):
+    # lengths on both sides of the epochs staged at a time (1024), a dense run
+    # that fills one bin across several chunks, and long empty stretches
+    rng = np.random.default_rng(8)
+    ts = [np.sort(rng.uniform(0, 50, n)) for n in (1023, 1024, 1025, 2048, 2049, 6000)]
+    ts.append(np.sort(np.concatenate([[0.0, 100.0], rng.uniform(30.0, 30.3, 3000)])))
+    ts.append(np.array([0.0, 0.1, 0.2, 99.7, 100.0]))
+    ys = [rng.uniform(1, 4, t.size) for t in ts]
+    ws = [rng.uniform(1, 9, t.size) for t in ts]
+    ws[2][:700] = 0.0  # the first bins without weight
+    ws[3][-700:] = 0.0  # and the last
+    off = np.zeros(len(ts) + 1, np.int64)
+    off[1:] = np.cumsum([t.size for t in ts])
+    dev = lambda a, dt=torch.float64: torch.tensor(a, dtype=dt, device="cuda")
+    lcs = hip.Lightcurves(dev(off, torch.int64), dev(np.concatenate(ts)),
+                          dev(np.concatenate(ys)), dev(np.concatenate(ws)))
+    _, xf = hip.sblm_resample(lcs, want_f32=True, want_bf16=False)
+    xf = xf.cpu().numpy().astype(np.float64)
+    for k, t in enumerate(ts):
+        ref = M.resample(t, ys[k], ws[k])
+        assert np.all(np.abs(xf[k] - ref) <= 1.2e-7 * np.abs(ref) + 1e-30), k
+
+
 def test_training_samples_match_oracle(hip):
     seed, first, n = 1234, 50, 12
     xb, xf, y = hip.mlp_make_data(seed, first, n, want_f32=True)
