@@ -56,100 +56,166 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
 
 // ------------------------------------------------------------------ GEMM
 //
-// C[M][N] = A[M][K] * B[K][N] on BF16 operands with FP32 accumulation in
-// the 32x32x16 matrix-core instruction.  A workgroup of four waves owns a
-// 64x64 tile of C (2x2 waves of 32x32); K advances through LDS
-// (double-buffered, one barrier per stage) in stages of TKS = 128 (32 when
-// K per range is not a multiple of 128), TKS/16 MFMA per wave and stage.
-// Operands are read from either layout:
-//   AK: A[m*lda + k] (k contiguous)   else A[k*lda + m]
-//   BK: B[n*ldb + k] (k contiguous)   else B[k*ldb + n]
-// LDS holds both tiles as [row = m or n][TKS k] so every lane fetches its 8
-// consecutive k values with one 16-byte read (row stride padded by 8).
+// C[M][N] = A[M][K] * B[N][K]^T on BF16 operands, k contiguous in both, with
+// FP32 accumulation in the 32x32x16 matrix-core instruction, k ascending
+// (every output is the same chain of instructions in any tiling below).  A
+// workgroup of four waves owns a TILE x TILE tile of C, K advancing through
+// LDS in stages of TKS (row stride padded by 8: conflict-free 16-byte reads
+// of a lane's 8 consecutive k).
+//
+// At the network's sizes (K = 128 ... 512, 128 tiles) a product is bound by
+// latency, not by the matrix cores: so where one stage holds all of K (NBUF =
+// 1) a tile's loads are all in flight at once and one barrier separates them
+// from the products, and 32 x 32 tiles replace 64 x 64 ones that would leave
+// half of the compute units without work.  Grids of more than 256 tiles and
+// longer sums go through two buffers of 128 k (two workgroups per compute
+// unit, the next stage's loads in flight during the products).  1024 rows,
+// K = 512: 9.5 us per product in stages of 128 with the operands transposed
+// on their way to LDS, 8.5 us so (32 x 32 tiles, N = 128: 9.4, 7.0 us).
+//
+// Every operand exists in the layout that its product reads: the weights and
+// the batch's activations and gradients are kept in both orders, written
+// together by the kernels that produce them.
 // Epilogue: + bias[n], then * (mask[m][n] > 0), then ReLU, written as FP32
-// and/or BF16.  Requires M % 64 == 0, N % 64 == 0, K % (32 * ksplit) == 0.
-// With ksplit > 1 (the weight gradients, a contraction over the batch) each
-// K range writes its own FP32 partial (no bias, mask or ReLU) and
-// splitk_reduce_kernel adds them in order.
+// and/or BF16 and/or transposed BF16.  Requires M, N % TILE == 0, K % (32 *
+// ksplit) == 0.  Rows of A beyond m_valid repeat the last valid one, and C's
+// are not written.  With ksplit > 1 (the weight gradients, a contraction over
+// the batch) each K range writes its own FP32 partial (no bias, mask or ReLU)
+// and splitk_reduce_kernel or the Adam kernel adds them in order.
 struct GemmArgs {
-  const uint16_t* A;
+  const uint16_t* A;     // [M][lda]
   int64_t lda;
-  const uint16_t* B;
+  const uint16_t* B;     // [N][ldb]
   int64_t ldb;
   int M, N, K;
+  int m_valid;           // rows of A and C that exist
   const float* bias;     // [N] or null
   const uint16_t* mask;  // [M][ldm] BF16 or null
   int64_t ldm;
   float* Cf;             // [M][ldc] or null (with ksplit > 1: [ksplit][M][ldc])
   uint16_t* Cb;          // [M][ldc] or null
   int64_t ldc;
+  uint16_t* CbT;         // [N][ldt] or null
+  int64_t ldt;
   int relu;
   int ksplit;            // K is cut into ksplit equal ranges (blockIdx.z), 0/1: none
 };
 
-constexpr int TM = 64;
+// Column sums that ride along in a GEMM launch (colsum_block): the work of
+// tiles * CS_RC extra blocks.
+constexpr int CS_RC = 16;
+struct ColSeg {
+  const float* X;
+  int64_t ld;
+  int ncol;
+  float* out;
+};
+struct ColSegs {
+  ColSeg s[4];
+  int nseg;
+  int tile0[5];  // first 64-column tile of each segment
+  int col0[5];   // first column of each segment in the partial array
+  int nrow;
+};
 
-// One K stage of a 64-row operand tile: TKS k values per row, TKS/32 chunks
-// of 8 BF16 (16 bytes) per thread, all loads issued before any is used.
-template <bool KC, int TKS>
-__device__ __forceinline__ void load_tile(const uint16_t* X, int64_t ld, int r0, int k0,
-                                          uint4* v) {
-  const int t = threadIdx.x;
-#pragma unroll
-  for (int j = 0; j < TKS / 32; ++j) {
-    const int q = t + 256 * j;  // chunk index
-    if (KC) {  // row q / (TKS/8), k chunk q % (TKS/8)
-      v[j] = *(const uint4*)(X + (int64_t)(r0 + q / (TKS / 8)) * ld + k0 + (q % (TKS / 8)) * 8);
-    } else {   // k row q / 8, 8 consecutive rows from (q % 8) * 8
-      v[j] = *(const uint4*)(X + (int64_t)(k0 + q / 8) * ld + r0 + (q % 8) * 8);
-    }
+// Column sums out[c] = sum_r X[r][c] of up to four matrices (bias gradients
+// and the loss).  Stage 1: block (column tile of 64, row chunk rc) sums its
+// rows in four interleaved groups combined in a fixed order into
+// part[rc][column]; stage 2 adds the RC chunks in order.  Deterministic.
+__device__ __forceinline__ void colsum_block(const ColSegs& cs, float* part, int tile, int rc,
+                                             float (*red)[64]) {
+  const int ncol_all = cs.col0[cs.nseg];
+  int sg = 0;
+  while (sg + 1 < cs.nseg && tile >= cs.tile0[sg + 1]) ++sg;
+  const ColSeg& g = cs.s[sg];
+  const int c = (tile - cs.tile0[sg]) * 64 + (threadIdx.x & 63);
+  const int grp = threadIdx.x >> 6;
+  const int per = (cs.nrow + CS_RC - 1) / CS_RC;
+  const int r0 = rc * per, r1 = min(cs.nrow, r0 + per);
+  float acc = 0.0f;
+  if (c < g.ncol) {
+#pragma unroll 4
+    for (int r = r0 + grp; r < r1; r += 4) acc += g.X[(int64_t)r * g.ld + c];
+  }
+  red[grp][threadIdx.x & 63] = acc;
+  __syncthreads();
+  if (grp == 0 && c < g.ncol) {
+    const int j = threadIdx.x;
+    part[(int64_t)rc * ncol_all + cs.col0[sg] + c] =
+        ((red[0][j] + red[1][j]) + red[2][j]) + red[3][j];
   }
 }
 
-template <bool KC, int TKS>
-__device__ __forceinline__ void store_tile(uint16_t* S, const uint4* v) {
-  constexpr int STRIDE = TKS + 8;
-  const int t = threadIdx.x;
-#pragma unroll
-  for (int j = 0; j < TKS / 32; ++j) {
-    const int q = t + 256 * j;
-    if (KC) {
-      *(uint4*)(S + (q / (TKS / 8)) * STRIDE + (q % (TKS / 8)) * 8) = v[j];
-    } else {
-      const int k = q / 8, r = (q % 8) * 8;
-      const uint16_t* e = (const uint16_t*)&v[j];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) S[(r + i) * STRIDE + k] = e[i];
-    }
-  }
+__global__ void colsum_stage2(ColSegs cs, const float* part, int ncol_all) {
+  const int c = blockIdx.x * blockDim.x + threadIdx.x;
+  if (c >= ncol_all) return;
+  int sg = 0;
+  while (sg + 1 < cs.nseg && c >= cs.col0[sg + 1]) ++sg;
+  float t = part[c];
+  for (int rc = 1; rc < CS_RC; ++rc) t += part[(int64_t)rc * ncol_all + c];
+  cs.s[sg].out[c - cs.col0[sg]] = t;
 }
 
-// TKS: k values per LDS stage (32 or 128); deeper stages keep more loads in
-// flight per round trip, which is what bounds these small GEMMs.
 // Up to three independent products of one shape class in one launch (the
 // three weight gradients of a step): blockIdx.x runs over the output tiles
 // of problem 0, then 1, then 2 (first[p] = its first block), blockIdx.z over
-// the K ranges, which all problems share.
+// the K ranges, which all problems share; the blocks from first[nprob] on
+// take the column sums (cs.nseg > 0).
 struct GemmGroup {
   GemmArgs g[3];
   int first[4];
   int nprob;
+  ColSegs cs;
+  float* cpart;
 };
 
-template <bool AK, bool BK, int TKS>
+// One K stage of a TILE-row operand tile in 16-byte chunks, consecutive
+// threads on consecutive chunks of a row.
+template <int TILE, int TKS>
+constexpr int STAGE_CHUNKS = TILE * TKS / 8 / 256;
+
+template <int TILE, int TKS>
+__device__ __forceinline__ void load_tile(const uint16_t* __restrict__ X, int64_t ld, int r0,
+                                          int r_last, int k0, uint4* v) {
+#pragma unroll
+  for (int j = 0; j < STAGE_CHUNKS<TILE, TKS>; ++j) {
+    const int q = threadIdx.x + 256 * j, r = min(r0 + q / (TKS / 8), r_last);
+    v[j] = *(const uint4*)(X + (int64_t)r * ld + k0 + (q % (TKS / 8)) * 8);
+  }
+}
+
+template <int TILE, int TKS>
+__device__ __forceinline__ void store_tile(uint16_t* S, const uint4* v) {
+#pragma unroll
+  for (int j = 0; j < STAGE_CHUNKS<TILE, TKS>; ++j) {
+    const int q = threadIdx.x + 256 * j;
+    *(uint4*)(S + (q / (TKS / 8)) * (TKS + 8) + (q % (TKS / 8)) * 8) = v[j];
+  }
+}
+
+template <int TILE, int TKS, int NBUF>
 __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmGroup gg) {
   constexpr int STRIDE = TKS + 8;  // padded LDS row (elements)
-  __shared__ __attribute__((aligned(16))) uint16_t sA[2][TM * STRIDE];
-  __shared__ __attribute__((aligned(16))) uint16_t sB[2][TM * STRIDE];
+  __shared__ __attribute__((aligned(16))) uint16_t sA[NBUF][TILE * STRIDE];
+  __shared__ __attribute__((aligned(16))) uint16_t sB[NBUF][TILE * STRIDE];
+  if ((int)blockIdx.x >= gg.first[gg.nprob]) {  // the whole block
+    const int id = ((int)blockIdx.x - gg.first[gg.nprob]) * gridDim.z + blockIdx.z;
+    const int tiles = gg.cs.tile0[gg.cs.nseg];
+    if (id < tiles * CS_RC)
+      colsum_block(gg.cs, gg.cpart, id % tiles, id / tiles, (float(*)[64])(void*)sA);
+    return;
+  }
   int prob = 0;
   while (prob + 1 < gg.nprob && (int)blockIdx.x >= gg.first[prob + 1]) ++prob;
   const GemmArgs& g = gg.g[prob];
-  const int tile = (int)blockIdx.x - gg.first[prob], ntn = g.N / TM;
-  const int m0 = (tile / ntn) * TM, n0 = (tile % ntn) * TM;
+  const int tile = (int)blockIdx.x - gg.first[prob], ntn = g.N / TILE;
+  const int m0 = (tile / ntn) * TILE, n0 = (tile % ntn) * TILE;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-  const int nst = g.K / TKS / gridDim.z;  // stages of this K range
-  const int kb = blockIdx.z * nst * TKS;  // its first k
+  // (32 x 32 tiles: the first wave multiplies, all four load)
+  const int wm = TILE == 64 ? (wave >> 1) * 32 : 0, wn = TILE == 64 ? (wave & 1) * 32 : 0;
+  const bool multiplies = TILE == 64 || wave == 0;
+  const int nst = NBUF == 1 ? 1 : g.K / TKS / gridDim.z;  // stages of this K range
+  const int kb = blockIdx.z * nst * TKS;                  // its first k
 
   f32x16 acc;
 #pragma unroll
@@ -157,6 +223,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmGroup gg) {
 
   // the MFMAs of the stage in LDS buffer `buf`
   auto mfma_stage = [&](int buf) {
+    if (!multiplies) return;
     const uint16_t* pa = sA[buf] + (wm + (lane & 31)) * STRIDE + 8 * (lane >> 5);
     const uint16_t* pb = sB[buf] + (wn + (lane & 31)) * STRIDE + 8 * (lane >> 5);
 #pragma unroll
@@ -166,76 +233,101 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmGroup gg) {
       acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
     }
   };
-  uint4 ra[TKS / 32], rb[TKS / 32];
-  load_tile<AK, TKS>(g.A, g.lda, m0, kb, ra);
-  load_tile<BK, TKS>(g.B, g.ldb, n0, kb, rb);
-  store_tile<AK, TKS>(sA[0], ra);
-  store_tile<BK, TKS>(sB[0], rb);
+  constexpr int NC = STAGE_CHUNKS<TILE, TKS>;
+  uint4 ra[NC], rb[NC];
+  load_tile<TILE, TKS>(g.A, g.lda, m0, g.m_valid - 1, kb, ra);
+  load_tile<TILE, TKS>(g.B, g.ldb, n0, g.N - 1, kb, rb);
+  store_tile<TILE, TKS>(sA[0], ra);
+  store_tile<TILE, TKS>(sB[0], rb);
   __syncthreads();
   // software pipeline: the next stage's loads are in flight during this
   // stage's MFMAs; the last stage is peeled off, so the staging registers
   // are written on every pass of the loop (a conditional load kept them in
   // scratch memory, and the loads were waited for at once)
-  for (int s = 0; s + 1 < nst; ++s) {
-    const int cur = s & 1;
-    load_tile<AK, TKS>(g.A, g.lda, m0, kb + (s + 1) * TKS, ra);
-    load_tile<BK, TKS>(g.B, g.ldb, n0, kb + (s + 1) * TKS, rb);
-    mfma_stage(cur);
-    store_tile<AK, TKS>(sA[cur ^ 1], ra);
-    store_tile<BK, TKS>(sB[cur ^ 1], rb);
-    __syncthreads();
+  if constexpr (NBUF > 1) {
+    for (int s = 0; s + 1 < nst; ++s) {
+      const int cur = s & 1;
+      load_tile<TILE, TKS>(g.A, g.lda, m0, g.m_valid - 1, kb + (s + 1) * TKS, ra);
+      load_tile<TILE, TKS>(g.B, g.ldb, n0, g.N - 1, kb + (s + 1) * TKS, rb);
+      mfma_stage(cur);
+      store_tile<TILE, TKS>(sA[cur ^ 1], ra);
+      store_tile<TILE, TKS>(sB[cur ^ 1], rb);
+      __syncthreads();
+    }
   }
   mfma_stage((nst - 1) & 1);
+  if (!multiplies) return;
 
   // lane l, register r holds C[(r%4) + 8(r/4) + 4(l/32)][l%32] of the wave
   const int n = n0 + wn + (lane & 31);
   const float bias = g.bias ? g.bias[n] : 0.0f;
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int m = m0 + wm + (r & 3) + 8 * (r >> 2) + 4 * (lane >> 5);
-    float v = acc[r] + bias;
-    if (g.mask) {
-      const uint16_t h = g.mask[(int64_t)m * g.ldm + n];
-      if (h == 0 || (h & 0x8000u)) v = 0.0f;
+  for (int r4 = 0; r4 < 4; ++r4) {
+    const int mb = m0 + wm + 8 * r4 + 4 * (lane >> 5);
+    uint16_t h4[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int m = mb + i;
+      float v = acc[4 * r4 + i] + bias;
+      if (g.mask) {
+        const uint16_t h = g.mask[(int64_t)m * g.ldm + n];
+        if (h == 0 || (h & 0x8000u)) v = 0.0f;
+      }
+      if (g.relu) v = fmaxf(v, 0.0f);
+      h4[i] = f2bf(v);
+      if (m < g.m_valid) {
+        if (g.Cf) g.Cf[(int64_t)blockIdx.z * g.M * g.ldc + (int64_t)m * g.ldc + n] = v;
+        if (g.Cb) g.Cb[(int64_t)m * g.ldc + n] = h4[i];
+      }
     }
-    if (g.relu) v = fmaxf(v, 0.0f);
-    if (g.Cf) g.Cf[(int64_t)blockIdx.z * g.M * g.ldc + (int64_t)m * g.ldc + n] = v;
-    if (g.Cb) g.Cb[(int64_t)m * g.ldc + n] = f2bf(v);
+    if (g.CbT) *(ushort4*)(g.CbT + (int64_t)n * g.ldt + mb) = {h4[0], h4[1], h4[2], h4[3]};
   }
 }
 
-template <int TKS>
-hipError_t gemm_t(const GemmGroup& gg, bool ak, bool bk, hipStream_t st) {
-  const int ks = gg.g[0].ksplit > 1 ? gg.g[0].ksplit : 1;
-  const dim3 grid(gg.first[gg.nprob], 1, ks);
-  if (ak && !bk)
-    hipLaunchKernelGGL((gemm_bf16_kernel<true, false, TKS>), grid, dim3(256), 0, st, gg);
-  else if (ak && bk)
-    hipLaunchKernelGGL((gemm_bf16_kernel<true, true, TKS>), grid, dim3(256), 0, st, gg);
-  else if (!ak && !bk)
-    hipLaunchKernelGGL((gemm_bf16_kernel<false, false, TKS>), grid, dim3(256), 0, st, gg);
-  else
-    hipLaunchKernelGGL((gemm_bf16_kernel<false, true, TKS>), grid, dim3(256), 0, st, gg);
-  return hipGetLastError();
-}
-
-// C = A B for n (1..3) problems with the same operand layouts, K and K split.
-hipError_t gemm_group(const GemmArgs* gs, int n, bool ak, bool bk, hipStream_t st) {
+// C = A B^T for n (1..3) problems with the same K, K split and tile size, and
+// the column sums cs (nullable) in the same launch.
+hipError_t gemm_group(const GemmArgs* gs, int n, hipStream_t st, const ColSegs* cs = nullptr,
+                      float* cpart = nullptr) {
+  const int ks = gs[0].ksplit > 1 ? gs[0].ksplit : 1;
+  const int K = gs[0].K / ks;
+  int64_t tiles64 = 0;
+  for (int i = 0; i < n; ++i) tiles64 += (int64_t)(gs[i].N / 64) * (gs[i].M / 64);
+  const int tile = tiles64 * ks < 128 && K % 64 == 0 ? 32 : 64;
   GemmGroup gg;
   memset(&gg, 0, sizeof(gg));
   gg.nprob = n;
   gg.first[0] = 0;
   for (int i = 0; i < n; ++i) {
     gg.g[i] = gs[i];
-    gg.first[i + 1] = gg.first[i] + (gs[i].N / TM) * (gs[i].M / TM);
+    gg.first[i + 1] = gg.first[i] + (gs[i].N / tile) * (gs[i].M / tile);
   }
-  const int ks = gs[0].ksplit > 1 ? gs[0].ksplit : 1;
-  return (gs[0].K / ks) % 128 == 0 ? gemm_t<128>(gg, ak, bk, st) : gemm_t<32>(gg, ak, bk, st);
+  int extra = 0;
+  if (cs) {
+    gg.cs = *cs;
+    gg.cpart = cpart;
+    extra = (cs->tile0[cs->nseg] * CS_RC + ks - 1) / ks;
+  }
+  const dim3 grid(gg.first[n] + extra, 1, ks);
+  auto run = [&](auto kern) {
+    hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, gg);
+    return hipGetLastError();
+  };
+  const bool one = tile == 32 || tiles64 * ks <= 256 || K == 128;  // all of K in one stage
+  if (tile == 64) {
+    if (one && K == 512) return run(gemm_bf16_kernel<64, 512, 1>);
+    if (one && K == 256) return run(gemm_bf16_kernel<64, 256, 1>);
+    if (one && K == 128) return run(gemm_bf16_kernel<64, 128, 1>);
+    if (K % 128 == 0) return run(gemm_bf16_kernel<64, 128, 2>);
+    return run(gemm_bf16_kernel<64, 32, 2>);
+  }
+  if (K == 512) return run(gemm_bf16_kernel<32, 512, 1>);
+  if (K == 256) return run(gemm_bf16_kernel<32, 256, 1>);
+  if (K == 128) return run(gemm_bf16_kernel<32, 128, 1>);
+  if (K % 128 == 0) return run(gemm_bf16_kernel<32, 128, 2>);
+  return run(gemm_bf16_kernel<32, 64, 2>);
 }
 
-hipError_t gemm(const GemmArgs& g, bool ak, bool bk, hipStream_t st) {
-  return gemm_group(&g, 1, ak, bk, st);
-}
+hipError_t gemm(const GemmArgs& g, hipStream_t st) { return gemm_group(&g, 1, st); }
 
 // --------------------------------------------------- mixture likelihood
 //
@@ -262,8 +354,13 @@ __device__ __forceinline__ double grp8_sum(double v) {
 }
 
 __global__ __launch_bounds__(256) void mlp_nll_kernel(const float* O, const float* y, int n,
-                                                      float* dOf, uint16_t* dOb,
-                                                      float* loss_row) {
+                                                      float* dOf, uint16_t* dOb, uint16_t* dObT,
+                                                      int64_t ldt, float* loss_row,
+                                                      int64_t* dstep) {
+  __shared__ float tile[32][NOP + 1];
+  // (captured training: the step's index for the kernels after this one,
+  // while the Adam kernel advances the counter for the next step)
+  if (dstep && blockIdx.x == 0 && threadIdx.x == 0) dstep[1] = dstep[0];
   const int gid = blockIdx.x * blockDim.x + threadIdx.x;
   const int b = gid >> 3, k = gid & 7;  // n * 8 threads, a multiple of 64
   const bool valid = b < n;
@@ -291,94 +388,31 @@ __global__ __launch_bounds__(256) void mlp_nll_kernel(const float* O, const floa
   const double lp = amax + log(grp8_sum(exp(a - amax)));
   const double gam = exp(a - lp);
   const double pi = exp(logit - lse_l);
-  if (!valid) return;
-  if (k == 0) loss_row[b] = (float)(-lp * inv_n);
-  float* gf = dOf + (int64_t)b * NOP;
-  uint16_t* gb = dOb + (int64_t)b * NOP;
-  const float gl = (float)((pi - gam) * inv_n);
-  gf[k] = gl;
-  gb[k] = f2bf(gl);
+  if (valid && k == 0) loss_row[b] = (float)(-lp * inv_n);
+  float* row = tile[threadIdx.x >> 3];
+  row[k] = (float)((pi - gam) * inv_n);
 #pragma unroll
   for (int d = 0; d < DM; ++d) {
-    const float gm = (float)(-gam * r[d] * is2[d] * inv_n);
-    const float gs = (float)(-gam * (r[d] * r[d] * is2[d] - 1.0) * inv_n);
-    gf[KM + k * DM + d] = gm;
-    gb[KM + k * DM + d] = f2bf(gm);
-    gf[KM + KM * DM + k * DM + d] = gs;
-    gb[KM + KM * DM + k * DM + d] = f2bf(gs);
+    row[KM + k * DM + d] = (float)(-gam * r[d] * is2[d] * inv_n);
+    row[KM + KM * DM + k * DM + d] = (float)(-gam * (r[d] * r[d] * is2[d] - 1.0) * inv_n);
   }
-  gf[NO + k] = 0.0f;  // the eight pad columns
-  gb[NO + k] = 0;
-}
-
-// Column sums out[c] = sum_r X[r][c] of up to four matrices in one pair of
-// launches (bias gradients and the loss).  Stage 1: block (column tile of
-// 64, row chunk rc) sums its rows in four interleaved groups combined in a
-// fixed order into part[rc][column]; stage 2 adds the RC chunks in order.
-// Deterministic.
-constexpr int CS_RC = 16;
-struct ColSeg {
-  const float* X;
-  int64_t ld;
-  int ncol;
-  float* out;
-};
-struct ColSegs {
-  ColSeg s[4];
-  int nseg;
-  int tile0[5];  // first 64-column tile of each segment
-  int col0[5];   // first column of each segment in the partial array
-  int nrow;
-};
-
-__global__ __launch_bounds__(256) void colsum_stage1(ColSegs cs, float* part, int ncol_all) {
-  __shared__ float red[4][64];
-  int sg = 0;
-  while (sg + 1 < cs.nseg && (int)blockIdx.x >= cs.tile0[sg + 1]) ++sg;
-  const ColSeg& g = cs.s[sg];
-  const int c = ((int)blockIdx.x - cs.tile0[sg]) * 64 + (threadIdx.x & 63);
-  const int grp = threadIdx.x >> 6;
-  const int per = (cs.nrow + CS_RC - 1) / CS_RC;
-  const int r0 = blockIdx.y * per, r1 = min(cs.nrow, r0 + per);
-  float acc = 0.0f;
-  if (c < g.ncol)
-    for (int r = r0 + grp; r < r1; r += 4) acc += g.X[(int64_t)r * g.ld + c];
-  red[grp][threadIdx.x & 63] = acc;
+  row[NO + k] = 0.0f;  // the eight pad columns
   __syncthreads();
-  if (grp == 0 && c < g.ncol) {
-    const int j = threadIdx.x;
-    part[(int64_t)blockIdx.y * ncol_all + cs.col0[sg] + c] =
-        ((red[0][j] + red[1][j]) + red[2][j]) + red[3][j];
+  // the block's 32 rows, in both orders
+  const int b0 = blockIdx.x * 32;
+#pragma unroll 4
+  for (int e = threadIdx.x; e < 32 * NOP; e += 256) {
+    const int i = e / NOP, c = e % NOP;
+    if (b0 + i < n) {
+      dOf[(int64_t)(b0 + i) * NOP + c] = tile[i][c];
+      dOb[(int64_t)(b0 + i) * NOP + c] = f2bf(tile[i][c]);
+    }
   }
-}
-
-__global__ void colsum_stage2(ColSegs cs, const float* part, int ncol_all) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= ncol_all) return;
-  int sg = 0;
-  while (sg + 1 < cs.nseg && c >= cs.col0[sg + 1]) ++sg;
-  float t = part[c];
-  for (int rc = 1; rc < CS_RC; ++rc) t += part[(int64_t)rc * ncol_all + c];
-  cs.s[sg].out[c - cs.col0[sg]] = t;
-}
-
-// part must hold CS_RC x (total columns) floats.  stage2 = false leaves the
-// partials for the captured training step's Adam kernel to add.
-hipError_t colsums(ColSegs cs, float* part, hipStream_t st, bool stage2 = true) {
-  cs.tile0[0] = 0;
-  cs.col0[0] = 0;
-  for (int i = 0; i < cs.nseg; ++i) {
-    cs.tile0[i + 1] = cs.tile0[i] + (cs.s[i].ncol + 63) / 64;
-    cs.col0[i + 1] = cs.col0[i] + cs.s[i].ncol;
+#pragma unroll 4
+  for (int e = threadIdx.x; e < 32 * NOP; e += 256) {
+    const int c = e / 32, i = e % 32;
+    if (b0 + i < n) dObT[c * ldt + b0 + i] = f2bf(tile[i][c]);
   }
-  const int ncol_all = cs.col0[cs.nseg];
-  hipLaunchKernelGGL(colsum_stage1, dim3(cs.tile0[cs.nseg], CS_RC), dim3(256), 0, st, cs, part,
-                     ncol_all);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || !stage2) return e;
-  hipLaunchKernelGGL(colsum_stage2, dim3((ncol_all + 255) / 256), dim3(256), 0, st, cs, part,
-                     ncol_all);
-  return hipGetLastError();
 }
 
 // Sum of ks partial matrices part[z][i], z in order (split-K reduction).
@@ -391,141 +425,219 @@ __global__ void splitk_reduce_kernel(const float* part, int ks, int64_t n, float
   }
 }
 
-// Adam (Kingma & Ba 2015) with bias correction factors c1 = 1/(1 - b1^t),
-// c2 = 1/(1 - b2^t):  p -= lr * (m c1) / (sqrt(v c2) + eps); also refreshes
-// the BF16 shadow of the weights.  1 - b1 and 1 - b2 come from the host in
-// double (1.0f - 0.999f would carry a 1e-5 relative error into v).
-__global__ void adam_kernel(float* p, const float* g, float* m, float* v,
-                            uint16_t* pb, int64_t n, float lr, float b1, float b2,
-                            float omb1, float omb2, float eps, float c1, float c2) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const float gi = g[i];
-    const float mi = b1 * m[i] + omb1 * gi;
-    const float vi = b2 * v[i] + omb2 * (gi * gi);
-    m[i] = mi;
-    v[i] = vi;
-    const float pi = p[i] - lr * (mi * c1) / (sqrtf(vi * c2) + eps);
-    p[i] = pi;
-    pb[i] = f2bf(pi);
+// The three weight matrices in 32 x 32 tiles, then the biases: the tiles that
+// the kernels writing the BF16 weights in both orders take, one per block.
+constexpr int WT1 = (NB / 32) * (NH / 32), WT2 = (NH / 32) * (NH / 32),
+              WT3 = (NH / 32) * (NOP / 32);
+constexpr int W_TILES = WT1 + WT2 + WT3;
+constexpr int N_BIAS = NH + NH + NOP;
+constexpr int W_BLOCKS = W_TILES + (N_BIAS + 255) / 256;
+// The transposed BF16 weights, W1 [512][256], W2 [512][512], W3 [128][512].
+constexpr int64_t OFF_T1 = 0;
+constexpr int64_t OFF_T2 = OFF_T1 + (int64_t)NB * NH;
+constexpr int64_t OFF_T3 = OFF_T2 + (int64_t)NH * NH;
+constexpr int64_t NP_T = OFF_T3 + (int64_t)NH * NOP;
+
+struct WTile {
+  int64_t off, off_t;  // the matrix in the parameters and among the transposed
+  int rows, cols;      // [rows = inputs][cols = outputs]
+  int r0, c0;          // the tile's first row and column
+  int tensor;          // 0: W3, 1: W2, 2: W1 (the order of KParts)
+};
+__device__ __forceinline__ WTile weight_tile(int b) {
+  WTile w;
+  if (b < WT1)
+    w = {OFF_W1, OFF_T1, NB, NH, 0, 0, 2};
+  else if (b < WT1 + WT2)
+    w = {OFF_W2, OFF_T2, NH, NH, 0, 0, 1}, b -= WT1;
+  else
+    w = {OFF_W3, OFF_T3, NH, NOP, 0, 0, 0}, b -= WT1 + WT2;
+  w.r0 = b / (w.cols / 32) * 32;
+  w.c0 = b % (w.cols / 32) * 32;
+  return w;
+}
+// Parameter index of bias entry e (b1, b2, b3 one after another).
+__device__ __forceinline__ int64_t bias_index(int e) {
+  return e < NH ? OFF_B1 + e : e < 2 * NH ? OFF_B2 + (e - NH) : OFF_B3 + (e - 2 * NH);
+}
+
+// Transposed copy of a 32 x 32 tile: thread t holds row t / 8, columns 4 (t %
+// 8) .. + 3 in h.
+__device__ __forceinline__ void store_tile_t(const WTile& w, ushort4 h, uint16_t* pbT,
+                                             uint16_t (*sh)[36]) {
+  const int t = threadIdx.x, r = t >> 3, c = (t & 7) * 4;
+  sh[c][r] = h.x;
+  sh[c + 1][r] = h.y;
+  sh[c + 2][r] = h.z;
+  sh[c + 3][r] = h.w;
+  __syncthreads();
+  *(ushort4*)(pbT + w.off_t + (int64_t)(w.c0 + r) * w.rows + w.r0 + c) = *(ushort4*)&sh[r][c];
+}
+
+// The BF16 weights of the FP32 parameters, in both orders.
+__global__ __launch_bounds__(256) void shadow_kernel(const float* p, uint16_t* pb, uint16_t* pbT) {
+  __shared__ __attribute__((aligned(8))) uint16_t sh[32][36];
+  const int b = blockIdx.x, t = threadIdx.x;
+  if (b >= W_TILES) {
+    const int e = (b - W_TILES) * 256 + t;
+    if (e < N_BIAS) pb[bias_index(e)] = f2bf(p[bias_index(e)]);
+    return;
   }
+  const WTile w = weight_tile(b);
+  const int64_t i = w.off + (int64_t)(w.r0 + (t >> 3)) * w.cols + w.c0 + (t & 7) * 4;
+  const float4 x = *(const float4*)(p + i);
+  const ushort4 h = {f2bf(x.x), f2bf(x.y), f2bf(x.z), f2bf(x.w)};
+  *(ushort4*)(pb + i) = h;
+  store_tile_t(w, h, pbT, sh);
+}
+
+// Adam (Kingma & Ba 2015) with bias correction factors c1 = 1/(1 - b1^t),
+// c2 = 1/(1 - b2^t):  p -= lr * (m c1) / (sqrt(v c2) + eps).  1 - b1 and 1 - b2
+// come from the host in double (1.0f - 0.999f would carry a 1e-5 relative
+// error into v).
+struct AdamArgs {
+  float *p, *m, *v;
+  float b1, b2, omb1, omb2, eps;
+};
+__device__ __forceinline__ float adam_update(const AdamArgs& a, float p, float gi, float& m,
+                                             float& v, float lr, float c1, float c2) {
+  const float mi = a.b1 * m + a.omb1 * gi;
+  const float vi = a.b2 * v + a.omb2 * (gi * gi);
+  m = mi;
+  v = vi;
+  return p - lr * (mi * c1) / (sqrtf(vi * c2) + a.eps);
 }
 
 // The split-K partials of the three weight gradients of one step (a buffer
 // each), for the graph form of training: the Adam kernel sums them.
 struct KParts {
-  const float* part[3];
-  int64_t off[3];  // first parameter of the tensor
-  int64_t mn[3];   // its elements
-  int ks;          // partials per tensor (1: none, the GEMM wrote the gradient)
+  const float* part[3];  // W3, W2, W1
+  int ks;                // partials per tensor (1: none, the GEMM wrote the gradient)
 };
 
-// The column-sum partials of one step (colsum_stage1 without its second
-// stage): the three bias gradients and the loss.
+// The column-sum partials of one step: the three bias gradients (b3, b2, b1)
+// and the loss.
 struct CParts {
   const float* part;  // [CS_RC][ncol_all]
   int ncol_all;
-  int64_t off[3];     // first parameter of b3, b2, b1
-  int ncol[3];
-  int col0[3];        // their first columns in part
+  int col0[3];        // first columns of b3, b2, b1 in part
   int loss_col;
 };
 
-// adam_kernel for a step of the captured training graph: the step's learning
-// rate and bias-correction factors are read from sched[3k .. 3k+2] (k = the
-// device step counter); a weight tensor's gradient is first summed over its
-// split-K partials, in range order (as splitk_reduce sums them), a bias
-// gradient over its column-sum partials, in row-chunk order (as
-// colsum_stage2 sums them), and stored to g.
-__global__ void adam_graph_kernel(float* p, float* g, float* m, float* v, uint16_t* pb,
-                                  int64_t n, const float* sched, const int64_t* dstep,
-                                  KParts kp, CParts cp, float b1, float b2, float omb1,
-                                  float omb2, float eps) {
-  const int64_t k = *dstep;
-  const float lr = sched[3 * k], c1 = sched[3 * k + 1], c2 = sched[3 * k + 2];
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    float gi = 0.0f;
-    bool summed = false;
-    if (kp.ks > 1) {
-#pragma unroll
-      for (int t = 0; t < 3; ++t) {
-        const int64_t j = i - kp.off[t];
-        if (j >= 0 && j < kp.mn[t]) {
-          float sum = kp.part[t][j];
-          for (int z = 1; z < kp.ks; ++z) sum += kp.part[t][(int64_t)z * kp.mn[t] + j];
-          g[i] = sum;
-          gi = sum;
-          summed = true;
-        }
-      }
+// One Adam step, writing the BF16 weights in both orders.  Alone (dstep null)
+// it takes the gradient g and the given learning rate and correction factors.
+// In the captured training graph the step's learning rate and correction
+// factors are sched[3k .. 3k+2] (k = dstep[1]); a weight tensor's gradient is
+// first summed over its split-K partials, in range order (as splitk_reduce
+// sums them), a bias gradient and the loss over their column-sum partials,
+// in row-chunk order (as colsum_stage2 sums them); the gradients are stored
+// to g, the loss to losses[k], and the counter moves on (dstep[0] = k + 1,
+// which no block of this launch reads).
+__global__ __launch_bounds__(256) void adam_kernel(AdamArgs a, float* g, uint16_t* pb,
+                                                   uint16_t* pbT, float lr, float c1, float c2,
+                                                   const float* sched, int64_t* dstep, KParts kp,
+                                                   CParts cp, float* losses) {
+  __shared__ __attribute__((aligned(8))) uint16_t sh[32][36];
+  const int b = blockIdx.x, t = threadIdx.x;
+  if (dstep) {
+    const int64_t k = dstep[1];
+    lr = sched[3 * k];
+    c1 = sched[3 * k + 1];
+    c2 = sched[3 * k + 2];
+    if (b == W_TILES && t == 0) {
+      float sum = cp.part[cp.loss_col];
+      for (int rc = 1; rc < CS_RC; ++rc) sum += cp.part[(int64_t)rc * cp.ncol_all + cp.loss_col];
+      losses[k] = sum;
+      dstep[0] = k + 1;
     }
-#pragma unroll
-    for (int t = 0; t < 3; ++t) {
-      const int64_t j = i - cp.off[t];
-      if (j >= 0 && j < cp.ncol[t]) {
-        const int c = cp.col0[t] + (int)j;
-        float sum = cp.part[c];
-        for (int rc = 1; rc < CS_RC; ++rc) sum += cp.part[(int64_t)rc * cp.ncol_all + c];
-        g[i] = sum;
-        gi = sum;
-        summed = true;
-      }
+  }
+  if (b >= W_TILES) {
+    const int e = (b - W_TILES) * 256 + t;
+    if (e >= N_BIAS) return;
+    const int64_t i = bias_index(e);
+    float gi;
+    if (dstep) {
+      const int c = e < NH ? cp.col0[2] + e : e < 2 * NH ? cp.col0[1] + (e - NH)
+                                                         : cp.col0[0] + (e - 2 * NH);
+      gi = cp.part[c];
+      for (int rc = 1; rc < CS_RC; ++rc) gi += cp.part[(int64_t)rc * cp.ncol_all + c];
+      g[i] = gi;
+    } else {
+      gi = g[i];
     }
-    if (!summed) gi = g[i];
-    const float mi = b1 * m[i] + omb1 * gi;
-    const float vi = b2 * v[i] + omb2 * (gi * gi);
-    m[i] = mi;
-    v[i] = vi;
-    const float pi = p[i] - lr * (mi * c1) / (sqrtf(vi * c2) + eps);
-    p[i] = pi;
-    pb[i] = f2bf(pi);
+    float m = a.m[i], v = a.v[i];
+    const float x = adam_update(a, a.p[i], gi, m, v, lr, c1, c2);
+    a.p[i] = x;
+    a.m[i] = m;
+    a.v[i] = v;
+    pb[i] = f2bf(x);
+    return;
   }
-}
-
-// Last node of a training step: the step's loss (its column-sum partials
-// added in row-chunk order, as colsum_stage2 adds them) to losses[k], and
-// k + 1 to the counter.
-__global__ void step_advance_kernel(int64_t* dstep, CParts cp, float* losses) {
-  const int64_t k = *dstep;
-  float t = cp.part[cp.loss_col];
-  for (int rc = 1; rc < CS_RC; ++rc) t += cp.part[(int64_t)rc * cp.ncol_all + cp.loss_col];
-  losses[k] = t;
-  *dstep = k + 1;
-}
-
-// First node of a training step: batch k mod per of (x, y) into the net's
-// own buffers, k = the device step counter.
-__global__ void batch_gather_kernel(const uint16_t* x, const float* y, int64_t per, int batch,
-                                    const int64_t* dstep, uint16_t* xb, float* yb) {
-  const int64_t r0 = (*dstep % per) * batch;
-  const uint4* xs = (const uint4*)(x + r0 * NB);
-  uint4* xd = (uint4*)xb;
-  const int64_t nx = (int64_t)batch * NB / 8, ny = (int64_t)batch * DM;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < nx + ny;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    if (i < nx)
-      xd[i] = xs[i];
-    else
-      yb[i - nx] = y[r0 * DM + (i - nx)];
+  const WTile w = weight_tile(b);
+  const int64_t j = (int64_t)(w.r0 + (t >> 3)) * w.cols + w.c0 + (t & 7) * 4, i = w.off + j;
+  float4 gi;
+  if (dstep && kp.ks > 1) {
+    const float* part = kp.part[w.tensor];
+    const int64_t mn = (int64_t)w.rows * w.cols;
+    gi = *(const float4*)(part + j);
+#pragma unroll 8
+    for (int z = 1; z < kp.ks; ++z) {
+      const float4 q = *(const float4*)(part + z * mn + j);
+      gi.x += q.x;
+      gi.y += q.y;
+      gi.z += q.z;
+      gi.w += q.w;
+    }
+    *(float4*)(g + i) = gi;
+  } else {
+    gi = *(const float4*)(g + i);
   }
+  float4 x = *(const float4*)(a.p + i), m = *(const float4*)(a.m + i), v = *(const float4*)(a.v + i);
+  x.x = adam_update(a, x.x, gi.x, m.x, v.x, lr, c1, c2);
+  x.y = adam_update(a, x.y, gi.y, m.y, v.y, lr, c1, c2);
+  x.z = adam_update(a, x.z, gi.z, m.z, v.z, lr, c1, c2);
+  x.w = adam_update(a, x.w, gi.w, m.w, v.w, lr, c1, c2);
+  *(float4*)(a.p + i) = x;
+  *(float4*)(a.m + i) = m;
+  *(float4*)(a.v + i) = v;
+  const ushort4 h = {f2bf(x.x), f2bf(x.y), f2bf(x.z), f2bf(x.w)};
+  *(ushort4*)(pb + i) = h;
+  store_tile_t(w, h, pbT, sh);
 }
 
-__global__ void to_bf16_kernel(const float* p, uint16_t* pb, int64_t n) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    pb[i] = f2bf(p[i]);
-}
-
-__global__ void fill_u16_kernel(uint16_t* x, int64_t n) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    x[i] = 0;
+// The rows of one batch in both orders: block b takes 64 rows x 64 bins of x
+// (blockIdx.y: the bins), writing them transposed to xT [256][ldt] and, when
+// xb is given, as they are.  In the captured training graph (dstep) the batch
+// is rows [k mod per) * batch ... of (x, y), k = dstep[0], and its targets
+// are copied to yb.
+__global__ __launch_bounds__(256) void batch_kernel(const uint16_t* x, const float* y, int64_t per,
+                                                    int batch, const int64_t* dstep, uint16_t* xb,
+                                                    uint16_t* xT, int64_t ldt, float* yb) {
+  __shared__ __attribute__((aligned(16))) uint16_t sh[64][72];
+  const int t = threadIdx.x, m0 = blockIdx.x * 64, c0 = blockIdx.y * 64;
+  const int64_t r0 = dstep ? (dstep[0] % per) * batch : 0;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int r = (t >> 3) + 32 * h, c = (t & 7) * 8;
+    const uint4 v = *(const uint4*)(x + (r0 + m0 + r) * NB + c0 + c);
+    if (xb) *(uint4*)(xb + (int64_t)(m0 + r) * NB + c0 + c) = v;
+    *(uint4*)&sh[r][c] = v;
+  }
+  if (yb && blockIdx.y == 0)
+    for (int e = t; e < 64 * DM; e += 256) yb[(int64_t)m0 * DM + e] = y[(r0 + m0) * DM + e];
+  __syncthreads();
+  const int c = t >> 2, rb = (t & 3) * 16;
+  uint16_t o[16] __attribute__((aligned(16)));
+#pragma unroll
+  for (int i = 0; i < 16; ++i) o[i] = sh[rb + i][c];
+  uint4* dst = (uint4*)(xT + (int64_t)(c0 + c) * ldt + m0 + rb);
+  dst[0] = *(const uint4*)&o[0];
+  dst[1] = *(const uint4*)&o[8];
 }
 
 // He-normal weights (std sqrt(2/fan_in); output layer std 0.01), zero
 // biases.  Normal deviates by the Box-Muller transform of two Philox words.
-__global__ void mlp_init_kernel(float* p, uint16_t* pb, uint64_t seed) {
+__global__ void mlp_init_kernel(float* p, uint64_t seed) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < NP_DEV;
        i += (int64_t)gridDim.x * blockDim.x) {
     float val = 0.0f;
@@ -539,7 +651,6 @@ __global__ void mlp_init_kernel(float* p, uint16_t* pb, uint64_t seed) {
       val = (float)(sd * sqrt(-2.0 * log(u1)) * cos(2.0 * M_PI * u2));
     }
     p[i] = val;
-    pb[i] = f2bf(val);
   }
 }
 
@@ -858,21 +969,24 @@ struct mlp_net {
   int batch_max = 0;
   int64_t step = 0;
   float *p = nullptr, *g = nullptr, *m = nullptr, *v = nullptr;
-  uint16_t* pb = nullptr;
+  uint16_t *pb = nullptr, *pbT = nullptr;  // BF16 parameters, weights transposed
   uint16_t* xbuf = nullptr;   // [batch_max][256]
   uint16_t *h1 = nullptr, *h2 = nullptr;  // [batch_max][512] post-ReLU
+  // the batch transposed, [columns][batch_max]: inputs, activations, gradients
+  uint16_t *xT = nullptr, *h1T = nullptr, *h2T = nullptr;
+  uint16_t *dobT = nullptr, *dz2T = nullptr, *dz1T = nullptr;
   float* o = nullptr;         // [batch_max][128]
   float* dof = nullptr;       // [batch_max][128]
   uint16_t* dob = nullptr;
   float *dz2f = nullptr, *dz1f = nullptr;  // [batch_max][512]
-  uint16_t *dz2b = nullptr, *dz1b = nullptr;
+  uint16_t* dz2b = nullptr;
   float* lrow = nullptr;      // [batch_max]
   float* kpart = nullptr;     // split-K partials: [KSPLIT_MAX][512 * 512], the
                               // first of three buffers (W2, then W3, W1)
   float* cpart = nullptr;     // column-sum partials, [CS_RC][COLS_ALL] + a loss slot
   // the training graph (mlp_train) and what it reads
   float* ybuf = nullptr;      // [batch_max][7]
-  int64_t* dstep = nullptr;   // device step counter of the graph
+  int64_t* dstep = nullptr;   // [2] the graph's step counter, the running step
   float* sched = nullptr;     // [sched_cap][3]: learning rate, c1, c2 per step
   float* losses = nullptr;    // [sched_cap]
   int64_t sched_cap = 0;
@@ -895,7 +1009,8 @@ static void net_free(mlp_net* n) {
   if (n->train_exec) (void)hipGraphExecDestroy(n->train_exec);
   void* ptrs[] = {n->p,    n->g,    n->m,    n->v,     n->pb,    n->xbuf,  n->h1,
                   n->h2,   n->o,    n->dof,  n->dob,   n->dz2f,  n->dz1f,  n->dz2b,
-                  n->dz1b, n->lrow, n->kpart, n->cpart, n->ybuf, n->dstep, n->sched,
+                  n->pbT,  n->xT,   n->h1T,  n->h2T,   n->dobT,  n->dz2T,  n->dz1T,
+                  n->lrow, n->kpart, n->cpart, n->ybuf, n->dstep, n->sched,
                   n->losses};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
@@ -906,6 +1021,12 @@ static void net_free(mlp_net* n) {
 
 static int grid_for(int64_t n) {
   return (int)std::min<int64_t>((n + 255) / 256, 4096);
+}
+
+// The BF16 weights from the FP32 parameters (null stream).
+static hipError_t shadow(mlp_net* n) {
+  hipLaunchKernelGGL(shadow_kernel, dim3(W_BLOCKS), dim3(256), 0, nullptr, n->p, n->pb, n->pbT);
+  return hipGetLastError();
 }
 
 extern "C" int mlp_create(int32_t batch_max, uint64_t seed, mlp_net** out) {
@@ -929,6 +1050,13 @@ extern "C" int mlp_create(int32_t batch_max, uint64_t seed, mlp_net** out) {
             hipMalloc(&n->m, NP_DEV * 4) == hipSuccess &&
             hipMalloc(&n->v, NP_DEV * 4) == hipSuccess &&
             hipMalloc(&n->pb, NP_DEV * 2) == hipSuccess &&
+            hipMalloc(&n->pbT, NP_T * 2) == hipSuccess &&
+            hipMalloc(&n->xT, B * NB * 2) == hipSuccess &&
+            hipMalloc(&n->h1T, B * NH * 2) == hipSuccess &&
+            hipMalloc(&n->h2T, B * NH * 2) == hipSuccess &&
+            hipMalloc(&n->dobT, B * NOP * 2) == hipSuccess &&
+            hipMalloc(&n->dz2T, B * NH * 2) == hipSuccess &&
+            hipMalloc(&n->dz1T, B * NH * 2) == hipSuccess &&
             hipMalloc(&n->xbuf, B * NB * 2) == hipSuccess &&
             hipMalloc(&n->h1, B * NH * 2) == hipSuccess &&
             hipMalloc(&n->h2, B * NH * 2) == hipSuccess &&
@@ -938,12 +1066,11 @@ extern "C" int mlp_create(int32_t batch_max, uint64_t seed, mlp_net** out) {
             hipMalloc(&n->dz2f, B * NH * 4) == hipSuccess &&
             hipMalloc(&n->dz1f, B * NH * 4) == hipSuccess &&
             hipMalloc(&n->dz2b, B * NH * 2) == hipSuccess &&
-            hipMalloc(&n->dz1b, B * NH * 2) == hipSuccess &&
             hipMalloc(&n->lrow, B * 4) == hipSuccess &&
             hipMalloc(&n->kpart, (size_t)KPART_ALL * 4) == hipSuccess &&
             hipMalloc(&n->cpart, ((size_t)CS_RC * COLS_ALL + 1) * 4) == hipSuccess &&
             hipMalloc(&n->ybuf, B * DM * 4) == hipSuccess &&
-            hipMalloc(&n->dstep, 8) == hipSuccess &&
+            hipMalloc(&n->dstep, 16) == hipSuccess &&
             hipStreamCreateWithFlags(&n->work, hipStreamNonBlocking) == hipSuccess &&
             hipEventCreateWithFlags(&n->ev_in, hipEventDisableTiming) == hipSuccess &&
             hipEventCreateWithFlags(&n->ev_out, hipEventDisableTiming) == hipSuccess;
@@ -953,9 +1080,9 @@ extern "C" int mlp_create(int32_t batch_max, uint64_t seed, mlp_net** out) {
     delete n;
     return set_error(SBLM_ENOMEM, "mlp_create: device allocation");
   }
-  hipLaunchKernelGGL(mlp_init_kernel, dim3(grid_for(NP_DEV)), dim3(256), 0, nullptr, n->p,
-                     n->pb, seed);
+  hipLaunchKernelGGL(mlp_init_kernel, dim3(grid_for(NP_DEV)), dim3(256), 0, nullptr, n->p, seed);
   int rc = check_hip(hipGetLastError(), "mlp_create: init launch");
+  if (rc == SBLM_OK) rc = check_hip(shadow(n), "mlp_create: shadow launch");
   if (rc == SBLM_OK)
     rc = check_hip(hipMemset(n->g, 0, NP_DEV * 4), "mlp_create: memset");
   if (rc == SBLM_OK)
@@ -1017,9 +1144,7 @@ extern "C" int mlp_set_params(mlp_net* n, const float* params) {
   if (!n || !params) return set_error(SBLM_EINVAL, "mlp_set_params: null argument");
   int rc = copy_canonical(n, n->p, (float*)params, false, "mlp_set_params");
   if (rc != SBLM_OK) return rc;
-  hipLaunchKernelGGL(to_bf16_kernel, dim3(grid_for(NP_DEV)), dim3(256), 0, nullptr, n->p,
-                     n->pb, NP_DEV);
-  rc = check_hip(hipGetLastError(), "mlp_set_params: launch");
+  rc = check_hip(shadow(n), "mlp_set_params: launch");
   if (rc == SBLM_OK) rc = check_hip(hipMemset(n->m, 0, NP_DEV * 4), "mlp_set_params");
   if (rc == SBLM_OK) rc = check_hip(hipMemset(n->v, 0, NP_DEV * 4), "mlp_set_params");
   if (rc == SBLM_OK) rc = check_hip(hipDeviceSynchronize(), "mlp_set_params");
@@ -1048,22 +1173,26 @@ extern "C" int mlp_set_grad(mlp_net* n, const float* grad) {
   return copy_canonical(n, n->g, (float*)grad, false, "mlp_set_grad");
 }
 
-// Forward pass of rows [0, nb) of X (nb % 64 == 0) into n->o.
-static hipError_t forward_rows(mlp_net* n, const uint16_t* X, int nb, hipStream_t st) {
+// Forward pass of rows [0, rows) of X into out [rows][128]; with `train` (rows
+// a multiple of 64) the activations are kept in both orders.
+static hipError_t forward_rows(mlp_net* n, const uint16_t* X, int rows, float* out, hipStream_t st,
+                               bool train) {
+  const int nb = (rows + 63) / 64 * 64;
   GemmArgs g;
   memset(&g, 0, sizeof(g));
-  g.A = X; g.lda = NB; g.B = n->pb + OFF_W1; g.ldb = NH;
-  g.M = nb; g.N = NH; g.K = NB; g.bias = n->p + OFF_B1; g.Cb = n->h1; g.ldc = NH;
+  g.A = X; g.lda = NB; g.B = n->pbT + OFF_T1; g.ldb = NB;
+  g.M = nb; g.m_valid = rows; g.N = NH; g.K = NB; g.bias = n->p + OFF_B1;
+  g.Cb = n->h1; g.ldc = NH; g.CbT = train ? n->h1T : nullptr; g.ldt = n->batch_max;
   g.relu = 1;
-  hipError_t e = gemm(g, true, false, st);
+  hipError_t e = gemm(g, st);
   if (e != hipSuccess) return e;
-  g.A = n->h1; g.lda = NH; g.B = n->pb + OFF_W2; g.ldb = NH; g.K = NH;
-  g.bias = n->p + OFF_B2; g.Cb = n->h2;
-  e = gemm(g, true, false, st);
+  g.A = n->h1; g.lda = NH; g.B = n->pbT + OFF_T2; g.ldb = NH; g.K = NH;
+  g.bias = n->p + OFF_B2; g.Cb = n->h2; g.CbT = train ? n->h2T : nullptr;
+  e = gemm(g, st);
   if (e != hipSuccess) return e;
-  g.A = n->h2; g.B = n->pb + OFF_W3; g.ldb = NOP; g.N = NOP; g.bias = n->p + OFF_B3;
-  g.Cb = nullptr; g.Cf = n->o; g.ldc = NOP; g.relu = 0;
-  return gemm(g, true, false, st);
+  g.A = n->h2; g.B = n->pbT + OFF_T3; g.N = NOP; g.bias = n->p + OFF_B3;
+  g.Cb = nullptr; g.CbT = nullptr; g.Cf = out; g.ldc = NOP; g.relu = 0;
+  return gemm(g, st);
 }
 
 extern "C" int mlp_forward(mlp_net* n, const uint16_t* x, int64_t rows, float* out,
@@ -1073,20 +1202,18 @@ extern "C" int mlp_forward(mlp_net* n, const uint16_t* x, int64_t rows, float* o
   if (rows == 0) return SBLM_OK;
   if (!x || !out) return set_error(SBLM_EINVAL, "mlp_forward: null x or out");
   hipStream_t st = (hipStream_t)stream;
+  // the first product reads the caller's rows in 16-byte pieces where their
+  // address allows it, else a copy of them
+  const bool aligned = ((uintptr_t)x & 15) == 0;
   for (int64_t r0 = 0; r0 < rows; r0 += n->batch_max) {
     const int nr = (int)std::min<int64_t>(n->batch_max, rows - r0);
-    const int nb = (nr + 63) / 64 * 64;
-    hipError_t e = hipMemcpyAsync(n->xbuf, x + r0 * NB, (size_t)nr * NB * 2,
-                                  hipMemcpyDeviceToDevice, st);
-    if (e == hipSuccess && nb > nr) {
-      hipLaunchKernelGGL(fill_u16_kernel, dim3(grid_for((int64_t)(nb - nr) * NB)), dim3(256),
-                         0, st, n->xbuf + (int64_t)nr * NB, (int64_t)(nb - nr) * NB);
-      e = hipGetLastError();
+    const uint16_t* src = x + r0 * NB;
+    hipError_t e = hipSuccess;
+    if (!aligned) {
+      e = hipMemcpyAsync(n->xbuf, src, (size_t)nr * NB * 2, hipMemcpyDeviceToDevice, st);
+      src = n->xbuf;
     }
-    if (e == hipSuccess) e = forward_rows(n, n->xbuf, nb, st);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(out + r0 * NOP, n->o, (size_t)nr * NOP * 4,
-                         hipMemcpyDeviceToDevice, st);
+    if (e == hipSuccess) e = forward_rows(n, src, nr, out + r0 * NOP, st, false);
     if (e != hipSuccess) return check_hip(e, "mlp_forward");
   }
   return SBLM_OK;
@@ -1100,55 +1227,48 @@ static int ksplit_for(int rows) {
   return ks;
 }
 
-// Loss and gradient of a batch.  fold: leave the weight gradients as split-K
-// partials and the bias gradients and the loss as column-sum partials (all
-// summed by adam_graph_kernel) instead of reducing them here.
+// Loss and gradient of a batch whose transposed inputs are in xT already.
+// `dstep` (captured training): leave the weight gradients as split-K partials
+// and the bias gradients and the loss as column-sum partials (all summed by
+// adam_kernel) instead of reducing them here.
 static hipError_t loss_grad(mlp_net* n, const uint16_t* x, const float* y, int rows,
-                            float* loss, hipStream_t st, bool fold = false) {
-  hipError_t e = forward_rows(n, x, rows, st);
+                            float* loss, hipStream_t st, int64_t* dstep = nullptr) {
+  const bool fold = dstep != nullptr;
+  const int64_t ldt = n->batch_max;
+  hipError_t e = forward_rows(n, x, rows, n->o, st, true);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(mlp_nll_kernel, dim3((rows * 8 + 255) / 256), dim3(256), 0, st, n->o, y,
-                     rows, n->dof, n->dob, n->lrow);
+                     rows, n->dof, n->dob, n->dobT, ldt, n->lrow, dstep);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   GemmArgs g;
   memset(&g, 0, sizeof(g));
   // dZ2 = (dO W3^T) * [H2 > 0]
   g.A = n->dob; g.lda = NOP; g.B = n->pb + OFF_W3; g.ldb = NOP;
-  g.M = rows; g.N = NH; g.K = NOP; g.mask = n->h2; g.ldm = NH;
-  g.Cf = n->dz2f; g.Cb = n->dz2b; g.ldc = NH;
-  if ((e = gemm(g, true, true, st)) != hipSuccess) return e;
+  g.M = rows; g.m_valid = rows; g.N = NH; g.K = NOP; g.mask = n->h2; g.ldm = NH;
+  g.Cf = n->dz2f; g.Cb = n->dz2b; g.ldc = NH; g.CbT = n->dz2T; g.ldt = ldt;
+  if ((e = gemm(g, st)) != hipSuccess) return e;
   // dZ1 = (dZ2 W2^T) * [H1 > 0]
   g.A = n->dz2b; g.lda = NH; g.B = n->pb + OFF_W2; g.ldb = NH; g.K = NH;
-  g.mask = n->h1; g.Cf = n->dz1f; g.Cb = n->dz1b;
-  if ((e = gemm(g, true, true, st)) != hipSuccess) return e;
+  g.mask = n->h1; g.Cf = n->dz1f; g.Cb = nullptr; g.CbT = n->dz1T;
+  if ((e = gemm(g, st)) != hipSuccess) return e;
   // weight gradients: gW = (layer input)^T dZ, a contraction over the batch,
-  // cut into K ranges of at least 128 rows (more workgroups, shorter chains)
+  // cut into K ranges of at least 128 rows (more workgroups, shorter chains);
+  // the three products in one launch (independent once dZ1 is known), with
+  // the column sums (bias gradients and the loss) beside them
   const int ks = ksplit_for(rows);
-  struct { const uint16_t* A; int64_t lda; const uint16_t* B; int64_t ldb; int M, N;
-           float* out; float* part; } wg[3] = {
-      {n->h2, NH, n->dob, NOP, NH, NOP, n->g + OFF_W3, n->kpart + KPART_W3},
-      {n->h1, NH, n->dz2b, NH, NH, NH, n->g + OFF_W2, n->kpart + KPART_W2},
-      {x, NB, n->dz1b, NH, NB, NH, n->g + OFF_W1, n->kpart + KPART_W1}};
-  // the three products in one launch (independent once dZ1 is known)
+  struct { const uint16_t *A, *B; int M, N; float *out, *part; } wg[3] = {
+      {n->h2T, n->dobT, NH, NOP, n->g + OFF_W3, n->kpart + KPART_W3},
+      {n->h1T, n->dz2T, NH, NH, n->g + OFF_W2, n->kpart + KPART_W2},
+      {n->xT, n->dz1T, NB, NH, n->g + OFF_W1, n->kpart + KPART_W1}};
   GemmArgs gw[3];
   for (int i = 0; i < 3; ++i) {
     memset(&gw[i], 0, sizeof(gw[i]));
-    gw[i].A = wg[i].A; gw[i].lda = wg[i].lda; gw[i].B = wg[i].B; gw[i].ldb = wg[i].ldb;
-    gw[i].M = wg[i].M; gw[i].N = wg[i].N; gw[i].K = rows; gw[i].ldc = wg[i].N;
+    gw[i].A = wg[i].A; gw[i].lda = ldt; gw[i].B = wg[i].B; gw[i].ldb = ldt;
+    gw[i].M = wg[i].M; gw[i].m_valid = wg[i].M; gw[i].N = wg[i].N; gw[i].K = rows;
+    gw[i].ldc = wg[i].N;
     gw[i].ksplit = ks;
     gw[i].Cf = ks > 1 ? wg[i].part : wg[i].out;
   }
-  if ((e = gemm_group(gw, 3, false, false, st)) != hipSuccess) return e;
-  for (int i = 0; i < 3; ++i) {
-    const GemmArgs& g = gw[i];
-    if (ks > 1 && !fold) {
-      const int64_t mn = (int64_t)g.M * g.N;
-      hipLaunchKernelGGL(splitk_reduce_kernel, dim3(grid_for(mn)), dim3(256), 0, st,
-                         wg[i].part, ks, mn, wg[i].out);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-  }
-  // bias gradients and the loss
   ColSegs cs;
   memset(&cs, 0, sizeof(cs));
   cs.s[0] = {n->dof, NOP, NOP, n->g + OFF_B3};
@@ -1157,7 +1277,21 @@ static hipError_t loss_grad(mlp_net* n, const uint16_t* x, const float* y, int r
   cs.s[3] = {n->lrow, 1, 1, loss ? loss : n->cpart};  // unused slot when no loss
   cs.nseg = loss ? 4 : 3;
   cs.nrow = rows;
-  return colsums(cs, n->cpart, st, !fold);
+  for (int i = 0; i < cs.nseg; ++i) {
+    cs.tile0[i + 1] = cs.tile0[i] + (cs.s[i].ncol + 63) / 64;
+    cs.col0[i + 1] = cs.col0[i] + cs.s[i].ncol;
+  }
+  if ((e = gemm_group(gw, 3, st, &cs, n->cpart)) != hipSuccess || fold) return e;
+  for (int i = 0; i < 3 && ks > 1; ++i) {
+    const int64_t mn = (int64_t)gw[i].M * gw[i].N;
+    hipLaunchKernelGGL(splitk_reduce_kernel, dim3(grid_for(mn)), dim3(256), 0, st, wg[i].part, ks,
+                       mn, wg[i].out);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  const int ncol_all = cs.col0[cs.nseg];
+  hipLaunchKernelGGL(colsum_stage2, dim3((ncol_all + 255) / 256), dim3(256), 0, st, cs, n->cpart,
+                     ncol_all);
+  return hipGetLastError();
 }
 
 extern "C" int mlp_loss_grad(mlp_net* n, const uint16_t* x, const float* y, int32_t rows,
@@ -1168,7 +1302,17 @@ extern "C" int mlp_loss_grad(mlp_net* n, const uint16_t* x, const float* y, int3
     return set_error(SBLM_EINVAL,
                      "mlp_loss_grad: rows = %d must be a multiple of 64 in [64, %d]", rows,
                      n->batch_max);
-  return check_hip(loss_grad(n, x, y, rows, loss, (hipStream_t)stream), "mlp_loss_grad");
+  const hipStream_t st = (hipStream_t)stream;
+  hipLaunchKernelGGL(batch_kernel, dim3(rows / 64, NB / 64), dim3(256), 0, st, x, y, 1, rows,
+                     nullptr, nullptr, n->xT, n->batch_max, nullptr);
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess) e = loss_grad(n, x, y, rows, loss, st);
+  return check_hip(e, "mlp_loss_grad");
+}
+
+static AdamArgs adam_args(mlp_net* n) {
+  const double b1 = 0.9, b2 = 0.999;
+  return {n->p, n->m, n->v, (float)b1, (float)b2, (float)(1.0 - b1), (float)(1.0 - b2), 1e-8f};
 }
 
 static hipError_t adam(mlp_net* n, float lr, hipStream_t st) {
@@ -1176,9 +1320,9 @@ static hipError_t adam(mlp_net* n, float lr, hipStream_t st) {
   n->step += 1;
   const double c1 = 1.0 / (1.0 - pow(b1, (double)n->step));
   const double c2 = 1.0 / (1.0 - pow(b2, (double)n->step));
-  hipLaunchKernelGGL(adam_kernel, dim3(grid_for(NP_DEV)), dim3(256), 0, st, n->p, n->g,
-                     n->m, n->v, n->pb, NP_DEV, lr, (float)b1, (float)b2,
-                     (float)(1.0 - b1), (float)(1.0 - b2), 1e-8f, (float)c1, (float)c2);
+  hipLaunchKernelGGL(adam_kernel, dim3(W_BLOCKS), dim3(256), 0, st, adam_args(n), n->g, n->pb,
+                     n->pbT, lr, (float)c1, (float)c2, nullptr, nullptr, KParts{}, CParts{},
+                     nullptr);
   return hipGetLastError();
 }
 
@@ -1188,59 +1332,39 @@ extern "C" int mlp_adam_step(mlp_net* n, float lr, void* stream) {
   return check_hip(adam(n, lr, (hipStream_t)stream), "mlp_adam_step");
 }
 
-// The captured training step: batch gather, forward, likelihood, backward,
-// Adam with the split-K and column sums, the loss and the step advance.
-// Every pointer it holds belongs
-// to the net (the caller's data is read through the gather node), so one
+// The captured training step: the batch in both orders, forward, likelihood,
+// backward, Adam with the split-K and column sums, the loss and the step
+// counter.  Every pointer it holds belongs
+// to the net (the caller's data is read through the batch node), so one
 // graph serves every step of a call and later calls with the same shape.
 static hipError_t capture_train(mlp_net* n, const uint16_t* x, const float* y, int64_t per,
                                 int batch) {
   hipStream_t w = n->work;
-  const int ks = ksplit_for(batch);
   hipGraph_t graph = nullptr;
   hipError_t e = hipStreamBeginCapture(w, hipStreamCaptureModeThreadLocal);
   if (e != hipSuccess) return e;
-  const int64_t nx = (int64_t)batch * NB / 8 + (int64_t)batch * DM;
-  hipLaunchKernelGGL(batch_gather_kernel, dim3(grid_for(nx)), dim3(256), 0, w, x, y, per, batch,
-                     n->dstep, n->xbuf, n->ybuf);
+  hipLaunchKernelGGL(batch_kernel, dim3(batch / 64, NB / 64), dim3(256), 0, w, x, y, per, batch,
+                     n->dstep, n->xbuf, n->xT, n->batch_max, n->ybuf);
   e = hipGetLastError();
   float* loss_slot = n->cpart + (int64_t)CS_RC * COLS_ALL;
-  if (e == hipSuccess) e = loss_grad(n, n->xbuf, n->ybuf, batch, loss_slot, w, true);
+  if (e == hipSuccess) e = loss_grad(n, n->xbuf, n->ybuf, batch, loss_slot, w, n->dstep);
   if (e == hipSuccess) {
-    const double b1 = 0.9, b2 = 0.999;
     KParts kp;
     kp.part[0] = n->kpart + KPART_W3;
     kp.part[1] = n->kpart + KPART_W2;
     kp.part[2] = n->kpart + KPART_W1;
-    kp.off[0] = OFF_W3;
-    kp.off[1] = OFF_W2;
-    kp.off[2] = OFF_W1;
-    kp.mn[0] = (int64_t)NH * NOP;
-    kp.mn[1] = (int64_t)NH * NH;
-    kp.mn[2] = (int64_t)NB * NH;
-    kp.ks = ks;
+    kp.ks = ksplit_for(batch);
     // the column sums' partials as loss_grad left them (b3, b2, b1, loss)
     CParts cp;
     cp.part = n->cpart;
     cp.ncol_all = COLS_ALL;
-    cp.off[0] = OFF_B3;
-    cp.off[1] = OFF_B2;
-    cp.off[2] = OFF_B1;
-    cp.ncol[0] = NOP;
-    cp.ncol[1] = NH;
-    cp.ncol[2] = NH;
     cp.col0[0] = 0;
     cp.col0[1] = NOP;
     cp.col0[2] = NOP + NH;
     cp.loss_col = NOP + 2 * NH;
-    hipLaunchKernelGGL(adam_graph_kernel, dim3(grid_for(NP_DEV)), dim3(256), 0, w, n->p, n->g,
-                       n->m, n->v, n->pb, NP_DEV, n->sched, n->dstep, kp, cp, (float)b1,
-                       (float)b2, (float)(1.0 - b1), (float)(1.0 - b2), 1e-8f);
+    hipLaunchKernelGGL(adam_kernel, dim3(W_BLOCKS), dim3(256), 0, w, adam_args(n), n->g, n->pb,
+                       n->pbT, 0.0f, 0.0f, 0.0f, n->sched, n->dstep, kp, cp, n->losses);
     e = hipGetLastError();
-    if (e == hipSuccess) {
-      hipLaunchKernelGGL(step_advance_kernel, dim3(1), dim3(1), 0, w, n->dstep, cp, n->losses);
-      e = hipGetLastError();
-    }
   }
   const hipError_t e_end = hipStreamEndCapture(w, &graph);
   if (e == hipSuccess) e = e_end;

@@ -155,6 +155,74 @@ def test_forward_matches_oracle(hip, rows):
     net.close()
 
 
+def test_forward_is_the_same_in_every_tiling(hip):
+    # the same chain of matrix instructions per output whatever the rows: one
+    # call over 9001 rows (64 x 64 tiles, two buffers), calls of 1 to 2048 rows
+    # (32 x 32 tiles and 64 x 64 tiles with all of K in one stage, a last tile
+    # with a single row) and rows at an address off 16 bytes, bit for bit
+    rng = np.random.default_rng(17)
+    x = torch.tensor(rng.normal(size=(9001, 256)), device="cuda").to(torch.bfloat16)
+    net = hip.MLP(batch_max=9024, seed=5)
+    ref = net.forward(x)
+    r0 = 0
+    for rows in (1, 63, 64, 65, 511, 1024, 1025, 2048):
+        assert torch.equal(net.forward(x[r0:r0 + rows]), ref[r0:r0 + rows]), rows
+        r0 += rows
+    off = torch.empty(200 * 256 + 1, dtype=torch.bfloat16, device="cuda")[1:].view(200, 256)
+    off.copy_(x[:200])
+    assert off.data_ptr() % 16 != 0
+    assert torch.equal(net.forward(off), ref[:200])
+    net.close()
+
+
+@pytest.mark.parametrize("rows", [64, 192, 320, 1024, 4096])
+def test_gradients_by_batch_size(hip, rows):
+    # K ranges of 64 and of 128 rows, one range and several: loss and gradients
+    # against an FP64 evaluation that rounds to BF16 where the kernels do
+    # (activations, output and hidden-layer gradients).  What is left is the
+    # FP32 accumulation (1e-6 of the sums), which flips about 1e-3 of the
+    # roundings by 2^-8: 1e-4 in the 2-norm, up to ten times that through the
+    # likelihood's exponentials
+    rng = np.random.default_rng(rows)
+    p = M.init_params(rng, scale_out=0.3)
+    net = hip.MLP(batch_max=4096, seed=1)
+    net.set_params(canon(p).astype(np.float32))
+    xb = torch.tensor(rng.normal(size=(rows, 256)), device="cuda").to(torch.bfloat16)
+    y = torch.tensor(rng.uniform(size=(rows, 7)), dtype=torch.float32, device="cuda")
+    loss = net.loss_grad(xb, y).item()
+    got = net.grad().astype(np.float64)
+    bf = lambda v: v.to(torch.bfloat16).double()
+    sizes = [256 * 512, 512, 512 * 512, 512, 512 * 120, 120]
+    W1, b1, W2, b2, W3, b3 = torch.split(torch.tensor(canon(p).astype(np.float32),
+                                                      device="cuda"), sizes)
+    W1, W2, W3 = bf(W1).view(256, 512), bf(W2).view(512, 512), bf(W3).view(512, 120)
+    x = xb.double()
+    h1 = bf(torch.relu(x @ W1 + b1.double()))
+    h2 = bf(torch.relu(h1 @ W2 + b2.double()))
+    o = (h2 @ W3 + b3.double()).requires_grad_()
+    mu, ls = o[:, 8:64].view(-1, 8, 7), o[:, 64:].view(-1, 8, 7)
+    r = y.double()[:, None, :] - mu
+    wrap = torch.zeros_like(r)
+    wrap[..., 3] = torch.floor(r[..., 3].detach() + 0.5)
+    r = r - wrap
+    a = torch.log_softmax(o[:, :8], 1) + \
+        (-0.5 * r ** 2 * torch.exp(-2 * ls) - ls - 0.5 * math.log(2 * math.pi)).sum(-1)
+    nll = -torch.logsumexp(a, 1).mean()
+    nll.backward()
+    dO = o.grad
+    dz2 = (bf(dO) @ W3.T) * (h2 > 0)
+    dz1 = (bf(dz2) @ W2.T) * (h1 > 0)
+    ref = [x.T @ bf(dz1), dz1.sum(0), h1.T @ bf(dz2), dz2.sum(0), h2.T @ bf(dO), dO.sum(0)]
+    assert abs(loss - nll.item()) < 5e-3 * abs(nll.item())
+    o0 = 0
+    for q in ref:
+        q = q.cpu().numpy().ravel()
+        g = got[o0:o0 + q.size]
+        assert np.linalg.norm(g - q) < 5e-3 * np.linalg.norm(q), (rows, o0)
+        o0 += q.size
+    net.close()
+
+
 def f32(a):
     return np.asarray(a, np.float64).astype(np.float32).astype(np.float64)
 
