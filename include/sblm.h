@@ -647,8 +647,9 @@ int mlp_get_params(mlp_net* net, float* params);
 /*
  * mlp_forward -- network output for `rows` inputs.
  *   x    [rows][256] BF16, device;   out  [rows][128] FP32, device
- * Any rows >= 0; processed in chunks of batch_max through the network's own
- * buffers (so calls on one network must not overlap).
+ * Any rows >= 0.  x at an address off 16 bytes is copied first, in chunks of
+ * batch_max, to the network's own buffer (so calls on one network must not
+ * overlap).
  */
 int mlp_forward(mlp_net* net, const uint16_t* x, int64_t rows, float* out,
                 void* stream);

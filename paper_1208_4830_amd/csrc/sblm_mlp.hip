@@ -56,49 +56,28 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
 
 // ------------------------------------------------------------------ GEMM
 //
-// C[M][N] = A[M][K] * B[N][K]^T on BF16 operands, k contiguous in both, with
-// FP32 accumulation in the 32x32x16 matrix-core instruction, k ascending
-// (every output is the same chain of instructions in any tiling below).  A
-// workgroup of four waves owns a TILE x TILE tile of C, K advancing through
-// LDS in stages of TKS (row stride padded by 8: conflict-free 16-byte reads
-// of a lane's 8 consecutive k).
-//
-// At the network's sizes (K = 128 ... 512, 128 tiles) a product is bound by
-// latency, not by the matrix cores: so where one stage holds all of K (NBUF =
-// 1) a tile's loads are all in flight at once and one barrier separates them
-// from the products, and 32 x 32 tiles replace 64 x 64 ones that would leave
-// half of the compute units without work.  Grids of more than 256 tiles and
-// longer sums go through two buffers of 128 k (two workgroups per compute
-// unit, the next stage's loads in flight during the products).  1024 rows,
-// K = 512: 9.5 us per product in stages of 128 with the operands transposed
-// on their way to LDS, 8.5 us so (32 x 32 tiles, N = 128: 9.4, 7.0 us).
-//
-// Every operand exists in the layout that its product reads: the weights and
-// the batch's activations and gradients are kept in both orders, written
-// together by the kernels that produce them.
-// Epilogue: + bias[n], then * (mask[m][n] > 0), then ReLU, written as FP32
-// and/or BF16 and/or transposed BF16.  Requires M, N % TILE == 0, K % (32 *
-// ksplit) == 0.  Rows of A beyond m_valid repeat the last valid one, and C's
-// are not written.  With ksplit > 1 (the weight gradients, a contraction over
-// the batch) each K range writes its own FP32 partial (no bias, mask or ReLU)
-// and splitk_reduce_kernel or the Adam kernel adds them in order.
+// The weight gradients: C[M][N] = A[M][K] * B[N][K]^T on BF16 operands, k (the
+// batch row) contiguous in both, with FP32 accumulation in the 32x32x16
+// matrix-core instruction, k ascending (every output is the same chain of
+// instructions in any tiling below).  A workgroup of four waves owns a TILE x
+// TILE tile of C, K advancing through LDS in stages of TKS (row stride padded
+// by 8: conflict-free 16-byte reads of a lane's 8 consecutive k).  At batch
+// 1024 (eight ranges of 128 rows) one stage holds a range (NBUF = 1): a
+// tile's loads are all in flight at once and one barrier separates them from
+// the products; longer sums go through two buffers, the next stage's loads in
+// flight during the products.  32 x 32 tiles replace 64 x 64 ones that would
+// leave half of the compute units without work (batches below 256).
+// Requires M, N % 64 == 0, K % (32 * ksplit) == 0.  With ksplit > 1 each K range
+// writes its own partial, and splitk_reduce_kernel or the Adam kernel adds
+// them in order.
 struct GemmArgs {
-  const uint16_t* A;     // [M][lda]
+  const uint16_t* A;  // [M][lda]
   int64_t lda;
-  const uint16_t* B;     // [N][ldb]
+  const uint16_t* B;  // [N][ldb]
   int64_t ldb;
   int M, N, K;
-  int m_valid;           // rows of A and C that exist
-  const float* bias;     // [N] or null
-  const uint16_t* mask;  // [M][ldm] BF16 or null
-  int64_t ldm;
-  float* Cf;             // [M][ldc] or null (with ksplit > 1: [ksplit][M][ldc])
-  uint16_t* Cb;          // [M][ldc] or null
-  int64_t ldc;
-  uint16_t* CbT;         // [N][ldt] or null
-  int64_t ldt;
-  int relu;
-  int ksplit;            // K is cut into ksplit equal ranges (blockIdx.z), 0/1: none
+  float* C;           // [M][N] (with ksplit > 1: [ksplit][M][N])
+  int ksplit;         // K is cut into ksplit equal ranges (blockIdx.z), 0/1: none
 };
 
 // Column sums that ride along in a GEMM launch (colsum_block): the work of
@@ -176,11 +155,11 @@ constexpr int STAGE_CHUNKS = TILE * TKS / 8 / 256;
 
 template <int TILE, int TKS>
 __device__ __forceinline__ void load_tile(const uint16_t* __restrict__ X, int64_t ld, int r0,
-                                          int r_last, int k0, uint4* v) {
+                                          int k0, uint4* v) {
 #pragma unroll
   for (int j = 0; j < STAGE_CHUNKS<TILE, TKS>; ++j) {
-    const int q = threadIdx.x + 256 * j, r = min(r0 + q / (TKS / 8), r_last);
-    v[j] = *(const uint4*)(X + (int64_t)r * ld + k0 + (q % (TKS / 8)) * 8);
+    const int q = threadIdx.x + 256 * j;
+    v[j] = *(const uint4*)(X + (int64_t)(r0 + q / (TKS / 8)) * ld + k0 + (q % (TKS / 8)) * 8);
   }
 }
 
@@ -235,8 +214,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmGroup gg) {
   };
   constexpr int NC = STAGE_CHUNKS<TILE, TKS>;
   uint4 ra[NC], rb[NC];
-  load_tile<TILE, TKS>(g.A, g.lda, m0, g.m_valid - 1, kb, ra);
-  load_tile<TILE, TKS>(g.B, g.ldb, n0, g.N - 1, kb, rb);
+  load_tile<TILE, TKS>(g.A, g.lda, m0, kb, ra);
+  load_tile<TILE, TKS>(g.B, g.ldb, n0, kb, rb);
   store_tile<TILE, TKS>(sA[0], ra);
   store_tile<TILE, TKS>(sB[0], rb);
   __syncthreads();
@@ -247,8 +226,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmGroup gg) {
   if constexpr (NBUF > 1) {
     for (int s = 0; s + 1 < nst; ++s) {
       const int cur = s & 1;
-      load_tile<TILE, TKS>(g.A, g.lda, m0, g.m_valid - 1, kb + (s + 1) * TKS, ra);
-      load_tile<TILE, TKS>(g.B, g.ldb, n0, g.N - 1, kb + (s + 1) * TKS, rb);
+      load_tile<TILE, TKS>(g.A, g.lda, m0, kb + (s + 1) * TKS, ra);
+      load_tile<TILE, TKS>(g.B, g.ldb, n0, kb + (s + 1) * TKS, rb);
       mfma_stage(cur);
       store_tile<TILE, TKS>(sA[cur ^ 1], ra);
       store_tile<TILE, TKS>(sB[cur ^ 1], rb);
@@ -259,29 +238,10 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmGroup gg) {
   if (!multiplies) return;
 
   // lane l, register r holds C[(r%4) + 8(r/4) + 4(l/32)][l%32] of the wave
-  const int n = n0 + wn + (lane & 31);
-  const float bias = g.bias ? g.bias[n] : 0.0f;
+  float* C = g.C + (int64_t)blockIdx.z * g.M * g.N + n0 + wn + (lane & 31);
 #pragma unroll
-  for (int r4 = 0; r4 < 4; ++r4) {
-    const int mb = m0 + wm + 8 * r4 + 4 * (lane >> 5);
-    uint16_t h4[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int m = mb + i;
-      float v = acc[4 * r4 + i] + bias;
-      if (g.mask) {
-        const uint16_t h = g.mask[(int64_t)m * g.ldm + n];
-        if (h == 0 || (h & 0x8000u)) v = 0.0f;
-      }
-      if (g.relu) v = fmaxf(v, 0.0f);
-      h4[i] = f2bf(v);
-      if (m < g.m_valid) {
-        if (g.Cf) g.Cf[(int64_t)blockIdx.z * g.M * g.ldc + (int64_t)m * g.ldc + n] = v;
-        if (g.Cb) g.Cb[(int64_t)m * g.ldc + n] = h4[i];
-      }
-    }
-    if (g.CbT) *(ushort4*)(g.CbT + (int64_t)n * g.ldt + mb) = {h4[0], h4[1], h4[2], h4[3]};
-  }
+  for (int r = 0; r < 16; ++r)
+    C[(int64_t)(m0 + wm + (r & 3) + 8 * (r >> 2) + 4 * (lane >> 5)) * g.N] = acc[r];
 }
 
 // C = A B^T for n (1..3) problems with the same K, K split and tile size, and
@@ -312,22 +272,14 @@ hipError_t gemm_group(const GemmArgs* gs, int n, hipStream_t st, const ColSegs* 
     hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, gg);
     return hipGetLastError();
   };
-  const bool one = tile == 32 || tiles64 * ks <= 256 || K == 128;  // all of K in one stage
   if (tile == 64) {
-    if (one && K == 512) return run(gemm_bf16_kernel<64, 512, 1>);
-    if (one && K == 256) return run(gemm_bf16_kernel<64, 256, 1>);
-    if (one && K == 128) return run(gemm_bf16_kernel<64, 128, 1>);
+    if (K == 128) return run(gemm_bf16_kernel<64, 128, 1>);
     if (K % 128 == 0) return run(gemm_bf16_kernel<64, 128, 2>);
     return run(gemm_bf16_kernel<64, 32, 2>);
   }
-  if (K == 512) return run(gemm_bf16_kernel<32, 512, 1>);
-  if (K == 256) return run(gemm_bf16_kernel<32, 256, 1>);
   if (K == 128) return run(gemm_bf16_kernel<32, 128, 1>);
-  if (K % 128 == 0) return run(gemm_bf16_kernel<32, 128, 2>);
   return run(gemm_bf16_kernel<32, 64, 2>);
 }
-
-hipError_t gemm(const GemmArgs& g, hipStream_t st) { return gemm_group(&g, 1, st); }
 
 // --------------------------------------------------- mixture likelihood
 //
@@ -353,20 +305,9 @@ __device__ __forceinline__ double grp8_sum(double v) {
   return v;
 }
 
-__global__ __launch_bounds__(256) void mlp_nll_kernel(const float* O, const float* y, int n,
-                                                      float* dOf, uint16_t* dOb, uint16_t* dObT,
-                                                      int64_t ldt, float* loss_row,
-                                                      int64_t* dstep) {
-  __shared__ float tile[32][NOP + 1];
-  // (captured training: the step's index for the kernels after this one,
-  // while the Adam kernel advances the counter for the next step)
-  if (dstep && blockIdx.x == 0 && threadIdx.x == 0) dstep[1] = dstep[0];
-  const int gid = blockIdx.x * blockDim.x + threadIdx.x;
-  const int b = gid >> 3, k = gid & 7;  // n * 8 threads, a multiple of 64
-  const bool valid = b < n;
-  const int bb = valid ? b : 0;
-  const float* o = O + (int64_t)bb * NOP;
-  const double inv_n = 1.0 / (double)n;
+// One sample's row in LDS: its outputs on entry, dO on return (thread k reads
+// and writes component k's entries only).  Returns the row's loss.
+__device__ __forceinline__ float nll_row(float* o, const float* y, int k, double inv_n) {
   const double HALF_LOG_2PI = 0.91893853320467274178;
   const double logit = (double)o[k];
   const double lse_l = [&] {
@@ -377,7 +318,7 @@ __global__ __launch_bounds__(256) void mlp_nll_kernel(const float* O, const floa
   double a = logit - lse_l;
 #pragma unroll
   for (int d = 0; d < DM; ++d) {
-    double rr = (double)y[(int64_t)bb * DM + d] - (double)o[KM + k * DM + d];
+    double rr = (double)y[d] - (double)o[KM + k * DM + d];
     if (d == MLP_PERIODIC) rr -= floor(rr + 0.5);
     const double ls = (double)o[KM + KM * DM + k * DM + d];
     is2[d] = exp(-2.0 * ls);
@@ -388,30 +329,223 @@ __global__ __launch_bounds__(256) void mlp_nll_kernel(const float* O, const floa
   const double lp = amax + log(grp8_sum(exp(a - amax)));
   const double gam = exp(a - lp);
   const double pi = exp(logit - lse_l);
-  if (valid && k == 0) loss_row[b] = (float)(-lp * inv_n);
-  float* row = tile[threadIdx.x >> 3];
-  row[k] = (float)((pi - gam) * inv_n);
+  o[k] = (float)((pi - gam) * inv_n);
 #pragma unroll
   for (int d = 0; d < DM; ++d) {
-    row[KM + k * DM + d] = (float)(-gam * r[d] * is2[d] * inv_n);
-    row[KM + KM * DM + k * DM + d] = (float)(-gam * (r[d] * r[d] * is2[d] - 1.0) * inv_n);
+    o[KM + k * DM + d] = (float)(-gam * r[d] * is2[d] * inv_n);
+    o[KM + KM * DM + k * DM + d] = (float)(-gam * (r[d] * r[d] * is2[d] - 1.0) * inv_n);
   }
-  row[NO + k] = 0.0f;  // the eight pad columns
+  o[NO + k] = 0.0f;  // the eight pad columns
+  return (float)(-lp * inv_n);
+}
+
+// ------------------------------------------------------- rows of a batch
+//
+// Everything that a sample's row goes through on its own: the three layers,
+// and in training the likelihood and the gradients of the two hidden layers.
+// A block of 16 waves takes 32 rows and keeps their activations in LDS; each
+// wave owns 32 of a layer's 512 columns (the output's 128: four waves) and
+// streams their weights from L2 in the order in which its matrix instructions
+// take them ("fragments": 64 lanes x 16 bytes per 32 columns x 16 k), eight
+// fragments in flight, a layer's first ones issued before the barrier that
+// ends the layer before.  k ascends, so every output is the same chain of
+// instructions as in a product of its own.  Bound by the weights' way into
+// the block (0.9 MB forward, 1.6 MB with the gradients) and by the chain of
+// five products; with a launch per product (7 to 11 us each, most of it the
+// launch and one round trip to memory) 1024 rows took 24 us forward and 54 us
+// with the gradients, here 16 and 29.
+// Written for the weight gradients (training): inputs, activations and
+// gradients transposed [columns][ldt]; for the bias gradients the FP32
+// gradients; the rows' losses.
+constexpr int FRAG = 512;  // elements of a fragment
+// fragment arrays of the weights: W1, W2, W3 by (output column, input k), and
+// for the gradients W2, W3 by (input column, output k)
+constexpr int64_t OFF_F1 = 0;
+constexpr int64_t OFF_F2 = OFF_F1 + (int64_t)NB * NH;
+constexpr int64_t OFF_F3 = OFF_F2 + (int64_t)NH * NH;
+constexpr int64_t OFF_R2 = OFF_F3 + (int64_t)NH * NOP;
+constexpr int64_t OFF_R3 = OFF_R2 + (int64_t)NH * NH;
+constexpr int64_t N_FRAG = OFF_R3 + (int64_t)NH * NOP;
+
+struct RowArgs {
+  const uint16_t* x;  // [rows][256]
+  int64_t rows;
+  const uint16_t* wf;  // fragments
+  const float* p;      // parameters (the biases)
+  float* out;          // [rows][128] (inference)
+  // training
+  const float* y;      // [rows][7]
+  uint16_t *xT, *h1T, *h2T, *dobT, *dz2T, *dz1T;  // [columns][ldt]
+  int64_t ldt;
+  float *dof, *dz2f, *dz1f, *lrow;
+  // captured training: rows [k mod per) * rows ... of (x, y), k = dstep[0],
+  // which is noted in dstep[1] for the kernels after this one (the Adam
+  // kernel moves dstep[0] on)
+  int64_t* dstep;
+  int64_t per;
+};
+
+constexpr int RB = 32;                       // rows of a block
+constexpr int SX = NB + 8, SH = NH + 8, SD = NOP + 8, SO = NOP + 4;  // padded LDS rows
+constexpr int PF = 8;                        // fragments in flight
+
+__device__ __forceinline__ void frag_load(uint4* pre, const uint4* __restrict__ f) {
+#pragma unroll
+  for (int i = 0; i < PF; ++i) pre[i] = f[i * 64];
+}
+// acc += (32 rows at pa, a lane's row and half of 16 k) x (KB fragments at f,
+// the first PF of them in pre)
+template <int KB>
+__device__ __forceinline__ f32x16 frag_mul(const uint16_t* pa, const uint4* __restrict__ f,
+                                           uint4* pre) {
+  f32x16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+#pragma unroll
+  for (int kb = 0; kb < KB; ++kb) {
+    const bf16x8 a = *(const bf16x8*)(pa + 16 * kb);
+    const uint4 w = pre[kb % PF];
+    if (kb + PF < KB) pre[kb % PF] = f[(kb + PF) * 64];
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8, w), acc, 0, 0, 0);
+  }
+  return acc;
+}
+// Row of accumulator register r in lane l: (r % 4) + 8 (r / 4) + 4 (l / 32);
+// its column: l % 32.
+__device__ __forceinline__ int acc_row(int r, int lane) {
+  return (r & 3) + 8 * (r >> 2) + 4 * (lane >> 5);
+}
+// Four consecutive rows of a lane's column, transposed to global memory.
+__device__ __forceinline__ void store_t(uint16_t* T, int64_t ldt, int n, int64_t row,
+                                        const uint16_t* h) {
+  *(ushort4*)(T + (int64_t)n * ldt + row) = {h[0], h[1], h[2], h[3]};
+}
+
+template <bool TRAIN>
+__global__ __launch_bounds__(1024) void net_rows_kernel(RowArgs a) {
+  __shared__ __attribute__((aligned(16))) uint16_t sX[RB * SX], sH1[RB * SH], sH2[RB * SH];
+  __shared__ __attribute__((aligned(16))) float sO[TRAIN ? RB * SO : 4];
+  __shared__ __attribute__((aligned(16))) uint16_t sD[TRAIN ? RB * SD : 8];
+  __shared__ __attribute__((aligned(16))) uint16_t sZ[TRAIN ? RB * SH : 8];
+  const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
+  const int64_t row0 = (int64_t)blockIdx.x * RB;
+  int64_t r0 = 0;
+  if (TRAIN && a.dstep) {
+    r0 = (a.dstep[0] % a.per) * a.rows;
+    if (blockIdx.x == 0 && t == 0) a.dstep[1] = a.dstep[0];
+  }
+  const uint4* wf = (const uint4*)a.wf + lane;
+  const uint4* f1 = wf + (OFF_F1 + (int64_t)wave * (NB / 16) * FRAG) / 8;
+  const uint4* f2 = wf + (OFF_F2 + (int64_t)wave * (NH / 16) * FRAG) / 8;
+  const uint4* f3 = wf + (OFF_F3 + (int64_t)(wave & 3) * (NH / 16) * FRAG) / 8;
+  const uint4* g2 = wf + (OFF_R2 + (int64_t)wave * (NH / 16) * FRAG) / 8;
+  const uint4* g3 = wf + (OFF_R3 + (int64_t)wave * (NOP / 16) * FRAG) / 8;
+  const int pr = lane & 31, pk = 8 * (lane >> 5);  // the lane's row and k in LDS
+  const int n = 32 * wave + pr;                    // its column in a hidden layer
+  uint4 pre[PF];
+  frag_load(pre, f1);
+  {
+    const int64_t r = row0 + (t >> 5);
+    const uint4 v =
+        *(const uint4*)(a.x + (r0 + (r < a.rows ? r : a.rows - 1)) * NB + (t & 31) * 8);
+    *(uint4*)(sX + (t >> 5) * SX + (t & 31) * 8) = v;
+  }
   __syncthreads();
-  // the block's 32 rows, in both orders
-  const int b0 = blockIdx.x * 32;
-#pragma unroll 4
-  for (int e = threadIdx.x; e < 32 * NOP; e += 256) {
-    const int i = e / NOP, c = e % NOP;
-    if (b0 + i < n) {
-      dOf[(int64_t)(b0 + i) * NOP + c] = tile[i][c];
-      dOb[(int64_t)(b0 + i) * NOP + c] = f2bf(tile[i][c]);
+  // hidden layers: bias, ReLU
+  auto hidden = [&](const f32x16& acc, float bias, uint16_t* sH, uint16_t* T) {
+#pragma unroll
+    for (int r4 = 0; r4 < 4; ++r4) {
+      uint16_t h[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        h[i] = f2bf(fmaxf(acc[4 * r4 + i] + bias, 0.0f));
+        sH[acc_row(4 * r4 + i, lane) * SH + n] = h[i];
+      }
+      if (TRAIN) store_t(T, a.ldt, n, row0 + acc_row(4 * r4, lane), h);
+    }
+  };
+  {
+    const float b1 = a.p[OFF_B1 + n];
+    const f32x16 acc = frag_mul<NB / 16>(sX + pr * SX + pk, f1, pre);
+    frag_load(pre, f2);
+    hidden(acc, b1, sH1, a.h1T);
+  }
+  if (TRAIN) {  // the inputs transposed: 8 rows of a column per thread
+    const int c = t >> 2, rb = (t & 3) * 8;
+    uint16_t o[8] __attribute__((aligned(16)));
+#pragma unroll
+    for (int i = 0; i < 8; ++i) o[i] = sX[(rb + i) * SX + c];
+    *(uint4*)(a.xT + (int64_t)c * a.ldt + row0 + rb) = *(const uint4*)o;
+  }
+  __syncthreads();
+  {
+    const float b2 = a.p[OFF_B2 + n];
+    const f32x16 acc = frag_mul<NH / 16>(sH1 + pr * SH + pk, f2, pre);
+    if (wave < 4)
+      frag_load(pre, f3);
+    else if (TRAIN)
+      frag_load(pre, g3);
+    hidden(acc, b2, sH2, a.h2T);
+  }
+  __syncthreads();
+  if (wave < 4) {
+    const float b3 = a.p[OFF_B3 + n];
+    const f32x16 acc = frag_mul<NH / 16>(sH2 + pr * SH + pk, f3, pre);
+    if (TRAIN) frag_load(pre, g3);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int m = acc_row(r, lane);
+      if constexpr (TRAIN)
+        sO[m * SO + n] = acc[r] + b3;
+      else if (row0 + m < a.rows)
+        a.out[(row0 + m) * NOP + n] = acc[r] + b3;
     }
   }
-#pragma unroll 4
-  for (int e = threadIdx.x; e < 32 * NOP; e += 256) {
-    const int c = e / 32, i = e % 32;
-    if (b0 + i < n) dObT[c * ldt + b0 + i] = f2bf(tile[i][c]);
+  if constexpr (TRAIN) {
+    __syncthreads();
+    if (wave < 4) {
+      const int i = t >> 3, k = t & 7;
+      const float l = nll_row(sO + i * SO, a.y + (r0 + row0 + i) * DM, k, 1.0 / (double)a.rows);
+      if (k == 0) a.lrow[row0 + i] = l;
+    }
+    __syncthreads();
+    {  // dO in FP32, in BF16 for the product below and transposed
+      const int i = t >> 5, c = (t & 31) * 4;
+      const float4 v = *(const float4*)(sO + i * SO + c);
+      *(float4*)(a.dof + (row0 + i) * NOP + c) = v;
+      *(ushort4*)(sD + i * SD + c) = {f2bf(v.x), f2bf(v.y), f2bf(v.z), f2bf(v.w)};
+      const int ct = t >> 3, rt = (t & 7) * 4;
+      uint16_t h[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) h[j] = f2bf(sO[(rt + j) * SO + ct]);
+      store_t(a.dobT, a.ldt, ct, row0 + rt, h);
+    }
+    __syncthreads();
+    // dZ = (gradient of the layer above) W^T * [H > 0]
+    auto grad = [&](const f32x16& acc, const uint16_t* sH, uint16_t* sZ_, float* F, uint16_t* T) {
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4) {
+        uint16_t h[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int m = acc_row(4 * r4 + i, lane);
+          const uint16_t act = sH[m * SH + n];
+          const float v = (act == 0 || (act & 0x8000u)) ? 0.0f : acc[4 * r4 + i];
+          h[i] = f2bf(v);
+          if (sZ_) sZ_[m * SH + n] = h[i];
+          F[(row0 + m) * NH + n] = v;
+        }
+        store_t(T, a.ldt, n, row0 + acc_row(4 * r4, lane), h);
+      }
+    };
+    {
+      const f32x16 acc = frag_mul<NOP / 16>(sD + pr * SD + pk, g3, pre);
+      frag_load(pre, g2);
+      grad(acc, sH2, sZ, a.dz2f, a.dz2T);
+    }
+    __syncthreads();
+    const f32x16 acc = frag_mul<NH / 16>(sZ + pr * SH + pk, g2, pre);
+    grad(acc, sH1, nullptr, a.dz1f, a.dz1T);
   }
 }
 
@@ -432,14 +566,10 @@ constexpr int WT1 = (NB / 32) * (NH / 32), WT2 = (NH / 32) * (NH / 32),
 constexpr int W_TILES = WT1 + WT2 + WT3;
 constexpr int N_BIAS = NH + NH + NOP;
 constexpr int W_BLOCKS = W_TILES + (N_BIAS + 255) / 256;
-// The transposed BF16 weights, W1 [512][256], W2 [512][512], W3 [128][512].
-constexpr int64_t OFF_T1 = 0;
-constexpr int64_t OFF_T2 = OFF_T1 + (int64_t)NB * NH;
-constexpr int64_t OFF_T3 = OFF_T2 + (int64_t)NH * NH;
-constexpr int64_t NP_T = OFF_T3 + (int64_t)NH * NOP;
-
 struct WTile {
-  int64_t off, off_t;  // the matrix in the parameters and among the transposed
+  int64_t off;         // the matrix in the parameters
+  int64_t off_f;       // its fragments for the forward pass and, if any, for
+  int64_t off_r;       // the gradients (-1: none)
   int rows, cols;      // [rows = inputs][cols = outputs]
   int r0, c0;          // the tile's first row and column
   int tensor;          // 0: W3, 1: W2, 2: W1 (the order of KParts)
@@ -447,11 +577,11 @@ struct WTile {
 __device__ __forceinline__ WTile weight_tile(int b) {
   WTile w;
   if (b < WT1)
-    w = {OFF_W1, OFF_T1, NB, NH, 0, 0, 2};
+    w = {OFF_W1, OFF_F1, -1, NB, NH, 0, 0, 2};
   else if (b < WT1 + WT2)
-    w = {OFF_W2, OFF_T2, NH, NH, 0, 0, 1}, b -= WT1;
+    w = {OFF_W2, OFF_F2, OFF_R2, NH, NH, 0, 0, 1}, b -= WT1;
   else
-    w = {OFF_W3, OFF_T3, NH, NOP, 0, 0, 0}, b -= WT1 + WT2;
+    w = {OFF_W3, OFF_F3, OFF_R3, NH, NOP, 0, 0, 0}, b -= WT1 + WT2;
   w.r0 = b / (w.cols / 32) * 32;
   w.c0 = b % (w.cols / 32) * 32;
   return w;
@@ -461,34 +591,35 @@ __device__ __forceinline__ int64_t bias_index(int e) {
   return e < NH ? OFF_B1 + e : e < 2 * NH ? OFF_B2 + (e - NH) : OFF_B3 + (e - 2 * NH);
 }
 
-// Transposed copy of a 32 x 32 tile: thread t holds row t / 8, columns 4 (t %
-// 8) .. + 3 in h.
-__device__ __forceinline__ void store_tile_t(const WTile& w, ushort4 h, uint16_t* pbT,
-                                             uint16_t (*sh)[36]) {
+// Element (column n, k) of a fragment array with KB fragments per 32 columns.
+__device__ __forceinline__ int64_t frag_index(int n, int k, int KB) {
+  return ((int64_t)(n / 32 * KB + k / 16) * 64 + (n & 31) + 32 * ((k >> 3) & 1)) * 8 + (k & 7);
+}
+
+// The BF16 weights of a 32 x 32 tile into the fragment arrays: thread t holds
+// row t / 8, columns 4 (t % 8) .. + 3 in h.
+__device__ __forceinline__ void store_frags(const WTile& w, ushort4 h, uint16_t* wf,
+                                            uint16_t (*sh)[36]) {
   const int t = threadIdx.x, r = t >> 3, c = (t & 7) * 4;
+  if (w.off_r >= 0)
+    *(ushort4*)(wf + w.off_r + frag_index(w.r0 + r, w.c0 + c, w.cols / 16)) = h;
   sh[c][r] = h.x;
   sh[c + 1][r] = h.y;
   sh[c + 2][r] = h.z;
   sh[c + 3][r] = h.w;
   __syncthreads();
-  *(ushort4*)(pbT + w.off_t + (int64_t)(w.c0 + r) * w.rows + w.r0 + c) = *(ushort4*)&sh[r][c];
+  *(ushort4*)(wf + w.off_f + frag_index(w.c0 + r, w.r0 + c, w.rows / 16)) =
+      *(const ushort4*)&sh[r][c];
 }
 
-// The BF16 weights of the FP32 parameters, in both orders.
-__global__ __launch_bounds__(256) void shadow_kernel(const float* p, uint16_t* pb, uint16_t* pbT) {
+// The BF16 weights of the FP32 parameters.
+__global__ __launch_bounds__(256) void shadow_kernel(const float* p, uint16_t* wf) {
   __shared__ __attribute__((aligned(8))) uint16_t sh[32][36];
-  const int b = blockIdx.x, t = threadIdx.x;
-  if (b >= W_TILES) {
-    const int e = (b - W_TILES) * 256 + t;
-    if (e < N_BIAS) pb[bias_index(e)] = f2bf(p[bias_index(e)]);
-    return;
-  }
-  const WTile w = weight_tile(b);
+  const int t = threadIdx.x;
+  const WTile w = weight_tile(blockIdx.x);
   const int64_t i = w.off + (int64_t)(w.r0 + (t >> 3)) * w.cols + w.c0 + (t & 7) * 4;
   const float4 x = *(const float4*)(p + i);
-  const ushort4 h = {f2bf(x.x), f2bf(x.y), f2bf(x.z), f2bf(x.w)};
-  *(ushort4*)(pb + i) = h;
-  store_tile_t(w, h, pbT, sh);
+  store_frags(w, {f2bf(x.x), f2bf(x.y), f2bf(x.z), f2bf(x.w)}, wf, sh);
 }
 
 // Adam (Kingma & Ba 2015) with bias correction factors c1 = 1/(1 - b1^t),
@@ -524,7 +655,7 @@ struct CParts {
   int loss_col;
 };
 
-// One Adam step, writing the BF16 weights in both orders.  Alone (dstep null)
+// One Adam step, writing the BF16 weights' fragments.  Alone (dstep null)
 // it takes the gradient g and the given learning rate and correction factors.
 // In the captured training graph the step's learning rate and correction
 // factors are sched[3k .. 3k+2] (k = dstep[1]); a weight tensor's gradient is
@@ -533,8 +664,8 @@ struct CParts {
 // in row-chunk order (as colsum_stage2 sums them); the gradients are stored
 // to g, the loss to losses[k], and the counter moves on (dstep[0] = k + 1,
 // which no block of this launch reads).
-__global__ __launch_bounds__(256) void adam_kernel(AdamArgs a, float* g, uint16_t* pb,
-                                                   uint16_t* pbT, float lr, float c1, float c2,
+__global__ __launch_bounds__(256) void adam_kernel(AdamArgs a, float* g, uint16_t* wf,
+                                                   float lr, float c1, float c2,
                                                    const float* sched, int64_t* dstep, KParts kp,
                                                    CParts cp, float* losses) {
   __shared__ __attribute__((aligned(8))) uint16_t sh[32][36];
@@ -570,7 +701,6 @@ __global__ __launch_bounds__(256) void adam_kernel(AdamArgs a, float* g, uint16_
     a.p[i] = x;
     a.m[i] = m;
     a.v[i] = v;
-    pb[i] = f2bf(x);
     return;
   }
   const WTile w = weight_tile(b);
@@ -600,39 +730,7 @@ __global__ __launch_bounds__(256) void adam_kernel(AdamArgs a, float* g, uint16_
   *(float4*)(a.p + i) = x;
   *(float4*)(a.m + i) = m;
   *(float4*)(a.v + i) = v;
-  const ushort4 h = {f2bf(x.x), f2bf(x.y), f2bf(x.z), f2bf(x.w)};
-  *(ushort4*)(pb + i) = h;
-  store_tile_t(w, h, pbT, sh);
-}
-
-// The rows of one batch in both orders: block b takes 64 rows x 64 bins of x
-// (blockIdx.y: the bins), writing them transposed to xT [256][ldt] and, when
-// xb is given, as they are.  In the captured training graph (dstep) the batch
-// is rows [k mod per) * batch ... of (x, y), k = dstep[0], and its targets
-// are copied to yb.
-__global__ __launch_bounds__(256) void batch_kernel(const uint16_t* x, const float* y, int64_t per,
-                                                    int batch, const int64_t* dstep, uint16_t* xb,
-                                                    uint16_t* xT, int64_t ldt, float* yb) {
-  __shared__ __attribute__((aligned(16))) uint16_t sh[64][72];
-  const int t = threadIdx.x, m0 = blockIdx.x * 64, c0 = blockIdx.y * 64;
-  const int64_t r0 = dstep ? (dstep[0] % per) * batch : 0;
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int r = (t >> 3) + 32 * h, c = (t & 7) * 8;
-    const uint4 v = *(const uint4*)(x + (r0 + m0 + r) * NB + c0 + c);
-    if (xb) *(uint4*)(xb + (int64_t)(m0 + r) * NB + c0 + c) = v;
-    *(uint4*)&sh[r][c] = v;
-  }
-  if (yb && blockIdx.y == 0)
-    for (int e = t; e < 64 * DM; e += 256) yb[(int64_t)m0 * DM + e] = y[(r0 + m0) * DM + e];
-  __syncthreads();
-  const int c = t >> 2, rb = (t & 3) * 16;
-  uint16_t o[16] __attribute__((aligned(16)));
-#pragma unroll
-  for (int i = 0; i < 16; ++i) o[i] = sh[rb + i][c];
-  uint4* dst = (uint4*)(xT + (int64_t)(c0 + c) * ldt + m0 + rb);
-  dst[0] = *(const uint4*)&o[0];
-  dst[1] = *(const uint4*)&o[8];
+  store_frags(w, {f2bf(x.x), f2bf(x.y), f2bf(x.z), f2bf(x.w)}, wf, sh);
 }
 
 // He-normal weights (std sqrt(2/fan_in); output layer std 0.01), zero
@@ -969,23 +1067,18 @@ struct mlp_net {
   int batch_max = 0;
   int64_t step = 0;
   float *p = nullptr, *g = nullptr, *m = nullptr, *v = nullptr;
-  uint16_t *pb = nullptr, *pbT = nullptr;  // BF16 parameters, weights transposed
-  uint16_t* xbuf = nullptr;   // [batch_max][256]
-  uint16_t *h1 = nullptr, *h2 = nullptr;  // [batch_max][512] post-ReLU
+  uint16_t* wf = nullptr;     // BF16 weights in fragments
+  uint16_t* xbuf = nullptr;   // [batch_max][256] (rows at an odd address)
   // the batch transposed, [columns][batch_max]: inputs, activations, gradients
   uint16_t *xT = nullptr, *h1T = nullptr, *h2T = nullptr;
   uint16_t *dobT = nullptr, *dz2T = nullptr, *dz1T = nullptr;
-  float* o = nullptr;         // [batch_max][128]
   float* dof = nullptr;       // [batch_max][128]
-  uint16_t* dob = nullptr;
   float *dz2f = nullptr, *dz1f = nullptr;  // [batch_max][512]
-  uint16_t* dz2b = nullptr;
   float* lrow = nullptr;      // [batch_max]
   float* kpart = nullptr;     // split-K partials: [KSPLIT_MAX][512 * 512], the
                               // first of three buffers (W2, then W3, W1)
   float* cpart = nullptr;     // column-sum partials, [CS_RC][COLS_ALL] + a loss slot
   // the training graph (mlp_train) and what it reads
-  float* ybuf = nullptr;      // [batch_max][7]
   int64_t* dstep = nullptr;   // [2] the graph's step counter, the running step
   float* sched = nullptr;     // [sched_cap][3]: learning rate, c1, c2 per step
   float* losses = nullptr;    // [sched_cap]
@@ -993,7 +1086,7 @@ struct mlp_net {
   hipStream_t work = nullptr;
   hipEvent_t ev_in = nullptr, ev_out = nullptr;
   hipGraphExec_t train_exec = nullptr;
-  int64_t train_key[4] = {0, 0, 0, 0};  // batch, split, rows per epoch, sched buffer
+  int64_t train_key[5] = {0, 0, 0, 0, 0};  // batch, x, y, steps per epoch, sched buffer
 };
 
 constexpr int KSPLIT_MAX = 8;
@@ -1007,11 +1100,9 @@ constexpr int64_t KPART_ALL = KPART_W1 + (int64_t)KSPLIT_MAX * NB * NH;
 
 static void net_free(mlp_net* n) {
   if (n->train_exec) (void)hipGraphExecDestroy(n->train_exec);
-  void* ptrs[] = {n->p,    n->g,    n->m,    n->v,     n->pb,    n->xbuf,  n->h1,
-                  n->h2,   n->o,    n->dof,  n->dob,   n->dz2f,  n->dz1f,  n->dz2b,
-                  n->pbT,  n->xT,   n->h1T,  n->h2T,   n->dobT,  n->dz2T,  n->dz1T,
-                  n->lrow, n->kpart, n->cpart, n->ybuf, n->dstep, n->sched,
-                  n->losses};
+  void* ptrs[] = {n->p,    n->g,    n->m,    n->v,    n->wf,    n->xbuf,  n->xT,
+                  n->h1T,  n->h2T,  n->dobT, n->dz2T, n->dz1T,  n->dof,   n->dz2f,
+                  n->dz1f, n->lrow, n->kpart, n->cpart, n->dstep, n->sched, n->losses};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
   if (n->ev_in) (void)hipEventDestroy(n->ev_in);
@@ -1025,7 +1116,7 @@ static int grid_for(int64_t n) {
 
 // The BF16 weights from the FP32 parameters (null stream).
 static hipError_t shadow(mlp_net* n) {
-  hipLaunchKernelGGL(shadow_kernel, dim3(W_BLOCKS), dim3(256), 0, nullptr, n->p, n->pb, n->pbT);
+  hipLaunchKernelGGL(shadow_kernel, dim3(W_TILES), dim3(256), 0, nullptr, n->p, n->wf);
   return hipGetLastError();
 }
 
@@ -1049,8 +1140,7 @@ extern "C" int mlp_create(int32_t batch_max, uint64_t seed, mlp_net** out) {
             hipMalloc(&n->g, NP_DEV * 4) == hipSuccess &&
             hipMalloc(&n->m, NP_DEV * 4) == hipSuccess &&
             hipMalloc(&n->v, NP_DEV * 4) == hipSuccess &&
-            hipMalloc(&n->pb, NP_DEV * 2) == hipSuccess &&
-            hipMalloc(&n->pbT, NP_T * 2) == hipSuccess &&
+            hipMalloc(&n->wf, N_FRAG * 2) == hipSuccess &&
             hipMalloc(&n->xT, B * NB * 2) == hipSuccess &&
             hipMalloc(&n->h1T, B * NH * 2) == hipSuccess &&
             hipMalloc(&n->h2T, B * NH * 2) == hipSuccess &&
@@ -1058,18 +1148,12 @@ extern "C" int mlp_create(int32_t batch_max, uint64_t seed, mlp_net** out) {
             hipMalloc(&n->dz2T, B * NH * 2) == hipSuccess &&
             hipMalloc(&n->dz1T, B * NH * 2) == hipSuccess &&
             hipMalloc(&n->xbuf, B * NB * 2) == hipSuccess &&
-            hipMalloc(&n->h1, B * NH * 2) == hipSuccess &&
-            hipMalloc(&n->h2, B * NH * 2) == hipSuccess &&
-            hipMalloc(&n->o, B * NOP * 4) == hipSuccess &&
             hipMalloc(&n->dof, B * NOP * 4) == hipSuccess &&
-            hipMalloc(&n->dob, B * NOP * 2) == hipSuccess &&
             hipMalloc(&n->dz2f, B * NH * 4) == hipSuccess &&
             hipMalloc(&n->dz1f, B * NH * 4) == hipSuccess &&
-            hipMalloc(&n->dz2b, B * NH * 2) == hipSuccess &&
             hipMalloc(&n->lrow, B * 4) == hipSuccess &&
             hipMalloc(&n->kpart, (size_t)KPART_ALL * 4) == hipSuccess &&
             hipMalloc(&n->cpart, ((size_t)CS_RC * COLS_ALL + 1) * 4) == hipSuccess &&
-            hipMalloc(&n->ybuf, B * DM * 4) == hipSuccess &&
             hipMalloc(&n->dstep, 16) == hipSuccess &&
             hipStreamCreateWithFlags(&n->work, hipStreamNonBlocking) == hipSuccess &&
             hipEventCreateWithFlags(&n->ev_in, hipEventDisableTiming) == hipSuccess &&
@@ -1173,26 +1257,15 @@ extern "C" int mlp_set_grad(mlp_net* n, const float* grad) {
   return copy_canonical(n, n->g, (float*)grad, false, "mlp_set_grad");
 }
 
-// Forward pass of rows [0, rows) of X into out [rows][128]; with `train` (rows
-// a multiple of 64) the activations are kept in both orders.
-static hipError_t forward_rows(mlp_net* n, const uint16_t* X, int rows, float* out, hipStream_t st,
-                               bool train) {
-  const int nb = (rows + 63) / 64 * 64;
-  GemmArgs g;
-  memset(&g, 0, sizeof(g));
-  g.A = X; g.lda = NB; g.B = n->pbT + OFF_T1; g.ldb = NB;
-  g.M = nb; g.m_valid = rows; g.N = NH; g.K = NB; g.bias = n->p + OFF_B1;
-  g.Cb = n->h1; g.ldc = NH; g.CbT = train ? n->h1T : nullptr; g.ldt = n->batch_max;
-  g.relu = 1;
-  hipError_t e = gemm(g, st);
-  if (e != hipSuccess) return e;
-  g.A = n->h1; g.lda = NH; g.B = n->pbT + OFF_T2; g.ldb = NH; g.K = NH;
-  g.bias = n->p + OFF_B2; g.Cb = n->h2; g.CbT = train ? n->h2T : nullptr;
-  e = gemm(g, st);
-  if (e != hipSuccess) return e;
-  g.A = n->h2; g.B = n->pbT + OFF_T3; g.N = NOP; g.bias = n->p + OFF_B3;
-  g.Cb = nullptr; g.CbT = nullptr; g.Cf = out; g.ldc = NOP; g.relu = 0;
-  return gemm(g, st);
+static hipError_t launch_rows(mlp_net* n, RowArgs& a, bool train, hipStream_t st) {
+  a.wf = n->wf;
+  a.p = n->p;
+  const dim3 grid((unsigned)((a.rows + RB - 1) / RB));
+  if (train)
+    hipLaunchKernelGGL((net_rows_kernel<true>), grid, dim3(1024), 0, st, a);
+  else
+    hipLaunchKernelGGL((net_rows_kernel<false>), grid, dim3(1024), 0, st, a);
+  return hipGetLastError();
 }
 
 extern "C" int mlp_forward(mlp_net* n, const uint16_t* x, int64_t rows, float* out,
@@ -1202,18 +1275,22 @@ extern "C" int mlp_forward(mlp_net* n, const uint16_t* x, int64_t rows, float* o
   if (rows == 0) return SBLM_OK;
   if (!x || !out) return set_error(SBLM_EINVAL, "mlp_forward: null x or out");
   hipStream_t st = (hipStream_t)stream;
-  // the first product reads the caller's rows in 16-byte pieces where their
-  // address allows it, else a copy of them
+  RowArgs a;
+  memset(&a, 0, sizeof(a));
+  // the kernel reads the caller's rows in 16-byte pieces: all of them in one
+  // launch where their address allows it, else chunks of batch_max from a copy
   const bool aligned = ((uintptr_t)x & 15) == 0;
-  for (int64_t r0 = 0; r0 < rows; r0 += n->batch_max) {
-    const int nr = (int)std::min<int64_t>(n->batch_max, rows - r0);
-    const uint16_t* src = x + r0 * NB;
+  const int64_t chunk = aligned ? (int64_t)1 << 30 : n->batch_max;
+  for (int64_t r0 = 0; r0 < rows; r0 += chunk) {
+    a.rows = std::min<int64_t>(chunk, rows - r0);
+    a.x = x + r0 * NB;
+    a.out = out + r0 * NOP;
     hipError_t e = hipSuccess;
     if (!aligned) {
-      e = hipMemcpyAsync(n->xbuf, src, (size_t)nr * NB * 2, hipMemcpyDeviceToDevice, st);
-      src = n->xbuf;
+      e = hipMemcpyAsync(n->xbuf, a.x, (size_t)a.rows * NB * 2, hipMemcpyDeviceToDevice, st);
+      a.x = n->xbuf;
     }
-    if (e == hipSuccess) e = forward_rows(n, src, nr, out + r0 * NOP, st, false);
+    if (e == hipSuccess) e = launch_rows(n, a, false, st);
     if (e != hipSuccess) return check_hip(e, "mlp_forward");
   }
   return SBLM_OK;
@@ -1227,30 +1304,28 @@ static int ksplit_for(int rows) {
   return ks;
 }
 
-// Loss and gradient of a batch whose transposed inputs are in xT already.
-// `dstep` (captured training): leave the weight gradients as split-K partials
-// and the bias gradients and the loss as column-sum partials (all summed by
-// adam_kernel) instead of reducing them here.
+// Loss and gradient of a batch.  `dstep` (captured training): the batch is the
+// step's rows of (x, y), and the weight gradients are left as split-K partials,
+// the bias gradients and the loss as column-sum partials (all summed by
+// adam_kernel) instead of being reduced here.
 static hipError_t loss_grad(mlp_net* n, const uint16_t* x, const float* y, int rows,
-                            float* loss, hipStream_t st, int64_t* dstep = nullptr) {
+                            float* loss, hipStream_t st, int64_t* dstep = nullptr,
+                            int64_t per = 1) {
   const bool fold = dstep != nullptr;
   const int64_t ldt = n->batch_max;
-  hipError_t e = forward_rows(n, x, rows, n->o, st, true);
+  RowArgs a;
+  memset(&a, 0, sizeof(a));
+  a.x = x;
+  a.rows = rows;
+  a.y = y;
+  a.xT = n->xT; a.h1T = n->h1T; a.h2T = n->h2T;
+  a.dobT = n->dobT; a.dz2T = n->dz2T; a.dz1T = n->dz1T;
+  a.ldt = ldt;
+  a.dof = n->dof; a.dz2f = n->dz2f; a.dz1f = n->dz1f; a.lrow = n->lrow;
+  a.dstep = dstep;
+  a.per = per;
+  hipError_t e = launch_rows(n, a, true, st);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(mlp_nll_kernel, dim3((rows * 8 + 255) / 256), dim3(256), 0, st, n->o, y,
-                     rows, n->dof, n->dob, n->dobT, ldt, n->lrow, dstep);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  GemmArgs g;
-  memset(&g, 0, sizeof(g));
-  // dZ2 = (dO W3^T) * [H2 > 0]
-  g.A = n->dob; g.lda = NOP; g.B = n->pb + OFF_W3; g.ldb = NOP;
-  g.M = rows; g.m_valid = rows; g.N = NH; g.K = NOP; g.mask = n->h2; g.ldm = NH;
-  g.Cf = n->dz2f; g.Cb = n->dz2b; g.ldc = NH; g.CbT = n->dz2T; g.ldt = ldt;
-  if ((e = gemm(g, st)) != hipSuccess) return e;
-  // dZ1 = (dZ2 W2^T) * [H1 > 0]
-  g.A = n->dz2b; g.lda = NH; g.B = n->pb + OFF_W2; g.ldb = NH; g.K = NH;
-  g.mask = n->h1; g.Cf = n->dz1f; g.Cb = nullptr; g.CbT = n->dz1T;
-  if ((e = gemm(g, st)) != hipSuccess) return e;
   // weight gradients: gW = (layer input)^T dZ, a contraction over the batch,
   // cut into K ranges of at least 128 rows (more workgroups, shorter chains);
   // the three products in one launch (independent once dZ1 is known), with
@@ -1264,10 +1339,9 @@ static hipError_t loss_grad(mlp_net* n, const uint16_t* x, const float* y, int r
   for (int i = 0; i < 3; ++i) {
     memset(&gw[i], 0, sizeof(gw[i]));
     gw[i].A = wg[i].A; gw[i].lda = ldt; gw[i].B = wg[i].B; gw[i].ldb = ldt;
-    gw[i].M = wg[i].M; gw[i].m_valid = wg[i].M; gw[i].N = wg[i].N; gw[i].K = rows;
-    gw[i].ldc = wg[i].N;
+    gw[i].M = wg[i].M; gw[i].N = wg[i].N; gw[i].K = rows;
     gw[i].ksplit = ks;
-    gw[i].Cf = ks > 1 ? wg[i].part : wg[i].out;
+    gw[i].C = ks > 1 ? wg[i].part : wg[i].out;
   }
   ColSegs cs;
   memset(&cs, 0, sizeof(cs));
@@ -1302,12 +1376,7 @@ extern "C" int mlp_loss_grad(mlp_net* n, const uint16_t* x, const float* y, int3
     return set_error(SBLM_EINVAL,
                      "mlp_loss_grad: rows = %d must be a multiple of 64 in [64, %d]", rows,
                      n->batch_max);
-  const hipStream_t st = (hipStream_t)stream;
-  hipLaunchKernelGGL(batch_kernel, dim3(rows / 64, NB / 64), dim3(256), 0, st, x, y, 1, rows,
-                     nullptr, nullptr, n->xT, n->batch_max, nullptr);
-  hipError_t e = hipGetLastError();
-  if (e == hipSuccess) e = loss_grad(n, x, y, rows, loss, st);
-  return check_hip(e, "mlp_loss_grad");
+  return check_hip(loss_grad(n, x, y, rows, loss, (hipStream_t)stream), "mlp_loss_grad");
 }
 
 static AdamArgs adam_args(mlp_net* n) {
@@ -1320,8 +1389,8 @@ static hipError_t adam(mlp_net* n, float lr, hipStream_t st) {
   n->step += 1;
   const double c1 = 1.0 / (1.0 - pow(b1, (double)n->step));
   const double c2 = 1.0 / (1.0 - pow(b2, (double)n->step));
-  hipLaunchKernelGGL(adam_kernel, dim3(W_BLOCKS), dim3(256), 0, st, adam_args(n), n->g, n->pb,
-                     n->pbT, lr, (float)c1, (float)c2, nullptr, nullptr, KParts{}, CParts{},
+  hipLaunchKernelGGL(adam_kernel, dim3(W_BLOCKS), dim3(256), 0, st, adam_args(n), n->g, n->wf,
+                     lr, (float)c1, (float)c2, nullptr, nullptr, KParts{}, CParts{},
                      nullptr);
   return hipGetLastError();
 }
@@ -1332,22 +1401,19 @@ extern "C" int mlp_adam_step(mlp_net* n, float lr, void* stream) {
   return check_hip(adam(n, lr, (hipStream_t)stream), "mlp_adam_step");
 }
 
-// The captured training step: the batch in both orders, forward, likelihood,
-// backward, Adam with the split-K and column sums, the loss and the step
-// counter.  Every pointer it holds belongs
-// to the net (the caller's data is read through the batch node), so one
-// graph serves every step of a call and later calls with the same shape.
+// The captured training step: the batch's rows (forward, likelihood,
+// backward), the weight gradients with the column sums, Adam with the split-K
+// and column sums, the loss and the step counter.  It holds the net's buffers
+// and the caller's (x, y), of which the step's index picks the batch, so one
+// graph serves every step of a call and later calls with the same data.
 static hipError_t capture_train(mlp_net* n, const uint16_t* x, const float* y, int64_t per,
                                 int batch) {
   hipStream_t w = n->work;
   hipGraph_t graph = nullptr;
   hipError_t e = hipStreamBeginCapture(w, hipStreamCaptureModeThreadLocal);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(batch_kernel, dim3(batch / 64, NB / 64), dim3(256), 0, w, x, y, per, batch,
-                     n->dstep, n->xbuf, n->xT, n->batch_max, n->ybuf);
-  e = hipGetLastError();
   float* loss_slot = n->cpart + (int64_t)CS_RC * COLS_ALL;
-  if (e == hipSuccess) e = loss_grad(n, n->xbuf, n->ybuf, batch, loss_slot, w, n->dstep);
+  e = loss_grad(n, x, y, batch, loss_slot, w, n->dstep, per);
   if (e == hipSuccess) {
     KParts kp;
     kp.part[0] = n->kpart + KPART_W3;
@@ -1362,8 +1428,8 @@ static hipError_t capture_train(mlp_net* n, const uint16_t* x, const float* y, i
     cp.col0[1] = NOP;
     cp.col0[2] = NOP + NH;
     cp.loss_col = NOP + 2 * NH;
-    hipLaunchKernelGGL(adam_kernel, dim3(W_BLOCKS), dim3(256), 0, w, adam_args(n), n->g, n->pb,
-                       n->pbT, 0.0f, 0.0f, 0.0f, n->sched, n->dstep, kp, cp, n->losses);
+    hipLaunchKernelGGL(adam_kernel, dim3(W_BLOCKS), dim3(256), 0, w, adam_args(n), n->g, n->wf,
+                       0.0f, 0.0f, 0.0f, n->sched, n->dstep, kp, cp, n->losses);
     e = hipGetLastError();
   }
   const hipError_t e_end = hipStreamEndCapture(w, &graph);
@@ -1435,7 +1501,7 @@ extern "C" int mlp_train(mlp_net* n, const uint16_t* x, const float* y, int64_t 
                              hipMemcpyHostToDevice),
                    "mlp_train: schedule");
   free(sched_h);
-  const int64_t key[4] = {batch, (int64_t)(uintptr_t)x ^ ((int64_t)(uintptr_t)y << 1), per,
+  const int64_t key[5] = {batch, (int64_t)(uintptr_t)x, (int64_t)(uintptr_t)y, per,
                           (int64_t)(uintptr_t)n->sched};
   if (!rc && (!n->train_exec || memcmp(key, n->train_key, sizeof(key)) != 0)) {
     rc = check_hip(capture_train(n, x, y, per, batch), "mlp_train: capture");
