@@ -86,7 +86,7 @@ struct NmWork {
   int32_t spec;    // this round's form of a step: 1 four points at once
   int32_t* fresh;  // [n] 1 in the first round of a run: its trial points start
                    // their root solves cold, not from the slot's root cache
-  unsigned int* active;
+  unsigned int* active;  // [2] simplices that ran, by the round's parity
   // iterated mode: slot j = k * reps + i of lightcurve k begins with start
   // i; a slot whose run ends takes the lightcurve's next unstarted start (the
   // slots ending in one round in slot order), until reps * runs starts have
@@ -183,14 +183,16 @@ __global__ void nm_nan_fill_kernel(double* p, int64_t n) {
   if (i < n) p[i] = NAN;
 }
 
-// The stopping test of this round (and the round's active count reset: the
-// update kernel that counts runs after this one on the same stream).  In
+// The stopping test of this round (and the active counts reset: the update
+// kernels that count run after this one on the same stream).  In
 // iterated mode a run that stops is recorded and its slot marked as ending;
 // the next kernel gives it its next start.
-__global__ void nm_test_kernel(NmWork w, double tol_x, double tol_f, int32_t max_iter) {
-  const int lc = blockIdx.x * blockDim.x + threadIdx.x;
-  if (lc == 0) *w.active = 0u;
-  if (lc >= w.n) return;
+struct NmStop {
+  double tol_x, tol_f;
+  int32_t max_iter;
+};
+
+__device__ __forceinline__ void test_simplex(const NmWork& w, int lc, const NmStop& stop) {
   if (w.iter) w.ending[lc] = 0;
   if (w.phase[lc] != PH_STEP) return;
   double dx = 0.0, df = 0.0;
@@ -202,13 +204,19 @@ __global__ void nm_test_kernel(NmWork w, double tol_x, double tol_f, int32_t max
     df = fmax(df, d);
     for (int g = 0; g < NP; ++g) dx = fmax(dx, fabs(vtx(w, v, g, lc) - vtx(w, 0, g, lc)));
   }
-  if ((!undefined && dx <= tol_x && df <= tol_f) || w.steps[lc] >= max_iter) {
+  if ((!undefined && dx <= stop.tol_x && df <= stop.tol_f) || w.steps[lc] >= stop.max_iter) {
     w.phase[lc] = PH_DONE;
     if (w.iter) {
       end_run(w, lc);
       w.ending[lc] = 1;
     }
   }
+}
+
+__global__ void nm_test_kernel(NmWork w, NmStop stop) {
+  const int lc = blockIdx.x * blockDim.x + threadIdx.x;
+  if (lc == 0) w.active[0] = w.active[1] = 0u;
+  if (lc < w.n) test_simplex(w, lc, stop);
 }
 
 // The centroid of the best six vertices and the worst vertex.
@@ -245,9 +253,7 @@ __device__ __forceinline__ void step_point(const double* xbar, const double* xw,
 // slots of a lightcurve that end in this round take them in slot order (the
 // update kernel then advances the lightcurve's counter), and a slot with
 // none left stays done.
-__global__ void nm_propose_kernel(NmWork w) {
-  const int lc = blockIdx.x * blockDim.x + threadIdx.x;
-  if (lc >= w.n) return;
+__device__ __forceinline__ void propose_trials(const NmWork& w, int lc) {
   int ph = w.phase[lc];
   double x[NP];
   if (w.iter && w.ending[lc]) {
@@ -312,6 +318,11 @@ __global__ void nm_propose_kernel(NmWork w) {
       break;
   }
   for (int s = 0; s < NS; ++s) w.skipT[(int64_t)lc * NS + s] = ((need >> s) & 1) ? 0 : 1;
+}
+
+__global__ void nm_propose_kernel(NmWork w) {
+  const int lc = blockIdx.x * blockDim.x + threadIdx.x;
+  if (lc < w.n) propose_trials(w, lc);
 }
 
 // Work order of a round: the entries of the fixed order (longest lightcurve
@@ -558,9 +569,8 @@ __device__ __forceinline__ void shrink(Vertex* s) {
     for (int g = 0; g < NP; ++g) s[v].x[g] = clip01(s[0].x[g] + sigma * (s[v].x[g] - s[0].x[g]));
 }
 
-__global__ __launch_bounds__(256) void nm_update_kernel(NmWork w) {
-  const int lc = blockIdx.x * blockDim.x + threadIdx.x;
-  if (lc >= w.n) return;
+// What the round's values make of simplex lc; false when it was done already.
+__device__ __forceinline__ bool update_simplex(const NmWork& w, int lc) {
   if (w.iter && lc % w.reps == 0) {  // starts taken by this round's ending slots
     const int k = lc / w.reps;
     int taken = 0;
@@ -571,7 +581,7 @@ __global__ __launch_bounds__(256) void nm_update_kernel(NmWork w) {
   }
   w.fresh[lc] = 0;
   const int ph = w.phase[lc];
-  if (ph == PH_DONE) return;
+  if (ph == PH_DONE) return false;
   Vertex s[NV];
   load_simplex(w, lc, s);
   int rank[NV];
@@ -704,7 +714,26 @@ __global__ __launch_bounds__(256) void nm_update_kernel(NmWork w) {
   }
   store_simplex(w, lc, s, rank);
   w.phase[lc] = next;
-  atomicAdd(w.active, 1u);
+  return true;
+}
+
+__global__ __launch_bounds__(256) void nm_update_kernel(NmWork w, int parity) {
+  const int lc = blockIdx.x * blockDim.x + threadIdx.x;
+  if (lc < w.n && update_simplex(w, lc)) atomicAdd(w.active + parity, 1u);
+}
+
+// Between two rounds of one form (not the iterated simplex, whose slots look
+// at each other between the steps): the update of the round just evaluated,
+// then the next round's stopping test and trial points, one launch where the
+// three took 16 us of a round's 80 and two more gaps.  Counts in
+// active[parity] and clears the other count for the round after.
+__global__ __launch_bounds__(256) void nm_step_kernel(NmWork w, NmStop stop, int parity) {
+  const int lc = blockIdx.x * blockDim.x + threadIdx.x;
+  if (lc == 0) w.active[parity ^ 1] = 0u;
+  if (lc >= w.n) return;
+  if (update_simplex(w, lc)) atomicAdd(w.active + parity, 1u);
+  test_simplex(w, lc, stop);
+  propose_trials(w, lc);
 }
 
 __global__ void nm_finish_kernel(NmWork w, double* x, double* chi2, double* Fs, double* Fb,
@@ -775,7 +804,7 @@ static size_t nm_carve(NmWork& w, char* base, size_t n, bool iter) {
   w.steps = (int32_t*)take(n * 4);
   w.skipT = (int32_t*)take(n * NS * 4);
   w.fresh = (int32_t*)take(n * 4);
-  w.active = (unsigned int*)take(4);
+  w.active = (unsigned int*)take(8);
   if (iter) {
     w.run = (int32_t*)take(n * 4);
     w.total = (int64_t*)take(n * 8);
@@ -949,7 +978,6 @@ int nm_run(const sblm_lcs& lcs, int32_t reps, const double* lo, const double* sp
     free(ord_h);
   }
   free(off_h);
-  a.order = ord;
   auto set_lanes = [&](int g) {
     a.lanes_per_ind = g;
     const int i = g == 64 ? 0 : g == 128 ? 1 : 2;
@@ -957,7 +985,11 @@ int nm_run(const sblm_lcs& lcs, int32_t reps, const double* lo, const double* sp
   };
   set_lanes(fixed_g ? fixed_g : 64);
   a.cold = w.fresh;
-  const dim3 grid((n + 255) / 256), blk(256);
+  // (a few simplices in blocks of one wave: their chains of loads run on as
+  // many compute units)
+  const int threads = n <= 16384 ? 64 : 256;
+  const dim3 grid((n + threads - 1) / threads), blk(threads);
+  const NmStop stop = {cfg.tol_x, cfg.tol_f, cfg.max_iter};
   if (rc == SBLM_OK) {
     hipLaunchKernelGGL(nm_start_kernel, grid, blk, 0, st, w, x0);
     rc = check_hip(hipGetLastError(), "nm_refine: start");
@@ -983,19 +1015,26 @@ int nm_run(const sblm_lcs& lcs, int32_t reps, const double* lo, const double* sp
       const int64_t tp = (int64_t)active * (w.spec ? NS : 1);
       set_lanes(tp * 64 >= want ? 64 : tp * 128 >= want ? 128 : 256);
     }
+    // A round that fits one residency of the chip (2048 waves) launches every
+    // trial slot: those not needed end at once beside the others, and packing
+    // the needed ones (5 us) would gain nothing.
+    const bool pack = ord && n_trial * a.lanes_per_ind > 2048 * 64;
+    a.order = pack ? ord : order;
     for (int k = 0; k < chunk && rc == SBLM_OK; ++k) {
-      hipLaunchKernelGGL(nm_test_kernel, grid, blk, 0, st, w, cfg.tol_x, cfg.tol_f,
-                         cfg.max_iter);
-      hipError_t e = hipGetLastError();
-      if (e == hipSuccess) {
-        hipLaunchKernelGGL(nm_propose_kernel, grid, blk, 0, st, w);
+      hipError_t e = hipSuccess;
+      if (k == 0 || iter) {
+        hipLaunchKernelGGL(nm_test_kernel, grid, blk, 0, st, w, stop);
         e = hipGetLastError();
+        if (e == hipSuccess) {
+          hipLaunchKernelGGL(nm_propose_kernel, grid, blk, 0, st, w);
+          e = hipGetLastError();
+        }
       }
-      if (e == hipSuccess && ord && n_trial <= COMPACT_ONE) {
+      if (e == hipSuccess && pack && n_trial <= COMPACT_ONE) {
         hipLaunchKernelGGL(nm_pack_kernel, dim3(1), dim3(1024), 0, st, w.skipT, order, n_trial,
                            ord);
         e = hipGetLastError();
-      } else if (e == hipSuccess && ord) {
+      } else if (e == hipSuccess && pack) {
         hipLaunchKernelGGL(nm_count_kernel, dim3((unsigned)n_blk), dim3(256), 0, st, w.skipT,
                            order, n_trial, counts);
         e = hipGetLastError();
@@ -1007,13 +1046,17 @@ int nm_run(const sblm_lcs& lcs, int32_t reps, const double* lo, const double* sp
       }
       if (e == hipSuccess) e = launch_fitness(a, cfg.mode, true, st, 4);
       if (e == hipSuccess) {
-        hipLaunchKernelGGL(nm_update_kernel, grid, blk, 0, st, w);
+        if (k == chunk - 1 || iter)
+          hipLaunchKernelGGL(nm_update_kernel, grid, blk, 0, st, w, k & 1);
+        else
+          hipLaunchKernelGGL(nm_step_kernel, grid, blk, 0, st, w, stop, k & 1);
         e = hipGetLastError();
       }
       rc = check_hip(e, "nm_refine: round");
     }
-    if (rc == SBLM_OK)
-      rc = check_hip(hipMemcpyAsync(&active, w.active, 4, hipMemcpyDeviceToHost, st),
+    if (rc == SBLM_OK)  // the count of the chunk's last round
+      rc = check_hip(hipMemcpyAsync(&active, w.active + ((chunk - 1) & 1), 4,
+                                    hipMemcpyDeviceToHost, st),
                      "nm_refine: copy");
     if (rc == SBLM_OK) rc = check_hip(hipStreamSynchronize(st), "nm_refine: synchronise");
     if (active == 0) break;
@@ -1023,7 +1066,7 @@ int nm_run(const sblm_lcs& lcs, int32_t reps, const double* lo, const double* sp
     rc = check_hip(hipGetLastError(), "nm_refine: finish");
   }
   if (rc == SBLM_OK && iter) {
-    hipLaunchKernelGGL(nm_best_kernel, dim3((lcs.n_lc + 255) / 256), blk, 0, st, w, iter->x,
+    hipLaunchKernelGGL(nm_best_kernel, dim3((lcs.n_lc + 255) / 256), dim3(256), 0, st, w, iter->x,
                        iter->chi2, iter->Fs, iter->Fb, iter->n_iter);
     rc = check_hip(hipGetLastError(), "nm_iterated: finish");
   }
