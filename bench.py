@@ -43,22 +43,25 @@ sys.path.insert(0, ROOT)
 # simultaneous-iteration sweep (FP64, FP32), image test + det J + sum over
 # three images, one more accepted image, an image refined on the lens
 # equation (one or two Newton steps), one residual evaluation, one
-# least-squares row.  fma = 2, reciprocal estimate = 1.
-FLOP_COUNTS = {"coef": 151, "warm": 72, "sweep64": 696, "sweep32": 691, "images": 380,
+# least-squares row, an epoch whose images are tracked.  fma = 2, reciprocal estimate = 1.
+FLOP_COUNTS = {"coef": 151, "warm": 59, "sweep64": 696, "sweep32": 691, "images": 380,
                "image_extra": 10, "refine1": 145, "refine": 227, "eval": 50, "lsq": 48,
-               "newton": 490, "nearest": 70}
+               "newton": 490, "nearest": 70, "track": 893}
 
 
-def flop_per_magnification(sweeps64, sweeps32, refined, newton=0.0, polishes=0.0):
+def flop_per_magnification(sweeps64, sweeps32, refined, newton=0.0, polishes=0.0,
+                           tracked=0.0):
     """Algorithmic FLOPs of one magnification + fit update at the lanes' own
     mean counts per solve: FP64 and FP32 sweeps, refined images, FP64 Newton
     polish passes and polishes (each judged on two sets of nearest-root
-    distances).  Iterations a wavefront runs past a lane's convergence are
+    distances), and at the fraction of epochs whose images were tracked
+    instead of solved for.  Iterations a wavefront runs past a lane's convergence are
     not credited; three accepted images are counted (a fifth-image epoch
     costs 2 x image_extra more)."""
     c = FLOP_COUNTS
-    return (c["coef"] + c["warm"] + sweeps64 * c["sweep64"] + sweeps32 * c["sweep32"]
-            + c["images"] + c["lsq"] + refined * c["refine"] + newton * c["newton"]
+    return ((1.0 - tracked) * (c["coef"] + c["warm"] + c["images"]) + tracked * c["track"]
+            + sweeps64 * c["sweep64"] + sweeps32 * c["sweep32"]
+            + c["lsq"] + refined * c["refine"] + newton * c["newton"]
             + polishes * 2 * c["nearest"])
 
 
@@ -71,7 +74,7 @@ N_GEN_FIT = 500
 # copy kernel of known size (profiles/fitness_kernel_fp64_256lc_1000ep_pop256_
 # traffic.md).  Valid only for the kernel sources it was taken on (the kernel
 # file and the arithmetic it shares).
-FITNESS_TRAFFIC = dict(source_sha256_16="fb6fe4a3fed6ba77", bytes_per_launch=13.74e6,
+FITNESS_TRAFFIC = dict(source_sha256_16="ac0913b7007c6b30", bytes_per_launch=343.1e6,
                        algorithmic_bytes_per_launch=10.86e6)
 FITNESS_SOURCES = ("sblm_fitness.hip", "sblm_math.h", "sblm_internal.h")
 
@@ -231,11 +234,15 @@ def run_form(sblm, torch, lcs, wl, chi2_true, pop, steps, args, mode, tune=True)
     sweeps = s["n_iter"] / n
     n32 = s["n_iter_fp32"] / n
     refined = s["n_polished"] / n
-    newton = s["n_newton"] / n
-    # MIXED: every solve with an FP32 phase is polished (all but degree-4
-    # polynomials and far roots, a few in 10^6)
-    polishes = (1.0 - s["n_degree4"] / n) if mode == sblm.MIXED else 0.0
-    flop = flop_per_magnification(sweeps - n32, n32, refined, newton, polishes)
+    tracked, newton = s["n_newton"] / n, 0.0
+    # MIXED, where n_newton holds the polish passes as well: the first epoch of
+    # every lane's chunk is solved and polished, the others tracked (but for
+    # some 0.5%)
+    if mode == sblm.MIXED:
+        newton, tracked = tracked, 1.0 - min(1.0, sched[0] * n_lc / int(wl.off[-1]))
+        newton -= tracked
+    polishes = (1.0 - tracked) if mode == sblm.MIXED else 0.0
+    flop = flop_per_magnification(sweeps - n32, n32, refined, newton, polishes, tracked)
     # what the wavefronts executed: lockstep sweeps (n_wave_iter) instead of
     # the lanes' own need
     wave = s["n_wave_iter"] / n
@@ -249,7 +256,7 @@ def run_form(sblm, torch, lcs, wl, chi2_true, pop, steps, args, mode, tune=True)
         kernel_ms=k_ms, kernel_launches=launches, kernel_ms_final_population=k_ms_final,
         kernel_mags_per_s=mags_per_gen / (k_ms / 1e3),
         sweeps_per_solve=sweeps, fp32_sweeps_per_solve=n32, flop_per_mag=flop,
-        newton_passes_per_solve=newton,
+        newton_passes_per_solve=newton, tracked_per_solve=tracked,
         kernel_tflops=flop * mags_per_gen / (k_ms / 1e3) / 1e12,
         kernel_tflops_executed=flop_exec * mags_per_gen / (k_ms / 1e3) / 1e12,
         capped=s["n_capped"], unsettled=s["n_unsettled"], fallback=s["n_fallback"],

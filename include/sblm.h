@@ -74,7 +74,8 @@ typedef enum {
 /* Device-side counters of numerical events, accumulated (not reset) by every
  * call that receives a non-NULL pointer.  64-bit device integers. */
 typedef struct {
-  unsigned long long n_solves;     /* polynomials solved                      */
+  unsigned long long n_solves;     /* epochs solved for, by the simultaneous
+                                      iteration or by tracked images (n_newton) */
   unsigned long long n_iter;       /* simultaneous-iteration sweeps, summed   */
   unsigned long long n_capped;     /* solves that reached the iteration cap,
                                       also after the cold retry (see
@@ -82,7 +83,8 @@ typedef struct {
   unsigned long long n_fallback;   /* MIXED: solves whose FP32 roots were not
                                       polished to the FP64 tolerance by two
                                       Newton steps and went on to FP64
-                                      simultaneous-iteration sweeps           */
+                                      simultaneous-iteration sweeps, and warm
+                                      solves, which start with those          */
   unsigned long long n_degree4;    /* leading coefficient negligible          */
   unsigned long long n_degenerate; /* chi^2 fits with a singular 2x2 system   */
   unsigned long long n_wave_iter;  /* sweeps the wavefront executed, summed
@@ -102,8 +104,11 @@ typedef struct {
                                       images (a fold or a cusp of the
                                       caustic), and their images are refined
                                       on the lens equation                    */
-  unsigned long long n_newton;     /* MIXED: FP64 Newton polish passes over the
-                                      five roots, summed                      */
+  unsigned long long n_newton;     /* epochs whose images were followed from the
+                                      epoch before by Newton steps on the lens
+                                      equation, with no simultaneous iteration;
+                                      MIXED: also FP64 Newton polish passes over
+                                      the five roots, summed                  */
 } sblm_stats;
 
 /* Ragged batch of lightcurves in CSR form.  Lightcurve k owns epochs
@@ -326,7 +331,8 @@ int ea_fitness_time(ea_state* st, double* ms, int64_t* launches);
 /*
  * ea_autotune -- choose the fitness schedule of this state by timing it on
  * the state's own population and lightcurves (coordinate descent over the
- * epoch stepping {asynchronous, lockstep}, waves per block {1, 2, 4} and a
+ * epoch stepping {asynchronous, lockstep: one kernel serves both, whose
+ * lanes step together}, waves per block {1, 2, 4} and a
  * persistent work-counter launch vs a one-shot grid; with 128 or 256 lanes
  * per individual only the waves per block that hold whole individuals, the
  * one-shot grid and lockstep stepping), starting from the current schedule
@@ -458,10 +464,10 @@ void nm_default_config(nm_config* cfg);
  * simplices run, else all four points of a step at once; either way the
  * simplices are those of the sequential method.
  * Allocates and frees a workspace of ~1 KB per simplex, a work order of
- * 32 B per simplex, and saved roots of 80 B per lane: the trial points of a
+ * 32 B per simplex, and saved images of 48 B per lane: the trial points of a
  * round are spread over 64, 128 or 256 lanes each, the fewest that give
  * 2^19 lanes for the round's trial points (read every 16 rounds), each
- * width with its own saved roots (140 KB per simplex for the three; where
+ * width with its own saved images (84 KB per simplex for the three; where
  * they would pass 1 GiB, one width: 256 lanes, else 128, else 64 without
  * saved roots).  The widths and the form of a round change results at the
  * rounding level only, and are a function of the simplices, so calls are

@@ -7,8 +7,7 @@
 // negation, absolute value and comparisons are free (operand modifiers and
 // compares).  Prints one JSON object with the counts per call:
 //   coef      source position, lens polynomial, degree-4 test (per epoch)
-//   warm      warm-start weights (quadratic case) and the five extrapolated
-//             roots (per warm-started epoch)
+//   warm      prediction of the three tracked images (cubic Hermite case)
 //   sweep64 / sweep32   one Ehrlich-Aberth sweep over the five roots
 //   images    the image test of the five roots and the sum of 1/|det J| over
 //             three accepted images (two more add 2 x rcp_acc)
@@ -18,6 +17,10 @@
 //   refine    ... by two Newton steps (three evaluations): the usual case,
 //             since the refined images start from roots accurate to ~1e-9
 //   eval      one residual evaluation of the lens equation
+//   track     an epoch whose images are tracked: source position, prediction,
+//             two steps on the lens equation and the velocity for each of
+//             three images, the other two roots from the sum and the product
+//             of all five, their residuals, the sum over three images
 //   lsq       one row of the streaming least-squares fit (both rotations)
 //   newton    one FP64 Newton polish pass over the five roots (MIXED)
 //   nearest   the nearest-root distances of five roots (twice per polish)
@@ -65,6 +68,8 @@ template <int B>
 Num<B> fma(Num<B> a, Num<B> b, Num<B> c) { g_flops += 2; return Num<B>(std::fma(a.v, b.v, c.v)); }
 template <int B>
 Num<B> rcp_hw(Num<B> x) { ++g_flops; return Num<B>(1.0 / x.v); }
+template <int B>
+Num<B> rsq_hw(Num<B> x) { ++g_flops; return Num<B>(1.0 / std::sqrt(x.v)); }
 template <int B>
 Num<B> vmin(Num<B> a, Num<B> b) { ++g_flops; return Num<B>(std::fmin(a.v, b.v)); }
 template <int B>
@@ -114,13 +119,13 @@ int main() {
     sblm::lens_coeffs(zeta, d, q, c);
     (void)sblm::drop_to_degree4(c);
   });
-  // warm start: quadratic weights, five roots
   cx<N64> z[5];
   for (int i = 0; i < 5; ++i) z[i] = {N64(0.3 * i - 0.5), N64(0.2 * i - 0.3)};
+  // prediction: Hermite weights, three images
   const long long warm = counted([&] {
-    N64 w1, w2, w3;
-    sblm::warm_weights(N64(10.0), N64(9.0), N64(8.0), N64(7.0), true, true, w1, w2, w3);
-    for (int i = 0; i < 5; ++i) z[i] = sblm::extrapolate(z[i], z[i], z[i], w1, w2, w3);
+    N64 wd, w1, w2;
+    sblm::track_weights(N64(10.0), N64(9.0), N64(8.0), wd, w1, w2);
+    for (int i = 0; i < 3; ++i) (void)sblm::predict(z[i], z[i], z[i], z[i], wd, w1, w2);
   });
   // one sweep in each precision
   N64 em64;
@@ -158,6 +163,25 @@ int main() {
     N64 iz2, ie2;
     (void)sblm::image_eval(img, zeta, d, q, res, g, &iz2, &ie2);
   });
+  // a tracked epoch in the usual case (three images, two steps)
+  const long long track = counted([&] {
+    const cx<N64> zt = sblm::source_position(N64(3.0), N64(1.0), N64(1.0 / 40.0), N64(0.6),
+                                             N64(0.8), N64(0.1));
+    N64 wd, w1, w2, A(0.0), inv;
+    sblm::track_weights(N64(10.0), N64(9.0), N64(8.0), wd, w1, w2);
+    cx<N64> zi[3] = {{N64(0.7), N64(0.4)}, {N64(-0.6), N64(0.5)}, {N64(1.3), N64(-0.2)}}, z3, z4, g;
+    for (int i = 0; i < 3; ++i) {
+      zi[i] = sblm::predict(zi[i], zi[i], zi[i], zi[i], wd, w1, w2);
+      sblm::image_newton(zi[i], zt, d, q);
+      (void)sblm::image_close(zi[i], zt, d, q, &g, &inv);
+      A += fabs(inv);
+      (void)sblm::image_velocity(zt, g, inv);
+      for (int j = 0; j < i; ++j) (void)sblm::c_norm(sblm::c_sub(zi[i], zi[j]));
+    }
+    (void)sblm::other_roots(zt, d, q, zi, z3, z4);
+    (void)sblm::lens_residual2(z3, zt, d, q);
+    (void)sblm::lens_residual2(z4, zt, d, q);
+  });
   // one least-squares row (both rotations)
   sblm::LsqT<N64> ls = {N64(2.0), N64(1.0), N64(0.5), N64(1.0), N64(0.3), N64(0.1)};
   const long long lsq =
@@ -165,8 +189,8 @@ int main() {
   std::printf(
       "{\"coef\": %lld, \"warm\": %lld, \"sweep64\": %lld, \"sweep32\": %lld, "
       "\"images\": %lld, \"image_extra\": %lld, \"refine1\": %lld, \"refine\": %lld, "
-      "\"eval\": %lld, \"lsq\": %lld, \"newton\": %lld, \"nearest\": %lld}\n",
+      "\"eval\": %lld, \"lsq\": %lld, \"newton\": %lld, \"nearest\": %lld, \"track\": %lld}\n",
       coef, warm, sweep64, sweep32, images, image_extra, refine1, refine, eval, lsq, newton,
-      nearest);
+      nearest, track);
   return 0;
 }

@@ -38,14 +38,6 @@ static int choose_group(int64_t by_rule, int least, int most) {
   return (int)by_rule;
 }
 
-// Epoch stepping of the stateless calls: lockstep unless SBLM_ASYNC=1 (the
-// asynchronous form measured slower on the MI355X for 200-5000-epoch
-// lightcurves: 6.8 vs 4.6 ms per batched evaluation).
-static int async_stepping() {
-  const char* env = getenv("SBLM_ASYNC");
-  return (env && atoi(env) == 1) ? 1 : 0;
-}
-
 static int waves_per_block() {
   const char* env = getenv("SBLM_WAVES_PER_BLOCK");
   if (env) {
@@ -88,7 +80,6 @@ extern "C" int sblm_magnify(const double* theta, int64_t n, const double* t,
   a.n_img = n_img;
   a.stats = stats;
   a.lanes_per_ind = choose_group(magnify_lanes(n, n_t), 1, 1024);
-  a.async = async_stepping() && a.lanes_per_ind <= 64;
   return check_hip(launch_fitness(a, mode, false, (hipStream_t)stream,
                                   block_waves(a.lanes_per_ind)),
                    "sblm_magnify launch");
@@ -122,7 +113,6 @@ extern "C" int sblm_chi2(const sblm_lcs* lcs, const double* theta, int32_t pop,
   a.Fb = Fb;
   a.stats = stats;
   a.lanes_per_ind = choose_group(default_lanes(a.n_ind), 8, 256);
-  a.async = async_stepping() && a.lanes_per_ind <= 64;
   return check_hip(launch_fitness(a, mode, true, (hipStream_t)stream,
                                   block_waves(a.lanes_per_ind)),
                    "sblm_chi2 launch");

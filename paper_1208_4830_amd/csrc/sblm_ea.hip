@@ -570,7 +570,7 @@ struct EaStateImpl {
   sblm_stats* graph_stats = nullptr;
   // fitness schedule: lanes per individual (default_lanes at creation),
   // waves per block, persistent launch with work counters, stepping (the
-  // last three chosen by ea_autotune)
+  // last three chosen by ea_autotune; both steppings run the one kernel there is)
   int lanes = 16;
   int wpb = 4;
   int persistent = 1;
@@ -683,7 +683,6 @@ static hipError_t enqueue_evaluate(EaStateImpl* s, sblm_stats* stats,
   a.stats = stats;
   a.lanes_per_ind = s->lanes;
   a.order = s->order;
-  a.async = s->async;
   a.skip = s->frozen;  // a frozen lightcurve's rows are evaluated as empty
   a.skip_per = a.pop;
   if (s->persistent) {

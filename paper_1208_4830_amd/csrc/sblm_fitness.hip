@@ -13,18 +13,21 @@
 //
 // Mapping onto CDNA4:
 //   * one group of G lanes per individual (8 to 64, several waves up to 256;
-//     magnifications from 1 to as many as there are epochs), each lane owning a contiguous chunk of C = ceil(L/G) epochs; the individual's
-//     parameters are wave-uniform (scalar registers), epochs are read once;
-//   * all five roots are found together by the Ehrlich-Aberth simultaneous
-//     iteration -- branch-free and identical work per lane, so a wavefront
-//     stays in lockstep.  The first epoch of a chunk starts from a circle
-//     around the root centroid; every later epoch starts from the previous
-//     epoch's roots (the source moves little between epochs), which cuts the
-//     wave-level sweep count by ~2.5x.  The loop ends when every lane of the
-//     wave has converged (wave vote);
+//     magnifications from 1 to as many as there are epochs), each lane owning
+//     a contiguous chunk of C = ceil(L/G) epochs; the individual's parameters
+//     are wave-uniform (scalar registers), epochs are read once;
+//   * at the first epoch of a chunk all five roots are found together by the
+//     Ehrlich-Aberth simultaneous iteration -- branch-free and identical work
+//     per lane, so a wavefront stays in lockstep -- from the roots in the
+//     limit of a light secondary.  The loop ends when every lane of the wave
+//     has converged (wave vote);
+//   * from there three images are followed on the lens equation itself, and
+//     the other two roots, and with them the image count, come from the sum
+//     and the product of all five (track_images); only an epoch that fails a
+//     check there goes through the iteration again;
 //   * FP64 mode iterates in FP64.  MIXED mode iterates in FP32 to a loose
 //     tolerance, then continues in FP64 (normally two sweeps) from there; the
-//     image test, det J and the fit are FP64 in both modes;
+//     tracking, the image test, det J and the fit are FP64 in both modes;
 //   * the weighted least-squares fit is accumulated on the fly with
 //     square-root-free Givens rotations (Gentleman 1973, the row-update form
 //     of a QR factorisation) over columns (1, A | y), so chi^2 comes out as
@@ -55,6 +58,10 @@
 #define SBLM_ROOT_TAU32 1e-5f
 #endif
 
+// Passes of track_images over images that are not final after their second
+// step.
+#define SBLM_TRACK_PASSES 8
+
 namespace sblm {
 
 // The primitive operations the shared arithmetic (sblm_math.h) takes from
@@ -69,6 +76,8 @@ __device__ __forceinline__ float vmax(float a, float b) { return fmaxf(a, b); }
 // Hardware reciprocal estimate (relative error < 5e-8 in FP64).
 __device__ __forceinline__ double rcp_hw(double x) { return __builtin_amdgcn_rcp(x); }
 __device__ __forceinline__ float rcp_hw(float x) { return __builtin_amdgcn_rcpf(x); }
+// Hardware estimate of 1/sqrt(x) (relative error < 1e-7 in FP64).
+__device__ __forceinline__ double rsq_hw(double x) { return __builtin_amdgcn_rsq(x); }
 
 }  // namespace sblm
 
@@ -191,11 +200,13 @@ __device__ __forceinline__ void cold_start(const cx<T> c[6], cx<double> zeta, do
 // Images, det J and the magnification from five FP64 roots.  The image
 // count and the choice of images use the roots' residuals (image_score); an
 // accepted image that needs it is refined on the lens equation
-// (refine_image).
+// (refine_image).  If next, *order receives, per root, its place when the three
+// images to be tracked from here come first: with three images those, with five the
+// three of largest |det J| (a pair about to merge goes last).  Returns A.
 __device__ __forceinline__ double magnification(const cx<double> z[5],
                                                 cx<double> zeta, double d,
                                                 double q, bool deg4,
-                                                int& nimg, int& npolish) {
+                                                int& nimg, int& npolish, bool next, int* order) {
   double r2[5], adet[5];
   bool refine[5];
 #pragma unroll
@@ -215,10 +226,21 @@ __device__ __forceinline__ double magnification(const cx<double> z[5],
     for (int j = 0; j < 5; ++j)
       rank += (r2[j] < r2[i] || (r2[j] == r2[i] && j < i)) ? 1 : 0;
     const bool acc = five || rank < 3;
+    order[i] = rank;
     if (acc && refine[i])
       todo |= 1u << i;
     else if (acc)
       A += rcp_acc(adet[i]);
+  }
+  if (next && five) {
+#pragma unroll
+    for (int i = 0; i < 5; ++i) {
+      int far = 0;
+#pragma unroll
+      for (int j = 0; j < 5; ++j)
+        far += (adet[j] > adet[i] || (adet[j] == adet[i] && j < i)) ? 1 : 0;
+      order[i] = far;
+    }
   }
   // refinement: one image per lane per pass, so the wavefront runs as many
   // passes as the lane with the most images to refine
@@ -238,6 +260,67 @@ __device__ __forceinline__ double magnification(const cx<double> z[5],
   return A;
 }
 
+// The tracked form of an epoch: the three images predicted in z, stepped
+// twice on the lens equation (a Newton step, then one that is judged), a lane's
+// images that are not final yet one per pass after that; their velocities v
+// for the source's vz; the other two roots in z3, z4.  True with A and the
+// image count when every check holds (see sblm_math.h): the images final and
+// apart, the other two roots clearly both images or clearly neither.
+//   Over the batched set 98.4% of the epochs end here (1.6% are the first of
+// a chain); in 95% of a wave's steps no lane is left for the iteration.
+__device__ __forceinline__ bool track_images(cx<double> z[3], cx<double> v[3], cx<double> zeta,
+                                             cx<double> vz, double d, double q, double& A,
+                                             int& nimg, cx<double>& z3, cx<double>& z4) {
+  double ai[3];
+  unsigned int todo = 0u;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) image_newton(z[i], zeta, d, q);
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    cx<double> g;
+    double inv;
+    if (!image_close(z[i], zeta, d, q, &g, &inv)) todo |= 1u << i;
+    ai[i] = fabs(inv);
+    v[i] = image_velocity(vz, g, inv);
+  }
+  for (int pass = 0; pass < SBLM_TRACK_PASSES && __any(todo != 0u); ++pass) {
+    if (todo) {
+      const int i = __builtin_ctz(todo);
+      cx<double> zi = i == 0 ? z[0] : i == 1 ? z[1] : z[2], g;
+      double inv;
+      const bool done = image_close(zi, zeta, d, q, &g, &inv);
+      const cx<double> vi = image_velocity(vz, g, inv);
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+        if (i == k) {
+          z[k] = zi;
+          v[k] = vi;
+          ai[k] = fabs(inv);
+        }
+      if (done) todo &= todo - 1u;
+    }
+  }
+  A = ai[0] + ai[1] + ai[2];
+  nimg = 3;
+  double apart = c_norm(c_sub(z[0], z[1]));
+  apart = vmin(c_norm(c_sub(z[0], z[2])), apart);
+  apart = vmin(c_norm(c_sub(z[1], z[2])), apart);
+  bool ok = todo == 0u && apart > SBLM_TRACK_APART2;
+  ok = other_roots(zeta, d, q, z, z3, z4) && ok;
+  const double r3 = lens_residual2(z3, zeta, d, q), r4 = lens_residual2(z4, zeta, d, q);
+  const bool spurious = r3 > SBLM_TRACK_SPURIOUS2 && r4 > SBLM_TRACK_SPURIOUS2;
+  if (ok && !spurious) {  // five images?
+    double i3, i4;
+    cx<double> a = z3, b = z4, g;
+    ok = r3 < SBLM_TRACK_IMAGE2 && r4 < SBLM_TRACK_IMAGE2;
+    ok = image_close(a, zeta, d, q, &g, &i3) && ok;
+    ok = image_close(b, zeta, d, q, &g, &i4) && ok;
+    A += fabs(i3) + fabs(i4);
+    nimg = 5;
+  }
+  return ok;
+}
+
 // ---------------------------------------------------------------- fit
 
 using Lsq = LsqT<double>;
@@ -255,6 +338,19 @@ struct LaneStats {
   unsigned int solves, iters, capped, fallback, deg4, wave_iters, iters32, polished, retried,
       unsettled, newton;
 };
+__device__ __forceinline__ void add_stats(LaneStats& a, const LaneStats& b) {
+  a.solves += b.solves;
+  a.iters += b.iters;
+  a.capped += b.capped;
+  a.fallback += b.fallback;
+  a.deg4 += b.deg4;
+  a.wave_iters += b.wave_iters;
+  a.iters32 += b.iters32;
+  a.polished += b.polished;
+  a.retried += b.retried;
+  a.unsettled += b.unsettled;
+  a.newton += b.newton;
+}
 
 // A solve that reaches the iteration cap has settled when its roots are
 // finite and its last sweep moved them by less than this much relative
@@ -270,12 +366,13 @@ struct LaneStats {
 // ok = converged to finite roots; settled = ok, or capped with finite roots
 // that no longer move (see SBLM_SETTLED_STEP2).  `retry` marks a second,
 // cold attempt at an epoch whose warm-started solve failed (not counted as
-// another solve).
+// another solve); `direct` sends a warm MIXED solve straight to FP64 sweeps.
 template <int MODE>
 __device__ __forceinline__ void solve_roots(const cx<double> c[6], cx<double> zeta, double d,
                                             double q, bool deg4, bool warm, bool active,
                                             cx<double> z[5], LaneStats& st,
-                                            bool& ok, bool& settled, bool retry = false) {
+                                            bool& ok, bool& settled, bool retry = false,
+                                            bool direct = false) {
   constexpr int MAXIT64 = 60, MAXIT32 = 30;
   // estimated relative error left after the last step
   const double tau64 = SBLM_ROOT_TAU;
@@ -290,13 +387,15 @@ __device__ __forceinline__ void solve_roots(const cx<double> c[6], cx<double> ze
     // and the fit in FP64.  A polish that has not converged after two steps
     // falls back to FP64 Aberth sweeps from the polished roots (counted).
     // A warm start (the previous epochs' roots, extrapolated) is already as
-    // close as FP32 can resolve and goes straight to the polish; degree-4
-    // polynomials (parked root out of FP32 range) and those with a far root
-    // (its powers overflow FP32) straight to FP64 sweeps.  The FP32
-    // iteration ends at its own convergence test, or, after its first few
-    // sweeps (the global phase, where steps need not shrink), when its steps
-    // stop shrinking (the FP32 rounding floor next to clustered roots).
-    const bool use32 = !deg4 && !far;
+    // close as FP32 can resolve and goes straight to the polish (or to FP64
+    // sweeps: a solve for what track_images did not settle has had its FP64
+    // steps there); degree-4 polynomials (parked root out of FP32 range) and
+    // those with a far root (its powers overflow FP32) straight to FP64 sweeps.
+    // The FP32 iteration ends at its own convergence test, or, after its first
+    // few sweeps (the global phase, where steps need not shrink), when its
+    // steps stop shrinking (the FP32 rounding floor next to clustered roots).
+    const bool use32 = !deg4 && !far && !(warm && direct);
+    fell_back = active && warm && direct;
     cx<float> cf[6];
 #pragma unroll
     for (int j = 0; j < 6; ++j) cf[j] = {(float)c[j].re, (float)c[j].im};
@@ -371,39 +470,10 @@ __device__ __forceinline__ void solve_roots(const cx<double> c[6], cx<double> ze
     st.deg4 += (deg4 && !retry) ? 1 : 0;
     // MIXED: a polish that needed the FP64 iteration after its two steps
     if (MODE == SBLM_MIXED) st.fallback += fell_back ? 1 : 0;
-    st.wave_iters += it_wave;
     st.iters32 += it32_lane;
     st.newton += newton_lane;
   }
-}
-
-// The cold second attempt at an epoch whose warm-started solve failed (a
-// warm start from the roots of another epoch or, in the simplex rounds, of
-// another point), called by the whole wave when any lane needs it; lanes
-// with active = 0 only follow along.  Kept out of line: a second inlined
-// copy of the iteration would cost the hot path registers.  Coefficients (then
-// the source position, d and q), roots (in and out) and the lane's counters
-// travel through memory.
-template <int MODE>
-__device__ __noinline__ void cold_retry(const double* cr, double* zr, int deg4, int active,
-                                        unsigned int* counts) {
-  cx<double> c[6], z[5];
-  for (int j = 0; j < 6; ++j) c[j] = {cr[2 * j], cr[2 * j + 1]};
-  for (int i = 0; i < 5; ++i) z[i] = {zr[2 * i], zr[2 * i + 1]};
-  LaneStats st = {};
-  bool ok, settled;
-  solve_roots<MODE>(c, {cr[12], cr[13]}, cr[14], cr[15], deg4 != 0, false, active != 0, z, st, ok,
-                    settled, true);
-  for (int i = 0; i < 5; ++i) {
-    zr[2 * i] = z[i].re;
-    zr[2 * i + 1] = z[i].im;
-  }
-  counts[0] = st.iters;
-  counts[1] = st.wave_iters;
-  counts[2] = st.iters32;
-  counts[3] = st.newton;
-  counts[4] = st.fallback;
-  counts[5] = (ok ? 1u : 0u) | (settled ? 2u : 0u);
+  st.wave_iters += it_wave;
 }
 
 // Per-lane context of one work item: the individual, its parameters and the
@@ -413,7 +483,7 @@ struct Item {
   int gl;  // lane within the group
   int64_t ind;
   double q, d, u0, sa, ca, t0, itE;
-  int64_t e0, k0, k1, Cg, C;  // C: longest chunk in the wave
+  int64_t e0, L, k0, k1, Cg;  // L: its epochs, Cg: the longest chunk
 };
 
 // The transcendental part of an individual's set-up: q = 10^(log10 q),
@@ -479,32 +549,20 @@ __device__ __forceinline__ Item item_setup(const FitArgs& a, int64_t wave_item) 
   if (!x.valid) e1 = e0;
   x.e0 = e0;
   const int64_t L = e1 - e0;
+  x.L = L;
   x.Cg = (L + lanes - 1) / lanes;
-  x.C = x.Cg;
-#pragma unroll
-  for (int o = G; o < 64; o <<= 1) {
-    const int64_t oc = __shfl_xor(x.C, o, 64);
-    x.C = oc > x.C ? oc : x.C;
-  }
   x.k0 = e0 + x.gl * x.Cg;
   x.k1 = (x.k0 + x.Cg < e1) ? x.k0 + x.Cg : e1;
   return x;
 }
 
-// Source position (Eq. sourcePos) and lens polynomial at epoch t.
-__device__ __forceinline__ bool epoch_poly(const Item& x, double t, cx<double>& zeta,
-                                           cx<double> c[6]) {
-  zeta = source_position(t, x.t0, x.itE, x.sa, x.ca, x.u0);
-  lens_coeffs(zeta, x.d, x.q, c);
-  return drop_to_degree4(c);
-}
-
-// Per-lane history of the roots of the two epochs before the current one,
-// kept in LDS (touched once per epoch, at the warm start; in registers it
-// would hold 40 VGPRs through the whole solve).  Dynamic shared memory of
-// ROOT_HIST_BYTES per thread; element [((slot*5 + i)*2 + part) * blockDim.x +
-// thread] holds root i of epoch slot (0: previous but one, 1: the one
-// before), real (part 0) or imaginary (part 1).
+// Per-lane history, kept in LDS (touched once per epoch, at the prediction; in
+// registers it would hold 24 or 40 VGPRs through the whole epoch).  Dynamic
+// shared memory of ROOT_HIST_BYTES per thread; element [((slot*5 + i)*2 + part)
+// * blockDim.x + thread] holds, real (part 0) or imaginary (part 1), of a
+// tracked chain the position (slot 0) and the velocity (slot 1) of image i < 3
+// at the previous epoch but one, else root i at that epoch (slot 0) and at the
+// one before it (slot 1).
 constexpr size_t ROOT_HIST_BYTES = 2 * 5 * 2 * sizeof(double);
 
 // Dynamic shared memory: the root history, then (G > 64) one least-squares
@@ -596,27 +654,169 @@ struct RootHist {
   }
 };
 
-// One wave's share of the work, lockstep form: 64/G individuals (items
-// wave_item*64/G ...); every lane solves its s-th epoch at the same time and
-// the wave moves on when all of them have converged.
-template <int MODE, bool CHI2, int G>
-__device__ __forceinline__ void fit_wave(const FitArgs& a, int64_t wave_item,
-                                         LaneStats& st) {
-  Item x = item_setup<G>(a, wave_item);
-  const int64_t C = x.C, Cg = x.Cg, k0 = x.k0, k1 = x.k1, e0 = x.e0, ind = x.ind;
-  const double q = x.q, d = x.d, t0 = x.t0;
-  Lsq ls = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  cx<double> z[5];
+// Where a lane saves its first epoch's start for the next simplex round.
+template <int G>
+__device__ __forceinline__ double* root_cache_of(const FitArgs& a, const Item& x) {
+  return a.root_cache ? a.root_cache + (x.ind * G + x.gl) * ROOT_CACHE : nullptr;
+}
+
+// Simplex rounds: a lane's first epoch starts from what the lane found there
+// for the same trial slot in the previous round (the simplex moves little
+// between rounds), else cold -- always cold in the first round of a run, so
+// that a run does not depend on what ran in its slot before.  N roots or images.
+template <int N>
+__device__ __forceinline__ bool cached_start(const FitArgs& a, const Item& x, const double* rc,
+                                             cx<double>* z) {
+  if (a.cold && a.cold[x.ind / a.cold_per]) return false;
+  cx<double> zc[N];
+  bool fin = true;
 #pragma unroll
-  for (int i = 0; i < 5; ++i) z[i] = {0.0, 0.0};
-  const RootHist hist = {fit_dyn_smem};  // zp (slot 0), zpp (slot 1)
+  for (int i = 0; i < N; ++i) {
+    zc[i] = {rc[2 * i], rc[2 * i + 1]};
+    fin = fin && isfinite(zc[i].re) && isfinite(zc[i].im);
+  }
+  if (fin) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) z[i] = zc[i];
+  }
+  return fin;
+}
+
+template <int N>
+__device__ __forceinline__ void save_start(double* rc, const cx<double>* z, bool ok) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    rc[2 * i] = ok ? z[i].re : NAN;
+    rc[2 * i + 1] = ok ? z[i].im : NAN;
+  }
+}
+
+// An epoch's magnification: a row of the fit, or the output.
+template <bool CHI2>
+__device__ __forceinline__ void put_epoch(const FitArgs& a, const Item& x, int64_t k, double wk,
+                                          double yk, double A, int nimg, Lsq& ls) {
+  if (CHI2) {
+    lsq_include(ls, wk, 1.0, A, yk);
+  } else {
+    const int64_t o = x.ind * a.n_t + (k - x.e0);
+    a.A[o] = A;
+    if (a.n_img) a.n_img[o] = (int8_t)nimg;
+  }
+}
+
+// The solve of an epoch whose images cannot be tracked, by the whole wave when
+// any lane needs it (the others only follow along): the five roots by
+// simultaneous iteration from z (three predicted images and two other roots,
+// warm) or from a cold start, the retry of a warm solve that failed, the
+// images and, where an epoch follows, which of them are tracked.  With
+// SOLVE_RETRY the cold second attempt of a chain that is not tracked.  Out of
+// line: few steps come here, and inlined it costs the tracked form registers
+// (64 x 1000 x 256 FP64: 838 us inlined, 751 so).  Everything travels through
+// memory: io[0..9] the roots (in and out; SOLVE_NEXT: the images to track come
+// first), [10, 11] zeta, [12] d, [13] q, [14] A (out); flags in: SOLVE_ACTIVE,
+// _WARM, _NEXT, _RETRY, and _FOLLOW for a lane with an epoch that needs no
+// solve; flags out: SOLVE_OK, the image count from bit 4; cnt: the lane's
+// counters (added to).
+enum {
+  SOLVE_ACTIVE = 1,
+  SOLVE_WARM = 2,
+  SOLVE_NEXT = 4,
+  SOLVE_FOLLOW = 8,
+  SOLVE_RETRY = 16,
+  SOLVE_OK = 1
+};
+template <int MODE>
+__device__ __noinline__ int solve_epoch(double* io, int flags, LaneStats* cnt) {
+  const bool active = (flags & SOLVE_ACTIVE) != 0;
+  const cx<double> zeta = {io[10], io[11]};
+  const double d = io[12], q = io[13];
+  cx<double> z[5], c[6];
+  bool fin = true;
 #pragma unroll
   for (int i = 0; i < 5; ++i) {
+    z[i] = {io[2 * i], io[2 * i + 1]};
+    fin = fin && isfinite(z[i].re) && isfinite(z[i].im);
+  }
+  lens_coeffs(zeta, d, q, c);
+  const bool deg4 = drop_to_degree4(c);
+  const bool warm = (flags & SOLVE_WARM) != 0 && !deg4 && fin;
+  LaneStats st = {};
+  bool ok, settled;
+  solve_roots<MODE>(c, zeta, d, q, deg4, warm, active, z, st, ok, settled,
+                    (flags & SOLVE_RETRY) != 0, true);
+  // a warm start that did not converge: solve again from the cold start;
+  // roots that still have not settled poison the result (A and with it chi^2
+  // become NaN, which ranks last)
+  const bool again = active && !ok && warm;
+  if (__any(again)) {
+    bool ok2, settled2;
+    LaneStats st2 = {};
+    solve_roots<MODE>(c, zeta, d, q, deg4, false, again, z, st2, ok2, settled2, true);
+    if (again) {
+      ok = ok2;
+      settled = settled2;
+      st.iters += st2.iters;
+      st.iters32 += st2.iters32;
+      st.newton += st2.newton;
+      st.fallback += st2.fallback;
+      st.retried += 1;
+      st.wave_iters += st2.wave_iters;
+    }
+  }
+  int out = 0;
+  if (active) {
+    int npol = 0, order[5], nimg;
+    const bool next = (flags & SOLVE_NEXT) != 0;
+    double A = magnification(z, zeta, d, q, deg4, nimg, npol, next, order);
+    if (!settled) {
+      A = NAN;
+      nimg = 0;
+    }
+    io[14] = A;
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+      cx<double> zk = z[k];
+      if (next) {
+#pragma unroll
+        for (int i = 0; i < 5; ++i)
+          if (order[i] == k) zk = z[i];
+      }
+      io[2 * k] = zk.re;
+      io[2 * k + 1] = zk.im;
+    }
+    out = (ok ? SOLVE_OK : 0) | (nimg << 4);
+    cnt->solves += st.solves;
+    cnt->iters += st.iters;
+    cnt->capped += ok ? 0 : 1;
+    cnt->fallback += st.fallback;
+    cnt->deg4 += st.deg4;
+    cnt->iters32 += st.iters32;
+    cnt->polished += npol;
+    cnt->retried += st.retried;
+    cnt->unsettled += settled ? 0 : 1;
+    cnt->newton += st.newton;
+  }
+  if (flags & (SOLVE_ACTIVE | SOLVE_FOLLOW)) cnt->wave_iters += st.wave_iters;
+  return out;
+}
+
+// Chains that are solved at every epoch, Cg of them in this lane and at most C
+// in the wave: the five roots start from those of the epochs before.
+template <int MODE, bool CHI2, int G>
+__device__ __forceinline__ void solve_chain(const FitArgs& a, const Item& x, int64_t Cg, int64_t C,
+                                            LaneStats& st, Lsq& ls) {
+  const int64_t k0 = x.k0, k1 = x.k1;
+  const double q = x.q, d = x.d, t0 = x.t0;
+  cx<double> z[5];
+  const RootHist hist = {fit_dyn_smem};  // the roots one (slot 0) and two epochs before z
+#pragma unroll
+  for (int i = 0; i < 5; ++i) {
+    z[i] = {0.0, 0.0};
     hist.set(0, i, {0.0, 0.0});
     hist.set(1, i, {0.0, 0.0});
   }
-  bool have_prev = false, prev_deg4 = false, have_prev2 = false, have_prev3 = false;
-  double t1 = 0.0, t2 = 0.0, t3 = 0.0;  // epochs of z, zp and zpp
+  int nhist = 0;                        // epochs known
+  double t1 = 0.0, t2 = 0.0, t3 = 0.0;  // those epochs
 
   // the epoch time one step ahead, the observation at the top of its step:
   // the loads are in flight during the solve
@@ -639,316 +839,240 @@ __device__ __forceinline__ void fit_wave(const FitArgs& a, int64_t wave_item,
       hp[i] = hist.get(0, i);
       hpp[i] = hist.get(1, i);
     }
-    cx<double> zeta, c[6];
-    const bool deg4 = epoch_poly(x, t, zeta, c);
-    bool warm = have_prev && !deg4 && !prev_deg4;
+    const cx<double> zeta = source_position(t, t0, x.itE, x.sa, x.ca, x.u0);
+    cx<double> c[6];
+    lens_coeffs(zeta, d, q, c);
+    const bool deg4 = drop_to_degree4(c);
     bool cached = false;  // started from the root cache (not a solved epoch)
-    if constexpr (G >= 64) {
-      // simplex rounds: a lane's first epoch starts from the roots the lane
-      // found there for the same trial slot in the previous round (the
-      // simplex moves little between rounds), else cold -- always cold in
-      // the first round of a run, so that a run does not depend on what ran
-      // in its slot before
-      if (s == 0 && a.root_cache && active && !deg4 &&
-          !(a.cold && a.cold[x.ind / a.cold_per])) {
-        const double* rc = a.root_cache + (x.ind * G + x.gl) * 10;
-        cx<double> zc[5];
-        bool fin = true;
-#pragma unroll
-        for (int i = 0; i < 5; ++i) {
-          zc[i] = {rc[2 * i], rc[2 * i + 1]};
-          fin = fin && isfinite(zc[i].re) && isfinite(zc[i].im);
-        }
-        if (fin) {
-#pragma unroll
-          for (int i = 0; i < 5; ++i) z[i] = zc[i];
-          warm = true;
-          cached = true;
-        }
+    double* rc = nullptr;
+    if constexpr (CHI2 && G >= 64) {
+      if (s == 0 && active) {
+        rc = root_cache_of<G>(a, x);
+        if (rc && !deg4) cached = cached_start<5>(a, x, rc, z);
       }
     }
+    const bool warm = (nhist >= 1 || cached) && !deg4;
     // Warm start: quadratic (Lagrange in t) extrapolation of every root from
     // the three previous epochs, else linear from two (warm_weights); the
     // history shifts as it is used.
     {
       double w1, w2, w3;
-      warm_weights(t, t1, t2, t3, warm && have_prev2, have_prev3, w1, w2, w3);
+      warm_weights(t, t1, t2, t3, nhist >= 2, nhist >= 3, w1, w2, w3);
 #pragma unroll
       for (int i = 0; i < 5; ++i) {
-        const cx<double> old = z[i], zp = hp[i], zpp = hpp[i];
-        z[i] = extrapolate(old, zp, zpp, w1, w2, w3);
-        hist.set(1, i, zp);
+        const cx<double> old = z[i];
+        z[i] = extrapolate(old, hp[i], hpp[i], w1, w2, w3);
+        hist.set(1, i, hp[i]);
         hist.set(0, i, old);
       }
     }
     bool ok, settled;
+    const unsigned int w0 = st.wave_iters;
     solve_roots<MODE>(c, zeta, d, q, deg4, warm, active, z, st, ok, settled);
-    {
-      // a warm start that did not converge: solve again from the cold
-      // start; roots that still have not settled poison the result (A and
-      // with it chi^2 become NaN, which ranks last)
-      const bool again = active && !ok && warm;
-      if (__any(again)) {
-        double cr[16], zr[10];
-        unsigned int cnt[6];
+    if (!active) st.wave_iters = w0;
+    // a warm start that did not converge: solve again from the cold start;
+    // roots that still have not settled poison the result (A and with it chi^2
+    // become NaN, which ranks last)
+    const bool again = active && !ok && warm;
+    double A = 0.0;
+    int nimg = 0;
+    if (__any(again)) {
+      double io[15];
+      LaneStats rs = {};
 #pragma unroll
-        for (int j = 0; j < 6; ++j) {
-          cr[2 * j] = c[j].re;
-          cr[2 * j + 1] = c[j].im;
-        }
-        cr[12] = zeta.re;
-        cr[13] = zeta.im;
-        cr[14] = d;
-        cr[15] = q;
-#pragma unroll
-        for (int i = 0; i < 5; ++i) {
-          zr[2 * i] = z[i].re;
-          zr[2 * i + 1] = z[i].im;
-        }
-        cold_retry<MODE>(cr, zr, deg4 ? 1 : 0, again ? 1 : 0, cnt);
-        if (again) {
-#pragma unroll
-          for (int i = 0; i < 5; ++i) z[i] = {zr[2 * i], zr[2 * i + 1]};
-          ok = (cnt[5] & 1u) != 0;
-          settled = (cnt[5] & 2u) != 0;
-          st.iters += cnt[0];
-          st.iters32 += cnt[2];
-          st.newton += cnt[3];
-          st.fallback += cnt[4];
-          st.retried += 1;
-        }
-        st.wave_iters += active ? cnt[1] : 0;
+      for (int i = 0; i < 5; ++i) {
+        io[2 * i] = z[i].re;
+        io[2 * i + 1] = z[i].im;
       }
-      if (active && !ok) st.capped += 1;
-      if (active && !settled) st.unsettled += 1;
-    }
-    if constexpr (G >= 64) {
-      if (s == 0 && a.root_cache && active) {
-        double* rc = a.root_cache + (x.ind * G + x.gl) * 10;
+      io[10] = zeta.re;
+      io[11] = zeta.im;
+      io[12] = d;
+      io[13] = q;
+      const int out = solve_epoch<MODE>(
+          io, again ? SOLVE_ACTIVE | SOLVE_RETRY : active ? SOLVE_FOLLOW : 0, &rs);
+      if (again) {
+        A = io[14];
+        nimg = out >> 4;
+        ok = (out & SOLVE_OK) != 0;
 #pragma unroll
-        for (int i = 0; i < 5; ++i) {
-          rc[2 * i] = ok ? z[i].re : NAN;
-          rc[2 * i + 1] = ok ? z[i].im : NAN;
-        }
+        for (int i = 0; i < 5; ++i) z[i] = {io[2 * i], io[2 * i + 1]};
+        st.retried += 1;
       }
+      add_stats(st, rs);
     }
-    // (roots started from the cache follow no solved epoch: the next epoch
-    // extrapolates from this one alone)
-    have_prev3 = have_prev2 && warm && ok;
-    have_prev2 = warm && !cached && ok;
+    if constexpr (CHI2 && G >= 64) {
+      if (rc) save_start<5>(rc, z, ok);
+    }
+    // (roots started from the cache follow no solved epoch, roots of a retry
+    // are in another order, a degree-4 polynomial's are not those of the next:
+    // the next epoch extrapolates from this one alone)
+    nhist = (!ok || deg4) ? 0 : (warm && !cached && !again) ? (nhist < 3 ? nhist + 1 : 3) : 1;
     t3 = t2;
     t2 = t1;
     t1 = t;
-    have_prev = ok;
-    prev_deg4 = deg4;
     if (active) {
-      int nimg, npol = 0;
-      double A = magnification(z, zeta, d, q, deg4, nimg, npol);
-      if (!settled) {
-        A = NAN;
-        nimg = 0;
-      }
-      st.polished += npol;
-      if (CHI2) {
-        lsq_include(ls, wk, 1.0, A, yk);
-      } else {
-        const int64_t o = ind * a.n_t + (k - e0);
-        a.A[o] = A;
-        if (a.n_img) a.n_img[o] = (int8_t)nimg;
-      }
-    }
-  }
-
-  if (CHI2) finish_chi2<G>(a, x, ls);
-}
-
-// One wave's share of the work, asynchronous form: every lane moves on to
-// its next epoch as soon as its own solve has converged, so a wavefront pays
-// for the lanes' own sweeps (plus the epoch set-up and image work of the
-// lanes finishing in a pass) instead of the slowest lane of every epoch.
-// The warm start is that of the lockstep form (warm_weights), and so is
-// every lane's arithmetic: the two forms give the same results bit for bit.
-template <int MODE, bool CHI2, int G>
-__device__ __forceinline__ void fit_wave_async(const FitArgs& a, int64_t wave_item,
-                                               LaneStats& st) {
-  constexpr int MAXIT64 = 60, MAXIT32 = 30;
-  const double tau64 = SBLM_ROOT_TAU;
-  const float tau32 = SBLM_ROOT_TAU32;
-  const Item x = item_setup<G>(a, wave_item);
-  Lsq ls = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  cx<double> z[5];  // iterate; the roots of the two epochs before are in LDS
-  const RootHist hist = {fit_dyn_smem};  // zp (slot 0), zpp (slot 1)
-#pragma unroll
-  for (int i = 0; i < 5; ++i) {
-    z[i] = {0.0, 0.0};
-    hist.set(0, i, {0.0, 0.0});
-    hist.set(1, i, {0.0, 0.0});
-  }
-  int nhist = 0;  // solved epochs held in z (after convergence), zp, zpp
-  double t1 = 0.0, t2 = 0.0, t3 = 0.0;
-  bool prev_deg4 = false;
-  int64_t k = x.k0;
-  bool busy = k < x.k1, need_setup = busy;
-  cx<double> zeta = {0.0, 0.0}, c[6];
-#pragma unroll
-  for (int j = 0; j < 6; ++j) c[j] = {0.0, 0.0};
-  // phase of the current solve: 0 FP32 iteration, 1 FP64 Newton polish
-  // (MIXED), 2 FP64 iteration
-  bool deg4 = false, warm = false, fell_back = false;
-  int phase = 2;
-  double t = 0.0;
-  int it64 = 0, it32 = 0, it_prior = 0, nw = 0;
-  double d2[5];  // squared nearest-root distances at the start of the polish
-#pragma unroll
-  for (int i = 0; i < 5; ++i) d2[i] = 0.0;
-  bool retried = false;
-  double em64 = INFINITY;
-  float prev32 = INFINITY;
-  unsigned long long passes = 0;
-  while (__any(busy)) {
-    ++passes;
-    if (busy) {
-      if (need_setup) {
-        t = a.t[k];
-        deg4 = epoch_poly(x, t, zeta, c);
-        warm = nhist >= 1 && !deg4 && !prev_deg4;
-        if (warm) {
-          // weights of z (epoch t1), zp (t2), zpp (t3)
-          double w1, w2, w3;
-          warm_weights(t, t1, t2, t3, nhist >= 2, nhist >= 3, w1, w2, w3);
-#pragma unroll
-          for (int i = 0; i < 5; ++i) {
-            const cx<double> zp = hist.get(0, i), zpp = hist.get(1, i);
-            const cx<double> p = extrapolate(z[i], zp, zpp, w1, w2, w3);
-            hist.set(1, i, zp);
-            hist.set(0, i, z[i]);
-            z[i] = p;
-          }
-          t3 = t2;
-          t2 = t1;
-        } else {
-          cold_start<double>(c, zeta, x.d, x.q, deg4, z, !deg4 && far_root(c));
-        }
-        phase = (MODE == SBLM_MIXED) && !deg4 && !far_root(c) ? (warm ? 1 : 0) : 2;
-        if (phase == 1) nearest2(z, d2);
-        it64 = 0;
-        it32 = 0;
-        nw = 0;
-        fell_back = false;
-        it_prior = 0;
-        retried = false;
-        em64 = INFINITY;
-        prev32 = INFINITY;
-        need_setup = false;
-      }
-      bool finished = false, conv = false;
-      if (MODE == SBLM_MIXED && phase == 0) {
-        // FP32 sweep on the rounded iterate (exactly representable back in FP64)
-        cx<float> cf[6], zf[5];
-#pragma unroll
-        for (int j = 0; j < 6; ++j) cf[j] = {(float)c[j].re, (float)c[j].im};
-#pragma unroll
-        for (int i = 0; i < 5; ++i) zf[i] = {(float)z[i].re, (float)z[i].im};
-        float em;
-        bool d32 = aberth_sweep<true>(cf, zf, false, tau32, &em);
-        d32 = d32 || (it32 >= 4 && em > 0.25f * prev32);
-        prev32 = em;
-#pragma unroll
-        for (int i = 0; i < 5; ++i) z[i] = {(double)zf[i].re, (double)zf[i].im};
-        ++it32;
-        if (d32 || it32 >= MAXIT32) {
-          phase = 1;
-          nearest2(z, d2);
-        }
-      } else if (MODE == SBLM_MIXED && phase == 1) {
-        // at most two FP64 Newton steps on every root (see solve_roots)
-        const bool pol = newton_pass(c, z, d2, tau64);
-        ++nw;
-        if (pol || nw >= 2) {
-          double d2n[5];
-          nearest2(z, d2n);
-          bool apart = true;
-#pragma unroll
-          for (int i = 0; i < 5; ++i) apart = apart && (d2n[i] >= 0.25 * d2[i]);
-          if (!apart) cold_start<double>(c, zeta, x.d, x.q, deg4, z, false);
-          if (pol && apart) {
-            conv = true;
-            finished = true;
-          } else {
-            phase = 2;
-            fell_back = true;
-          }
-        }
-      } else {
-        conv = aberth_sweep<false>(c, z, deg4, tau64, (double*)nullptr);
-        ++it64;
-        finished = conv || it64 >= MAXIT64;
-        // a capped solve: one more sweep measures how far its roots still move
-        if (finished && !conv) (void)aberth_sweep<true>(c, z, deg4, tau64, &em64);
-      }
-      bool finite = true;
-      if (finished) {
-#pragma unroll
-        for (int i = 0; i < 5; ++i)
-          finite = finite && isfinite(z[i].re) && isfinite(z[i].im);
-        if (!(conv && finite) && warm && !retried) {
-          // the warm-started solve failed: again from the cold start (see
-          // the lockstep form)
-          cold_start<double>(c, zeta, x.d, x.q, deg4, z, !deg4 && far_root(c));
-          warm = false;
-          retried = true;
-          phase = (MODE == SBLM_MIXED) && !deg4 && !far_root(c) ? 0 : 2;
-          it_prior += it64 + it32;
-          st.iters32 += it32;
-          st.newton += nw;
-          it64 = 0;
-          it32 = 0;
-          nw = 0;
-          fell_back = false;
-          em64 = INFINITY;
-          prev32 = INFINITY;
-          st.retried += 1;
-          finished = false;
-        }
-      }
-      if (finished) {
-        const bool ok = conv && finite;
-        const bool settled = finite && (conv || em64 <= SBLM_SETTLED_STEP2);
-        int nimg, npol = 0;
-        double A = magnification(z, zeta, x.d, x.q, deg4, nimg, npol);
+      if (!again) {
+        int npol = 0, order[5];
+        A = magnification(z, zeta, d, q, deg4, nimg, npol, false, order);
+        st.polished += npol;
+        st.capped += ok ? 0 : 1;
         if (!settled) {
           A = NAN;
           nimg = 0;
+          st.unsettled += 1;
         }
-        if (CHI2) {
-          lsq_include(ls, a.w[k], 1.0, A, a.y[k]);
-        } else {
-          const int64_t o = x.ind * a.n_t + (k - x.e0);
-          a.A[o] = A;
-          if (a.n_img) a.n_img[o] = (int8_t)nimg;
-        }
-        st.solves += 1;
-        st.iters += it_prior + it64 + it32;
-        st.iters32 += it32;
-        st.capped += ok ? 0 : 1;
-        st.unsettled += settled ? 0 : 1;
-        st.deg4 += deg4 ? 1 : 0;
-        st.polished += npol;
-        if (MODE == SBLM_MIXED) {
-          st.fallback += fell_back ? 1 : 0;
-          st.newton += nw;
-        }
-        // z now holds the roots of epoch t
-        nhist = ok ? (warm ? (nhist < 3 ? nhist + 1 : 3) : 1) : 0;
-        t1 = t;
-        prev_deg4 = deg4;
-        ++k;
-        busy = k < x.k1;
-        need_setup = busy;
       }
+      put_epoch<CHI2>(a, x, k, wk, yk, A, nimg, ls);
     }
   }
-  if (x.k1 > x.k0) st.wave_iters += passes;
+}
+
+// Chains along which three images are carried: predicted from the epochs
+// before and tracked (track_images); the lanes that fail a check solve for all
+// five roots (solve_epoch), which a wave goes through when any of its lanes
+// does.
+//   Bound by FP64 arithmetic (893 FLOPs per tracked epoch, 1920 of a solve with
+// the sweeps a wave takes in lockstep).  Solved at every epoch, 256 x 1000
+// epochs x 256 individuals took 4.23 ms FP64 over the prior and 3.23 ms for an
+// evolved population, tracked 2.43 and 2.05; 256 x 200-5000 x 128 5.03 and 3.07
+// ms; 64 x 1000 x 256 MIXED 1.58 and 1.02 ms.
+template <int MODE, bool CHI2, int G>
+__device__ __forceinline__ void track_chain(const FitArgs& a, const Item& x, int64_t Cg, int64_t C,
+                                            LaneStats& st, Lsq& ls) {
+  const int64_t k0 = x.k0, k1 = x.k1;
+  const double q = x.q, d = x.d, t0 = x.t0;
+  cx<double> zt[3], vt[3];  // the images at the epoch before, their velocities
+  const RootHist hist = {fit_dyn_smem};  // ... at the one before that (slots 0 and 1)
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    zt[i] = {0.0, 0.0};
+    vt[i] = {0.0, 0.0};
+    hist.set(0, i, {0.0, 0.0});
+    hist.set(1, i, {0.0, 0.0});
+  }
+  const cx<double> vz = {x.sa * x.itE, -x.ca * x.itE};  // the source's velocity
+  bool warm = false;                                    // the images are known
+  double t1 = 0.0, t2 = 0.0;                            // those epochs
+  unsigned int tracked = 0;
+  LaneStats slow = {};  // (in memory: solve_epoch adds to it)
+
+  double t_next = (0 < Cg && k0 < k1) ? a.t[k0] : t0;  // as in solve_chain
+  for (int64_t s = 0; s < C; ++s) {
+    const int64_t k = k0 + s;
+    const bool active = (s < Cg) && (k < k1);
+    const double t = active ? t_next : t0;
+    t_next = (s + 1 < Cg && k + 1 < k1) ? a.t[k + 1] : t0;
+    double wk = 0.0, yk = 0.0;
+    if (CHI2 && active) {
+      wk = a.w[k];
+      yk = a.y[k];
+    }
+    const cx<double> zeta = source_position(t, t0, x.itE, x.sa, x.ca, x.u0);
+    double* rc = nullptr;
+    if constexpr (CHI2 && G >= 64) {
+      if (s == 0 && active) {
+        rc = root_cache_of<G>(a, x);
+        if (rc) warm = cached_start<3>(a, x, rc, zt);
+      }
+    }
+    // prediction of every image (track_weights); the history shifts as it is
+    // used
+    cx<double> z[5];
+    {
+      double wd, w1, w2;
+      track_weights(t, t1, t2, wd, w1, w2);
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        z[i] = predict(zt[i], hist.get(0, i), vt[i], hist.get(1, i), wd, w1, w2);
+        hist.set(0, i, zt[i]);
+        hist.set(1, i, vt[i]);
+      }
+    }
+    double A = 0.0;
+    int nimg = 3;
+    bool ok = true, need = active;
+    if (active && warm) {
+#pragma unroll
+      for (int i = 0; i < 3; ++i) zt[i] = z[i];
+      need = !track_images(zt, vt, zeta, vz, d, q, A, nimg, z[3], z[4]);
+      tracked += need ? 0u : 1u;
+    }
+    const bool any_need = __any(need);
+    if (any_need) {
+      double io[15];
+      if (need && warm) (void)other_roots(zeta, d, q, z, z[3], z[4]);
+#pragma unroll
+      for (int i = 0; i < 5; ++i) {
+        io[2 * i] = z[i].re;
+        io[2 * i + 1] = z[i].im;
+      }
+      io[10] = zeta.re;
+      io[11] = zeta.im;
+      io[12] = d;
+      io[13] = q;
+      const int in = need ? SOLVE_ACTIVE | SOLVE_NEXT | (warm ? SOLVE_WARM : 0)
+                          : (active ? SOLVE_FOLLOW : 0);
+      const int out = solve_epoch<MODE>(io, in, &slow);
+      if (need) {
+        A = io[14];
+        nimg = out >> 4;
+        ok = (out & SOLVE_OK) != 0;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) zt[i] = {io[2 * i], io[2 * i + 1]};
+      }
+    }
+    if constexpr (CHI2 && G >= 64) {
+      if (rc) save_start<3>(rc, zt, ok);
+    }
+    // a chain that starts here: its history from the expansion of the images
+    // about this epoch
+    if (s + 1 < C && (s == 0 || any_need)) {
+      if (s == 0 || need) {
+        const double h = t_next - t;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+          cx<double> z2, v2;
+          image_history(zt[i], zeta, vz, d, q, h, vt[i], z2, v2);
+          hist.set(0, i, z2);
+          hist.set(1, i, v2);
+        }
+        t1 = t - h;
+      }
+    }
+    warm = ok;
+    t2 = t1;
+    t1 = t;
+    if (active) put_epoch<CHI2>(a, x, k, wk, yk, A, nimg, ls);
+  }
+  slow.solves += tracked;
+  slow.newton += tracked;
+  add_stats(st, slow);
+}
+
+// The longest of the chunks c of a wave's groups.
+template <int G>
+__device__ __forceinline__ int64_t wave_longest(int64_t c) {
+#pragma unroll
+  for (int o = G; o < 64; o <<= 1) {
+    const int64_t oc = __shfl_xor(c, o, 64);
+    c = oc > c ? oc : c;
+  }
+  return c;
+}
+
+// One wave's share of the work: 64/G individuals (items wave_item*64/G ...);
+// every lane takes its s-th epoch at the same time.  Where a wave holds chains
+// of both kinds (tracked_chains) it goes through both loops.
+template <int MODE, bool CHI2, int G>
+__device__ __forceinline__ void fit_wave(const FitArgs& a, int64_t wave_item, LaneStats& st) {
+  const Item x = item_setup<G>(a, wave_item);
+  Lsq ls = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  const int64_t lanes = G == WIDE ? a.lanes_per_ind : G;
+  const bool track = tracked_chains(a.n_ind, lanes, x.L, x.Cg);
+  const int64_t Cs = track ? 0 : x.Cg, Ct = track ? x.Cg : 0;
+  const int64_t ws = wave_longest<G>(Cs), wt = wave_longest<G>(Ct);
+  if (ws > 0) solve_chain<MODE, CHI2, G>(a, x, Cs, ws, st, ls);
+  if (wt > 0) track_chain<MODE, CHI2, G>(a, x, Ct, wt, st, ls);
   if (CHI2) finish_chi2<G>(a, x, ls);
 }
 
@@ -956,13 +1080,13 @@ __device__ __forceinline__ void fit_wave_async(const FitArgs& a, int64_t wave_it
 // counter.  All forms are compiled for two waves per SIMD: left alone, the
 // mixed form takes 272 registers and runs one, where its dependent FP64
 // chains leave the SIMD idle half of the time.
-template <int MODE, bool CHI2, int G, int PERSIST, int ASYNC>
+template <int MODE, bool CHI2, int G, int PERSIST>
 __global__ __launch_bounds__(256, 2) void fitness_kernel(
     FitArgs a) {
   // (blocks of at most 256 threads: launch_gg refuses larger ones)
   constexpr int GPW = G > 64 ? 1 : 64 / G;  // individuals per wave
   const int lane = threadIdx.x & 63;
-  LaneStats st = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+  LaneStats st = {};
   // One-shot grid: wave w takes wave item w (blocks remapped so that
   // consecutive logical blocks sit on one XCD, unless a work order is
   // given).  Persistent grid: waves take items from a shared counter until
@@ -986,10 +1110,7 @@ __global__ __launch_bounds__(256, 2) void fitness_kernel(
           if (lane == 0) v = atomicAdd(a.queue + x, 1u);
           const int64_t wi = w0 + (int64_t)__shfl(v, 0, 64);
           if (wi >= w1) break;
-          if constexpr (ASYNC)
-            fit_wave_async<MODE, CHI2, G>(a, wi, st);
-          else
-            fit_wave<MODE, CHI2, G>(a, wi, st);
+          fit_wave<MODE, CHI2, G>(a, wi, st);
         }
       }
     } else {
@@ -998,10 +1119,7 @@ __global__ __launch_bounds__(256, 2) void fitness_kernel(
         if (lane == 0) v = atomicAdd(a.queue, 1u);
         const int64_t wi = (int64_t)__shfl(v, 0, 64);
         if (wi >= n_wave_items) break;
-        if constexpr (ASYNC)
-          fit_wave_async<MODE, CHI2, G>(a, wi, st);
-        else
-          fit_wave<MODE, CHI2, G>(a, wi, st);
+        fit_wave<MODE, CHI2, G>(a, wi, st);
       }
     }
   } else {
@@ -1014,16 +1132,13 @@ __global__ __launch_bounds__(256, 2) void fitness_kernel(
                    : (xcd < rem) ? xcd * (per + 1) + idx
                                  : rem * (per + 1) + (xcd - rem) * per + idx;
     const int64_t wi = (int64_t)lb * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    if constexpr (ASYNC)
-      fit_wave_async<MODE, CHI2, G>(a, wi, st);
-    else
-      fit_wave<MODE, CHI2, G>(a, wi, st);
+    fit_wave<MODE, CHI2, G>(a, wi, st);
   }
   if (a.stats) {
     // wave sums in 64 bits
-    unsigned long long v[11] = {st.solves,  st.iters,     st.capped,   st.fallback,
-                                st.deg4,    st.wave_iters, st.iters32, st.polished,
-                                st.retried, st.unsettled, st.newton};
+    unsigned long long v[11] = {st.solves,     st.iters,   st.capped,   st.fallback,
+                                st.deg4,       st.wave_iters, st.iters32, st.polished,
+                                st.retried,    st.unsettled, st.newton};
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1)
 #pragma unroll
@@ -1052,11 +1167,11 @@ static hipError_t launch_gg(const FitArgs& a, hipStream_t s, int wpb) {
     // several waves per individual: one-shot grid, lockstep; for chi^2, where
     // they meet at the merge, whole individuals in every block
     const int P = (G == WIDE ? a.lanes_per_ind : G) / 64;
-    if (a.queue || a.async || (CHI2 && wpb % P != 0)) return hipErrorInvalidConfiguration;
+    if (a.queue || (CHI2 && wpb % P != 0)) return hipErrorInvalidConfiguration;
     const size_t smem = ROOT_HIST_BYTES * 64 * wpb + 6 * sizeof(double) * wpb;
     const int64_t nblk = (a.n_ind * P + wpb - 1) / wpb;
     if (nblk <= 0) return hipSuccess;
-    hipLaunchKernelGGL((fitness_kernel<MODE, CHI2, G, 0, 0>), dim3((unsigned)nblk),
+    hipLaunchKernelGGL((fitness_kernel<MODE, CHI2, G, 0>), dim3((unsigned)nblk),
                        dim3(64 * wpb), smem, s, a);
     return hipGetLastError();
   } else {
@@ -1066,10 +1181,7 @@ static hipError_t launch_gg(const FitArgs& a, hipStream_t s, int wpb) {
     if (nblk <= 0) return hipSuccess;
     if (!CHI2 && a.queue) return hipErrorInvalidConfiguration;
     constexpr int PF = CHI2 ? 1 : 0;  // (magnifications: the one-shot grid only)
-    auto kern = a.async ? (a.queue ? fitness_kernel<MODE, CHI2, G, PF, 1>
-                                   : fitness_kernel<MODE, CHI2, G, 0, 1>)
-                        : (a.queue ? fitness_kernel<MODE, CHI2, G, PF, 0>
-                                   : fitness_kernel<MODE, CHI2, G, 0, 0>);
+    auto kern = a.queue ? fitness_kernel<MODE, CHI2, G, PF> : fitness_kernel<MODE, CHI2, G, 0>;
     if (a.queue) {  // persistent grid: as many blocks as can be resident
       int dev = 0, ncu = 0, per_cu = 0;
       hipError_t e = hipGetDevice(&dev);

@@ -14,6 +14,9 @@ namespace sblm {
 int set_error(int code, const char* fmt, ...);
 int check_hip(hipError_t e, const char* what);
 
+// Doubles a lane saves of its first epoch (see FitArgs::root_cache).
+constexpr int ROOT_CACHE = 10;
+
 // Arguments of the batched fitness kernels (one wave per individual).
 struct FitArgs {
   // population: theta[j * n_ind + i] decoded, or encoded P with lo/hi
@@ -38,9 +41,10 @@ struct FitArgs {
   sblm_stats* stats;  // nullable
   // schedule
   const int32_t* order;  // nullable: item -> individual permutation
-  double* root_cache;     // nullable, G >= 64 only: [n_ind][G][10] roots of
-                          // each lane's first epoch, read as its start
-                          // (when finite) and rewritten after the solve
+  double* root_cache;     // nullable, G >= 64 only: [n_ind][G][ROOT_CACHE],
+                          // the roots (tracked: three images) of each lane's
+                          // first epoch, read as its start (when finite) and
+                          // rewritten after it
   const int32_t* cold;    // nullable (with root_cache): individual i ignores
                           // the cache when cold[i / cold_per] != 0
   int64_t cold_per;
@@ -53,10 +57,27 @@ struct FitArgs {
   const int64_t* xcd_start;  // nullable: [9] order positions; the items at
                              // [xcd_start[x], xcd_start[x+1]) belong to XCD x
                           // (must read 0 when the kernel starts)
-  int32_t async;          // 1: lanes step through their epochs independently
   const int32_t* skip;    // nullable (CSR only): individual i is evaluated
   int32_t skip_per;       // as empty when skip[i / skip_per] != 0
 };
+
+// Lanes of one residency of the chip: 256 compute units x 8 waves.
+constexpr int64_t RESIDENT_LANES = 2048 * 64;
+
+// Whether images are tracked along the chains of C epochs of an individual with
+// L epochs, G lanes each of n_ind: where the epochs are dense enough that a step
+// of a wave seldom needs a solve all the same, and the chain long enough to
+// repay its dearer first epoch.  For epochs over a few tE, solved and tracked
+// us FP64 in a launch of 8 residencies of the chip (65536 individuals, 16
+// lanes): 638 and 720 for 80 epochs, 828 and 848 for 100, 1006 and 939 for 130,
+// 1761 and 1265 for 300, 2962 and 1754 for 600.  Where little runs, the slowest
+// wave decides, and it has most of the failures (4096 individuals, 32 lanes):
+// 102 and 137 for 130, 126 and 148 for 200, 157 and 156 for 300, 196 and 186 for
+// 400, 258 and 207 for 600; and in chains of three (256 individuals, 256 lanes,
+// 600 epochs) 48 and 52.
+inline __host__ __device__ bool tracked_chains(int64_t n_ind, int64_t G, int64_t L, int64_t C) {
+  return n_ind * G >= 4 * RESIDENT_LANES ? L > 112 && C > 2 : L > 320 && C > 3;
+}
 
 // Launch the FP64 or mixed fitness kernel; chi2 = false writes A/n_img.
 // Lanes per individual for a launch of n_ind individuals: the fewest of 8,
@@ -66,7 +87,7 @@ struct FitArgs {
 // compute units x 8 waves) takes the widest group, up to 256 lanes over
 // several waves, that fits one.
 inline int default_lanes(int64_t n_ind) {
-  constexpr int64_t RESIDENT = 2048 * 64;
+  constexpr int64_t RESIDENT = RESIDENT_LANES;
   if (n_ind * 64 <= RESIDENT) {
     int g = 64;
     while (g < 256 && n_ind * (2 * g) <= RESIDENT) g *= 2;
@@ -80,23 +101,25 @@ inline int default_lanes(int64_t n_ind) {
 // Lanes per individual for the magnifications of n individuals at n_t shared
 // epochs, where no sum over the epochs ties the lanes together: the number of
 // lowest modelled time, the fewest among equals.  A lane's chain of C epochs
-// costs 2.5 for the cold start and w for every warm one, w = 1 for dense
-// epochs, more (a poorer extrapolation) for few.  The n G lanes are r = n G /
-// 2^17 residencies of the chip; below one residency only the chain's length
-// counts (a little slower when waves share a SIMD), above it the work grows
+// costs 2.5 for the cold start and w for every other one, w = 0.6 where images
+// are tracked, else 1 for dense epochs, more (a poorer extrapolation) for few.
+// The n G lanes are r = n G / 2^17 residencies of the chip; below one residency
+// only the chain's length counts (a little slower when waves share a SIMD), above it the work grows
 // with r and more, shorter waves even out what the slowest lane of each
 // holds up (the factor, fitted to 1 <= r <= 32 at 4096 x 1000).  In us at G
 // lanes against the rule's choice: 2^20 single epochs 1660 (8), 187 (1); one
-// curve of 1000 epochs 21 (256), 11 (1024); 16384 x 256 470 (8), 442 (32);
-// 4096 x 1000 405 (32), 347 (128); 10^5 x 4 135 (8), 85 (4); 16 x 5000 131
-// (256), 30 (8192); 65536 x 256 1601 (64), 1507 (16).
+// curve of 1000 epochs 18 (256), 11 (1024); 256 x 1000 46 (512), 41 (256);
+// 16384 x 256 470 (8), 345 (32); 4096 x 1000 238 (32), 229 (64); 10^5 x 4 135
+// (8), 85 (4); 16 x 5000 72 (256), 31 (8192); 65536 x 256 1191 (64), 980 (16).
 inline int64_t magnify_lanes(int64_t n, int64_t n_t) {
-  const double w = 1.0 + fmin(1.5, 12.0 / (double)n_t);
+  const double w_solved = 1.0 + fmin(1.5, 12.0 / (double)n_t);
   int64_t best = 1;
   double best_cost = 0.0;
   for (int64_t g = 1;; g *= 2) {
-    const double r = (double)n * (double)g / (double)(2048 * 64);
-    const double chain = 2.5 + w * (double)((n_t + g - 1) / g - 1);
+    const double r = (double)n * (double)g / (double)RESIDENT_LANES;
+    const int64_t C = (n_t + g - 1) / g;
+    const double w = tracked_chains(n, g, n_t, C) ? 0.6 : w_solved;
+    const double chain = 2.5 + w * (double)(C - 1);
     const double cost = chain * (r < 1.0 ? 1.3 + 0.8 * r : r + 1.1 * sqrt(r));
     if (g == 1 || cost < best_cost) {
       best = g;

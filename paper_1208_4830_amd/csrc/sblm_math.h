@@ -7,8 +7,8 @@
 // kernel (device code, R = double or float) and the FLOP counting build
 // (host code, R = a number type that counts its operations), so that the
 // operation counts used for the roofline come from this very code.  Every R
-// supplies, found by overload resolution: fma(a, b, c), rcp_hw(x) (the
-// hardware reciprocal estimate), vmin / vmax (minimum / maximum), fabs and
+// supplies, found by overload resolution: fma(a, b, c), rcp_hw(x) and rsq_hw(x)
+// (the hardware estimates of 1/x and 1/sqrt(x)), vmin / vmax (minimum / maximum), fabs and
 // isfinite; is_single<R> says whether R stands for FP32 (its reciprocal
 // steps take no refinement).
 #pragma once
@@ -354,6 +354,149 @@ SBLM_FN R refine_image(cx<R> zi, cx<R> zeta, R d, R q) {
   return rcp_acc(fabs(R(1.0) - c_norm(g)));
 }
 
+// ---------------------------------------------------------------- tracking
+
+// At most epochs of a chain the images move a little and none appears or
+// vanishes.  Then three images followed on the lens equation itself (Newton
+// from their extrapolation) give the other two roots of the lens polynomial
+// in closed form, from the sum and the product of all five, and with them
+// the image count: no simultaneous iteration.  Any three distinct solutions of
+// the lens equation will do -- they are roots of the polynomial -- so a step
+// only has to show that it has arrived at one; where it cannot (next to a
+// caustic, after a long gap, a source on a lens) the five roots are solved
+// for.
+
+// Square root to about 1 ulp from the hardware estimate of 1/sqrt(x) (x > 0).
+template <typename R>
+SBLM_FN R sqrt_acc(R x) {
+  const R y = rsq_hw(x);
+  R g = x * y, h = R(0.5) * y;
+  const R e = fma(-h, g, R(0.5));
+  g = fma(g, e, g);
+  h = fma(h, e, h);
+  return fma(fma(-g, g, x), h, g);
+}
+
+#define SBLM_TRACK_EST 1e-12 /* relative error of an image's A after its last step */
+#define SBLM_TRACK_SPURIOUS2 1e-8 /* |residual|^2 above which a root is no image */
+#define SBLM_TRACK_IMAGE2 1e-16   /* ... and below which it is one */
+#define SBLM_TRACK_APART2 1e-10   /* |z_i - z_j|^2 of two images at least */
+
+// The lens equation at a trial image z, as image_eval: residual r, g =
+// a^2 + q b^2 with a = 1/conj(z), b = 1/(d - conj(z)).
+template <typename R>
+struct LensAt {
+  cx<R> a, b, a2, qb2, r, g;
+  R iz, ie;
+};
+template <bool ACC, typename R>
+SBLM_FN LensAt<R> lens_at(cx<R> z, cx<R> zeta, R d, R q) {
+  LensAt<R> e;
+  const R x = z.re, y = z.im;
+  const R n2 = fma(x, x, y * y);
+  const R ex = d - x;
+  const R e2 = fma(ex, ex, y * y);
+  const R ip = ACC ? rcp_acc(n2 * e2) : rcp_fast(n2 * e2);
+  e.iz = e2 * ip;
+  e.ie = n2 * ip;
+  e.a = {x * e.iz, y * e.iz};
+  e.b = {ex * e.ie, -y * e.ie};
+  e.r = {fma(-q, e.b.re, (zeta.re - x) + e.a.re), fma(-q, e.b.im, (zeta.im - y) + e.a.im)};
+  e.a2 = c_mul(e.a, e.a);
+  const cx<R> b2 = c_mul(e.b, e.b);
+  e.qb2 = {q * b2.re, q * b2.im};
+  e.g = {e.a2.re + e.qb2.re, e.a2.im + e.qb2.im};
+  return e;
+}
+
+// |residual|^2 of the lens equation at z.
+template <typename R>
+SBLM_FN R lens_residual2(cx<R> z, cx<R> zeta, R d, R q) {
+  const R x = z.re, y = z.im;
+  const R n2 = fma(x, x, y * y);
+  const R ex = d - x;
+  const R e2 = fma(ex, ex, y * y);
+  const R ip = rcp_fast(n2 * e2);
+  const R iz = e2 * ip, qe = q * (n2 * ip);
+  return c_norm(cx<R>{fma(x, iz, fma(-ex, qe, zeta.re - x)), fma(y, iz, fma(y, qe, zeta.im - y))});
+}
+
+// One Newton step on the lens equation, z += (r - g conj(r))/(1 - |g|^2).
+template <typename R>
+SBLM_FN void image_newton(cx<R>& z, cx<R> zeta, R d, R q) {
+  const LensAt<R> e = lens_at<false>(z, zeta, d, q);
+  const R id = rcp_raw(R(1.0) - c_norm(e.g));
+  const cx<R> gr = c_mul(e.g, cx<R>{e.r.re, -e.r.im});
+  z = {fma(e.r.re - gr.re, id, z.re), fma(e.r.im - gr.im, id, z.im)};
+}
+
+// A Newton step that is meant to be the last: *g is g after it to first order
+// in dz, g + h conj(dz) with h = dg/dconj(z) = 2 q b^3 - 2 a^3, *inv the
+// reciprocal of det J = 1 - |g|^2.  Returns whether A_i = |1/det J| is final:
+// what is neglected (|dz|^2 dg''/2 in g, and the position's remaining error K
+// |dz|^2, K = |h| (1 + |g|)/(2 |det|)) moves it by at most SBLM_TRACK_EST
+// relative.  (|g| <= (1 + |g|^2)/2 keeps square roots out of the bound; false
+// for NaN.)
+template <typename R>
+SBLM_FN bool image_close(cx<R>& z, cx<R> zeta, R d, R q, cx<R>* g, R* inv) {
+  const LensAt<R> e = lens_at<true>(z, zeta, d, q);
+  const R gn = c_norm(e.g), det = R(1.0) - gn;
+  const R id = rcp_fast(det);
+  const cx<R> gr = c_mul(e.g, cx<R>{e.r.re, -e.r.im});
+  const cx<R> dz = {(e.r.re - gr.re) * id, (e.r.im - gr.im) * id};
+  // h/2 and g after the step
+  const cx<R> a3 = c_mul(e.a2, e.a);
+  const cx<R> hh = c_fma(e.qb2, e.b, cx<R>{-a3.re, -a3.im});
+  const cx<R> dh = c_mul(hh, cx<R>{dz.re, -dz.im});
+  *g = {fma(R(2.0), dh.re, e.g.re), fma(R(2.0), dh.im, e.g.im)};
+  *inv = rcp_acc(R(1.0) - c_norm(*g));
+  z = {z.re + dz.re, z.im + dz.im};
+  const R dn = c_norm(dz), hn = c_norm(hh);
+  return (R(1.0) + gn) * dn *
+             fma(R(3.0) * fma(e.iz, e.iz, q * e.ie * e.ie), fabs(det), hn * (R(3.0) + gn)) <=
+         R(SBLM_TRACK_EST) * (det * det);
+}
+
+// The other two roots (z3, z4) of the lens polynomial from three of them, by
+// the sum -c4/c5 and the product -c0/c5 of all five.  False where that loses
+// accuracy: a root far out (|c4| > 1e3 |c5|), or the two closer than about
+// 1e-4 of their mean.
+template <typename R>
+SBLM_FN bool other_roots(cx<R> zeta, R d, R q, const cx<R> z[3], cx<R>& z3, cx<R>& z4) {
+  // c5 = -n2 m2, c4 = zeta n2 m2 - (n2 m1 + n1 m2) + m2 + q n2, c0 = zeta d^2
+  // (lens_coeffs)
+  const cx<R> w = {zeta.re, -zeta.im};
+  const R opq = R(1.0) + q;
+  const cx<R> n1 = {fma(-d, w.re, opq), -d * w.im};
+  const cx<R> m2 = {w.re - d, w.im};
+  const cx<R> m1 = {fma(d, d, n1.re), n1.im};
+  const cx<R> c5 = c_mul(w, m2);  // -c5
+  const cx<R> nm3 = c_fma(w, m1, c_mul(n1, m2));
+  const cx<R> c4 = c_fma(zeta, c5, cx<R>{m2.re + fma(q, w.re, -nm3.re),
+                                         m2.im + fma(q, w.im, -nm3.im)});
+  const R n5 = c_norm(c5);
+  if (!(c_norm(c4) <= R(1e6) * n5)) return false;
+  const cx<R> t = c_mul(c_mul(c_mul(z[0], z[1]), z[2]), c5);  // -c5 z0 z1 z2
+  const R nt = c_norm(t);
+  const R ip = rcp_acc(n5 * nt);
+  const R i5 = nt * ip, it = n5 * ip * (d * d);
+  // S = z3 + z4 = c4/(-c5) - z0 - z1 - z2, P = z3 z4 = c0/(-c5 z0 z1 z2)
+  const cx<R> S = {fma(fma(c4.re, c5.re, c4.im * c5.im), i5, -z[0].re) - z[1].re - z[2].re,
+                   fma(fma(c4.im, c5.re, -c4.re * c5.im), i5, -z[0].im) - z[1].im - z[2].im};
+  const cx<R> P = {fma(zeta.re, t.re, zeta.im * t.im) * it,
+                   fma(zeta.im, t.re, -zeta.re * t.im) * it};
+  const cx<R> hs = {R(0.5) * S.re, R(0.5) * S.im};
+  const cx<R> D2 = c_fma(hs, hs, cx<R>{-P.re, -P.im});
+  const R m = sqrt_acc(c_norm(D2));
+  const R u = sqrt_acc(R(0.5) * (m + fabs(D2.re)));
+  const R v = R(0.5) * D2.im * rcp_acc(u);
+  const bool pos = !(D2.re < R(0.0));
+  const cx<R> D = {pos ? u : v, pos ? v : u};  // (for re < 0: i (u - i v))
+  z3 = {hs.re + D.re, hs.im + D.im};
+  z4 = {hs.re - D.re, hs.im - D.im};
+  return m > R(1e-8) * c_norm(hs);
+}
+
 // ---------------------------------------------------------------- fit
 
 // Square-root-free Givens state for columns (1, A | y): D = diag(d1, d2),
@@ -433,6 +576,71 @@ SBLM_FN void warm_weights(R t, R t1, R t2, R t3, bool have2, bool have3, R& w1, 
 template <typename R>
 SBLM_FN cx<R> extrapolate(cx<R> z1, cx<R> z2, cx<R> z3, R w1, R w2, R w3) {
   return {fma(w1, z1.re, fma(w2, z2.re, w3 * z3.re)), fma(w1, z1.im, fma(w2, z2.im, w3 * z3.im))};
+}
+
+// ---------------------------------------------------------------- prediction
+
+// Velocity of an image, dz/dt = (v - g conj(v)) inv with v = dzeta/dt, from g
+// and inv = 1/(1 - |g|^2) at the image.
+template <typename R>
+SBLM_FN cx<R> image_velocity(cx<R> v, cx<R> g, R inv) {
+  const cx<R> gv = c_mul(g, cx<R>{v.re, -v.im});
+  return {(v.re - gv.re) * inv, (v.im - gv.im) * inv};
+}
+
+// An image z of a source at zeta with constant velocity vz: its velocity v
+// and, from the expansion to third order in time, where it was and how fast it
+// went a time h earlier (z2, v2) -- the history of a chain that starts here.
+// Differentiating dz/dt + g conj(dz/dt) = vz, with h1 = dg/dconj(z) = 2 q b^3 -
+// 2 a^3 and h2 = 6 (a^4 + q b^4), gives every order by the solve of
+// image_velocity.
+template <typename R>
+SBLM_FN void image_history(cx<R> z, cx<R> zeta, cx<R> vz, R d, R q, R h, cx<R>& v, cx<R>& z2,
+                           cx<R>& v2) {
+  const LensAt<R> e = lens_at<true>(z, zeta, d, q);
+  const R inv = rcp_acc(R(1.0) - c_norm(e.g));
+  v = image_velocity(vz, e.g, inv);
+  const cx<R> a3 = c_mul(e.a2, e.a), qb3 = c_mul(e.qb2, e.b);
+  const cx<R> h1 = {R(2.0) * (qb3.re - a3.re), R(2.0) * (qb3.im - a3.im)};
+  const cx<R> vb = {v.re, -v.im};
+  const cx<R> gd = c_mul(h1, vb);  // dg/dt
+  const cx<R> wa = c_mul(gd, vb);
+  const cx<R> acc = image_velocity(cx<R>{-wa.re, -wa.im}, e.g, inv);
+  const cx<R> ab = {acc.re, -acc.im};
+  const cx<R> h2 = c_fma(e.a2, e.a2, c_mul(qb3, e.b));
+  const cx<R> gdd = c_fma(h1, ab, c_mul(c_mul(cx<R>{R(6.0) * h2.re, R(6.0) * h2.im}, vb), vb));
+  const cx<R> wj = c_fma(gdd, vb, c_mul(cx<R>{R(2.0) * gd.re, R(2.0) * gd.im}, ab));
+  const cx<R> jerk = image_velocity(cx<R>{-wj.re, -wj.im}, e.g, inv);
+  const R hh = R(0.5) * h, h3 = h * R(1.0 / 3.0);
+  z2 = {fma(-h, fma(-hh, fma(-h3, jerk.re, acc.re), v.re), z.re),
+        fma(-h, fma(-hh, fma(-h3, jerk.im, acc.im), v.im), z.im)};
+  v2 = {fma(-h, fma(-hh, jerk.re, acc.re), v.re), fma(-h, fma(-hh, jerk.im, acc.im), v.im)};
+}
+
+// Weights for the position of an image at epoch t from its positions and
+// velocities at the two previous epochs t1 > t2 (cubic Hermite extrapolation),
+// z = z1 + wd (z1 - z2) + w1 v1 + w2 v2; along its velocity where t1 = t2.  The
+// error is s^2 (s + h)^2 z^(4)/24 (s = t - t1, h = t1 - t2) against s (s + h)
+// (s + 2h) z^(3)/6 for the parabola through three positions; it carries
+// across a gap in the cadence (a night between two runs of epochs minutes
+// apart) up to a thousand spacings, where rounding (about 2 (s/h)^3 ulp) takes
+// over.  A poor start costs steps, never a wrong image.
+template <typename R>
+SBLM_FN void track_weights(R t, R t1, R t2, R& wd, R& w1, R& w2) {
+  const R s = t - t1, h = t1 - t2;
+  R r = s * rcp_fast(h);
+  if (!(h > R(0.0) && r <= R(1e3))) r = R(0.0);
+  const R u = R(1.0) + r;
+  wd = r * r * fma(R(2.0), r, R(3.0));
+  w1 = s * u * u;
+  w2 = s * r * u;
+  wd = -wd;
+}
+
+template <typename R>
+SBLM_FN cx<R> predict(cx<R> z1, cx<R> z2, cx<R> v1, cx<R> v2, R wd, R w1, R w2) {
+  return {fma(w1, v1.re, fma(w2, v2.re, fma(wd, z1.re - z2.re, z1.re))),
+          fma(w1, v1.im, fma(w2, v2.im, fma(wd, z1.im - z2.im, z1.im)))};
 }
 
 }  // namespace sblm

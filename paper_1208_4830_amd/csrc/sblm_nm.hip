@@ -883,7 +883,7 @@ int nm_run(const sblm_lcs& lcs, int32_t reps, const double* lo, const double* sp
   // trial point) shorten.  So the lanes follow the number of simplices that
   // ran in the last round (read every 16 rounds): the fewest of 64, 128, 256
   // that give the round's trial points 2^19 lanes, else 256.  Every width
-  // keeps the roots of each lane's first epoch (80 B per lane and trial
+  // keeps three images of each lane's first epoch (48 B per lane and trial
   // slot) and starts there in its next round (the simplex moves little
   // between rounds; a cache of a width not used for a while is only a
   // poorer start).  The choice depends on the simplices alone, so results
@@ -922,7 +922,7 @@ int nm_run(const sblm_lcs& lcs, int32_t reps, const double* lo, const double* sp
     const int g = 64 << i;
     if (fixed_g ? (g == fixed_g && g > 64) : true) {
       cache_off[i] = n_cache;
-      n_cache += n_trial * g * 10;
+      n_cache += n_trial * g * ROOT_CACHE;
     }
   }
   if (rc == SBLM_OK && n_cache > 0) {

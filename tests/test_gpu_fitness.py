@@ -80,6 +80,73 @@ def test_magnify_lanes_by_shape(hip, n, n_t):
     _check_magnify(hip, theta, t, 0, 1e-10)
 
 
+def _chain_epochs(pattern):
+    rng = np.random.default_rng(107)
+    if pattern == "dense":
+        return np.linspace(-60.0, 60.0, 1501)
+    if pattern == "few":  # with 64 lanes chains of one and of two epochs
+        return np.linspace(-60.0, 60.0, 101)
+    if pattern == "nights":  # runs of epochs minutes apart, some repeated
+        t = np.concatenate([k + 0.01 * np.arange(30) for k in range(-20, 20)])
+        return np.repeat(t, rng.integers(1, 3, t.size))
+    return rng.permutation(np.linspace(-60.0, 60.0, 401))  # "shuffled"
+
+
+@pytest.mark.parametrize("lanes", [1, 8, 64])
+@pytest.mark.parametrize("pattern", ["dense", "few", "nights", "shuffled"])
+def test_magnify_chains(hip, monkeypatch, pattern, lanes):
+    # images carried from epoch to epoch along chains of every length, across
+    # caustics, gaps, repeated and unordered epochs: magnifications and image
+    # counts are the oracle's, which solves for every epoch by itself
+    monkeypatch.setenv("SBLM_LANES", str(lanes))
+    rng = np.random.default_rng(108)
+    theta = inputs.draw_theta(rng, 16)
+    theta[0, ::4] = -3.0  # a planet's small caustics
+    theta[2, ::2] *= 0.2
+    t = _chain_epochs(pattern)
+    for mode, floor in ((0, 1e-10), (1, 1e-6)):
+        _, s = _check_magnify(hip, theta, t, mode, floor)
+        if pattern in ("dense", "nights") and lanes == 1:  # images tracked
+            assert s["n_newton"] > 0.8 * s["n_solves"], s
+    # an epoch that is no number: NaN there, and nothing else changes
+    A = hip.sblm_magnify(_cuda(theta), _cuda(t)).cpu().numpy()
+    t[t.size // 3] = np.nan
+    B = hip.sblm_magnify(_cuda(theta), _cuda(t)).cpu().numpy()
+    assert np.all(np.isnan(B[:, t.size // 3]))
+    keep = ~np.isnan(t)
+    assert np.all(rel_err(B[:, keep], A[:, keep]) < 1e-9)
+
+
+@pytest.mark.parametrize("n_t,tracked", [(112, False), (113, True), (200, True)])
+def test_magnify_chains_of_a_full_chip(hip, monkeypatch, n_t, tracked):
+    # a launch of many individuals tracks images along shorter chains of sparser
+    # epochs than one of few does; the magnifications are the same
+    monkeypatch.setenv("SBLM_LANES", "32")
+    rng = np.random.default_rng(109)
+    theta = inputs.draw_theta(rng, 16384)
+    t = np.linspace(-80.0, 80.0, n_t)
+    some = slice(0, 64)
+    for mode, floor in ((0, 1e-10), (1, 1e-6)):
+        st = hip.new_stats()
+        n_img = torch.zeros((theta.shape[1], n_t), dtype=torch.int8, device=DEV)
+        A = hip.sblm_magnify(_cuda(theta), _cuda(t), mode=mode, n_img=n_img, stats=st)
+        A, n_img = A.cpu().numpy()[some], n_img.cpu().numpy()[some]
+        s = hip.stats_dict(st)
+        assert s["n_solves"] == theta.shape[1] * n_t and s["n_unsettled"] == 0
+        if mode == 0:
+            assert (s["n_newton"] > 0) == tracked, s
+        Ao, no = O.magnify(theta[:, some], t)
+        err = rel_err(A, Ao)
+        zeta = source_positions(theta[:, some], t)
+        tau = (t[None, :] - theta[5, some][:, None]) / theta[4, some][:, None]
+        for i, k in np.argwhere(err > floor):
+            q, d = 10 ** theta[0, i], theta[1, i]
+            kappa = magnification_condition(zeta[i, k], d, q, tau[i, k], theta[2, i])
+            assert err[i, k] <= max(floor, kappa), (i, k, err[i, k], kappa, A[i, k])
+        for i, k in np.argwhere(n_img != no):
+            assert ambiguous_count(zeta[i, k], theta[1, i], 10 ** theta[0, i]), (i, k)
+
+
 def test_magnify_cold_starts_on_symmetry_axes(hip):
     # sources on the lens axis and on the axis perpendicular to it (u0 = 0,
     # alpha a multiple of pi/2), single epochs, so that every solve starts
