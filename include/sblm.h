@@ -284,9 +284,10 @@ int ea_evaluate(ea_state* st, sblm_stats* stats, void* stream);
  * (evaluate the fitness of every individual, then rank, select, reproduce
  * and mutate, test for stagnation and restart, repeated generation after
  * generation), each = ea_evaluate + (when due, the migration of ea_config,
- * Sec. 5.3) + ea_generation on the state's own buffers, replayed from one
- * captured HIP graph.
- *   n_gen  >= 0; 0 only captures the graph (bound to `stats`) when it is
+ * Sec. 5.3) + ea_generation on the state's own buffers, replayed from
+ * captured HIP graphs (of one generation, and of eight for a fit of 32 or
+ * more).
+ *   n_gen  >= 0; 0 only captures the graphs (bound to `stats`) when they are
  *          not captured yet, so that a later timed call replays at once
  *   stats  nullable device pointer; accumulates the counters of every
  *          generation's fitness evaluation
@@ -684,12 +685,13 @@ int mlp_adam_step(mlp_net* net, float lr, void* stream);
  * from lr0 (first step) to lr1 (last step).  loss (nullable, device float
  * [epochs*floor(rows/batch)]) receives the loss of every step.  The steps
  * are the ones that mlp_loss_grad and mlp_adam_step would take one call at
- * a time, bit for bit; here one step is captured as a HIP graph (batch
- * gather, forward, likelihood, backward, Adam, all reading the step index
- * from device memory) and replayed on the net's own stream, which follows
- * `stream` and which `stream` then waits for.  The graph is kept with the
- * net for later calls of the same shape and data; step buffers of 16 B per
- * step grow as needed (with a synchronisation of the net's stream).
+ * a time, bit for bit; here one step (and, for a call of 32 or more, eight
+ * in a row) is captured as a HIP graph (batch gather, forward, likelihood,
+ * backward, Adam, all reading the step index from device memory) and
+ * replayed on the net's own stream, which follows `stream` and which
+ * `stream` then waits for.  The graphs are kept with the net for later calls
+ * of the same shape and data; step buffers of 16 B per step grow as needed
+ * (with a synchronisation of the net's stream).
  * Errors: SBLM_EINVAL, SBLM_ERANGE (more than 2^31 steps), SBLM_ENOMEM,
  * SBLM_EDEVICE.
  */

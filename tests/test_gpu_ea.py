@@ -260,6 +260,28 @@ def test_fit_improves_and_best_is_monotone(hip, mode):
     assert best[-1] < best[0] and np.isfinite(best[-1]) and chi2_true > 0
 
 
+@pytest.mark.parametrize("islands", [1, 2])
+@pytest.mark.parametrize("n_gen", [31, 32, 45])
+def test_long_fits_equal_single_generations(hip, n_gen, islands):
+    # whole graphs of several generations, their remainder, and graphs dropped
+    # by a new schedule: the state and the counters of one generation at a time
+    wl = csr_workload(13, [40, 90])
+    kw = dict(n_islands=2, mig_every=3, n_migrants=2) if islands > 1 else {}
+    a, _, _ = _make_state(hip, wl, 24, seed=5, **kw)
+    b, _, _ = _make_state(hip, wl, 24, seed=5, **kw)
+    sa, sb = hip.new_stats(), hip.new_stats()
+    for _ in range(2):
+        a.fit(n_gen, stats=sa)
+        for _ in range(n_gen):
+            b.fit(1, stats=sb)
+        assert a.save() == b.save()
+        assert hip.stats_dict(sa) == hip.stats_dict(sb)
+        a.set_schedule(128, 4, 0, 0)
+        b.set_schedule(128, 4, 0, 0)
+    a.close()
+    b.close()
+
+
 # every schedule ea_set_schedule accepts, by lanes per individual
 _SCHEDULES = {g: [(g, wpb, pers, asy) for wpb in (1, 2, 4) for pers in (1, 0) for asy in (0, 1)]
               for g in (8, 16, 32, 64)}

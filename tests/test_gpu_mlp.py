@@ -380,6 +380,31 @@ def test_training_graph_equals_stepping_through_the_api(hip):
     b.close()
 
 
+@pytest.mark.parametrize("per,epochs", [(31, 1), (4, 8), (5, 7)])
+def test_training_graphs_of_several_steps(hip, per, epochs):
+    # 31, 32 and 35 steps, then one epoch more: whole graphs of several steps,
+    # their remainder, and a later call that finds the graph there, all equal
+    # to one step at a time, bit for bit
+    xb, _, y = hip.mlp_make_data(6, 0, 64 * per)
+    a, b = hip.MLP(batch_max=64, seed=9), hip.MLP(batch_max=64, seed=9)
+    f32 = lambda v: float(np.float32(v))
+    lr0, lr1 = f32(1e-3), f32(1e-4)
+    for ep in (epochs, 2):
+        la = a.train(xb, y, batch=64, epochs=ep, lr0=lr0, lr1=lr1).cpu().numpy()
+        total, lb = per * ep, []
+        for k in range(total):
+            r0 = (k % per) * 64
+            fr = k / (total - 1)  # (the schedule takes lr0 - lr1 in single precision)
+            lr = f32(lr1 + 0.5 * f32(lr0 - lr1) * (1.0 + math.cos(math.pi * fr)))
+            lb.append(b.loss_grad(xb[r0:r0 + 64], y[r0:r0 + 64]).item())
+            b.adam_step(lr)
+        torch.cuda.synchronize()
+        assert np.array_equal(la, np.array(lb, np.float32))
+        assert np.array_equal(a.get_params(), b.get_params())
+    a.close()
+    b.close()
+
+
 def test_seeding_matches_oracle(hip):
     lengths = [40, 0, 300, 1, 1200]
     lcs, off, (t, y, w) = make_lcs(hip, lengths, seed=4, special=False)
