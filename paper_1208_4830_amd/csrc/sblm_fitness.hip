@@ -270,7 +270,8 @@ __device__ __forceinline__ double magnification(const cx<double> z[5],
 // a chain); in 95% of a wave's steps no lane is left for the iteration.
 __device__ __forceinline__ bool track_images(cx<double> z[3], cx<double> v[3], cx<double> zeta,
                                              cx<double> vz, double d, double q, double& A,
-                                             int& nimg, cx<double>& z3, cx<double>& z4) {
+                                             int& nimg, cx<double>& z3, cx<double>& z4,
+                                             int passes = SBLM_TRACK_PASSES) {
   double ai[3];
   unsigned int todo = 0u;
 #pragma unroll
@@ -283,7 +284,7 @@ __device__ __forceinline__ bool track_images(cx<double> z[3], cx<double> v[3], c
     ai[i] = fabs(inv);
     v[i] = image_velocity(vz, g, inv);
   }
-  for (int pass = 0; pass < SBLM_TRACK_PASSES && __any(todo != 0u); ++pass) {
+  for (int pass = 0; pass < passes && __any(todo != 0u); ++pass) {
     if (todo) {
       const int i = __builtin_ctz(todo);
       cx<double> zi = i == 0 ? z[0] : i == 1 ? z[1] : z[2], g;
@@ -1076,6 +1077,29 @@ __device__ __forceinline__ void fit_wave(const FitArgs& a, int64_t wave_item, La
   if (CHI2) finish_chi2<G>(a, x, ls);
 }
 
+// Adds the wave's counters.
+__device__ __forceinline__ void put_stats(sblm_stats* stats, const LaneStats& st, int lane) {
+  // wave sums in 64 bits
+  unsigned long long v[11] = {st.solves,     st.iters,   st.capped,   st.fallback,
+                              st.deg4,       st.wave_iters, st.iters32, st.polished,
+                              st.retried,    st.unsettled, st.newton};
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1)
+#pragma unroll
+    for (int k = 0; k < 11; ++k) v[k] += __shfl_down(v[k], off, 64);
+  if (lane == 0 && v[0]) {
+    unsigned long long* dst[11] = {&stats->n_solves,    &stats->n_iter,
+                                   &stats->n_capped,    &stats->n_fallback,
+                                   &stats->n_degree4,   &stats->n_wave_iter,
+                                   &stats->n_iter_fp32, &stats->n_polished,
+                                   &stats->n_retried,   &stats->n_unsettled,
+                                   &stats->n_newton};
+#pragma unroll
+    for (int k = 0; k < 11; ++k)
+      if (v[k]) atomicAdd(dst[k], v[k]);
+  }
+}
+
 // PERSIST = 0: one-shot grid.  PERSIST = 1: persistent grid fed by a work
 // counter.  All forms are compiled for two waves per SIMD: left alone, the
 // mixed form takes 272 registers and runs one, where its dependent FP64
@@ -1135,25 +1159,138 @@ __global__ __launch_bounds__(256, 2) void fitness_kernel(
     fit_wave<MODE, CHI2, G>(a, wi, st);
   }
   if (a.stats) {
-    // wave sums in 64 bits
-    unsigned long long v[11] = {st.solves,     st.iters,   st.capped,   st.fallback,
-                                st.deg4,       st.wave_iters, st.iters32, st.polished,
-                                st.retried,    st.unsettled, st.newton};
+    put_stats(a.stats, st, lane);
+  }
+}
+
+// ---------------------------------------------------------------- single epochs
+
+// Sweeps of the simultaneous iteration before a pair's images are tried, and
+// passes of that try (see magnify_pairs_kernel).
+#define SBLM_PAIR_SWEEPS 1
+#define SBLM_PAIR_PASSES 6
+
+// A pair (individual, epoch) p = ind n_t + k: the source, the lens.
+__device__ __forceinline__ void pair_setup(const double* theta, const double* t, int64_t n_ind,
+                                           int64_t n_t, int64_t p, cx<double>& zeta, double& d,
+                                           double& q) {
+  const int64_t ind = n_t == 1 ? p : p / n_t;
+  const ItemTrig tr = item_trig(theta[ind], theta[3 * n_ind + ind], theta[4 * n_ind + ind]);
+  q = tr.q;
+  d = theta[n_ind + ind];
+  zeta = source_position(t[p - ind * n_t], theta[5 * n_ind + ind], tr.itE, tr.sa, tr.ca,
+                         theta[2 * n_ind + ind]);
+}
+
+// The cold solve of up to 64 pairs, one per lane, with the output.
+template <int MODE>
+__device__ __noinline__ void solve_pairs(const double* theta, const double* t, int64_t n_ind,
+                                         int64_t n_t, int64_t p, int active, double* A,
+                                         int8_t* n_img, LaneStats* cnt) {
+  cx<double> zeta;
+  double io[15], d, q;
+  pair_setup(theta, t, n_ind, n_t, p, zeta, d, q);
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1)
+  for (int i = 0; i < 10; ++i) io[i] = 0.0;
+  io[10] = zeta.re;
+  io[11] = zeta.im;
+  io[12] = d;
+  io[13] = q;
+  const int out = solve_epoch<MODE>(io, active ? SOLVE_ACTIVE : 0, cnt);
+  if (active) {
+    A[p] = io[14];
+    if (n_img) n_img[p] = (int8_t)(out >> 4);
+  }
+}
+
+// Magnifications of pairs that share no chain, `batches` times 64 of them per
+// wave; blocks of 256 threads.
+//   Bound by FP64 arithmetic in lockstep: a cold solve takes 2.7 sweeps, the
+// slowest of 64 lanes 7.6.  So a pair gets one sweep, and its three roots of
+// least residual go through the checks of a tracked epoch (track_images): over
+// the prior 6% fail, and are put aside until they fill a wave of their own.
+// (After two sweeps 3% fail, after four 0.4%, but of 64 lanes one in 85% and
+// 25% of the cases.)  At the end the block's waves share out what is left; one
+// residency of long-lived blocks, so that this, some 15 us of latency, comes
+// once: 2^20 single epochs 200 us in lockstep, 147 so (205, 187 and 162 us with
+// 2, 3 and 4 batches a wave instead of 8); two sweeps and 3 passes 148 us, one
+// and 4 162, one and 8 152.
+template <int MODE>
+__global__ __launch_bounds__(256, 2) void magnify_pairs_kernel(FitArgs a, int batches) {
+  // pairs of each wave still to be solved, and how many at the end
+  __shared__ int left[4][128], n_end[4];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t n = a.n_ind * a.n_t;
+  const int64_t p0 = ((int64_t)blockIdx.x * 4 + w) * batches * 64;
+  int n_left = 0;
+  unsigned int tracked = 0;
+  LaneStats slow = {};
+  for (int b = 0; b < batches && p0 + b * 64 < n; ++b) {
+    const int64_t p = p0 + b * 64 + lane;
+    const bool active = p < n;
+    cx<double> zeta, c[6], z[5];
+    double d, q;
+    pair_setup(a.theta, a.t, a.n_ind, a.n_t, active ? p : n - 1, zeta, d, q);
+    lens_coeffs(zeta, d, q, c);
+    cx<float> zf[5];
+    bool ok = active && q <= 2.0 && light_secondary_start(zeta, d, q, zf);
+    double A = 0.0;
+    int nimg = 3;
+    if (ok) {
 #pragma unroll
-      for (int k = 0; k < 11; ++k) v[k] += __shfl_down(v[k], off, 64);
-    if (lane == 0 && v[0]) {
-      unsigned long long* dst[11] = {&a.stats->n_solves,    &a.stats->n_iter,
-                                     &a.stats->n_capped,    &a.stats->n_fallback,
-                                     &a.stats->n_degree4,   &a.stats->n_wave_iter,
-                                     &a.stats->n_iter_fp32, &a.stats->n_polished,
-                                     &a.stats->n_retried,   &a.stats->n_unsettled,
-                                     &a.stats->n_newton};
+      for (int i = 0; i < 5; ++i) z[i] = {(double)zf[i].re, (double)zf[i].im};
+#pragma unroll 1
+      for (int k = 0; k < SBLM_PAIR_SWEEPS; ++k)
+        (void)aberth_sweep<false>(c, z, false, SBLM_ROOT_TAU, (double*)nullptr);
+      // the three roots of least residual
+      double r2[5];
 #pragma unroll
-      for (int k = 0; k < 11; ++k)
-        if (v[k]) atomicAdd(dst[k], v[k]);
+      for (int i = 0; i < 5; ++i) r2[i] = lens_residual2(z[i], zeta, d, q);
+      cx<double> zt[3] = {z[0], z[1], z[2]}, vt[3], z3, z4;
+#pragma unroll
+      for (int i = 0; i < 5; ++i) {
+        int rank = 0;
+#pragma unroll
+        for (int j = 0; j < 5; ++j)
+          rank += (r2[j] < r2[i] || (r2[j] == r2[i] && j < i)) ? 1 : 0;
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+          if (rank == k) zt[k] = z[i];
+      }
+      ok = track_images(zt, vt, zeta, {0.0, 0.0}, d, q, A, nimg, z3, z4, SBLM_PAIR_PASSES);
+      tracked += ok ? 1u : 0u;
     }
+    if (ok) {
+      a.A[p] = A;
+      if (a.n_img) a.n_img[p] = (int8_t)nimg;
+    }
+    // those left, in order; solved as soon as they fill a wave
+    const unsigned long long m = __ballot(active && !ok);
+    if (active && !ok)
+      left[w][n_left + __popcll(m & ((1ull << lane) - 1ull))] = b * 64 + lane;
+    n_left += __popcll(m);
+    if (n_left >= 64) {
+      n_left -= 64;
+      solve_pairs<MODE>(a.theta, a.t, a.n_ind, a.n_t, p0 + left[w][n_left + lane], 1, a.A,
+                        a.n_img, &slow);
+    }
+  }
+  // the rest of the block's, shared out anew
+  if (lane == 0) n_end[w] = n_left;
+  __syncthreads();
+  int j = 0, i = w * 64 + lane;
+  while (j < 4 && i >= n_end[j]) i -= n_end[j++];
+  if (__any(j < 4)) {
+    const int64_t p =
+        j < 4 ? ((int64_t)blockIdx.x * 4 + j) * batches * 64 + left[j][i] : n - 1;
+    solve_pairs<MODE>(a.theta, a.t, a.n_ind, a.n_t, p, j < 4 ? 1 : 0, a.A, a.n_img, &slow);
+  }
+  if (a.stats) {
+    slow.solves += tracked;
+    slow.newton += tracked;
+    slow.iters += tracked * SBLM_PAIR_SWEEPS;
+    slow.wave_iters += tracked * SBLM_PAIR_SWEEPS;
+    put_stats(a.stats, slow, lane);
   }
 }
 
@@ -1197,12 +1334,25 @@ static hipError_t launch_gg(const FitArgs& a, hipStream_t s, int wpb) {
   }
 }
 
+template <int MODE>
+static hipError_t launch_pairs(const FitArgs& a, hipStream_t s) {
+  const int64_t n = a.n_ind * a.n_t;
+  // as many blocks as the chip holds at once, each wave with as many pairs
+  const int64_t batches = (n + RESIDENT_LANES - 1) / RESIDENT_LANES;
+  if (batches > (1 << 24)) return hipErrorInvalidConfiguration;
+  const int64_t nblk = (n + batches * 256 - 1) / (batches * 256);
+  hipLaunchKernelGGL((magnify_pairs_kernel<MODE>), dim3((unsigned)nblk), dim3(256), 0, s, a,
+                     (int)batches);
+  return hipGetLastError();
+}
+
 template <int MODE, bool CHI2>
 static hipError_t launch_g(const FitArgs& a, hipStream_t s, int wpb) {
   if constexpr (CHI2) {
     if (a.lanes_per_ind == 256) return launch_gg<MODE, CHI2, 256>(a, s, wpb);
     if (a.lanes_per_ind == 128) return launch_gg<MODE, CHI2, 128>(a, s, wpb);
   } else {
+    if (a.lanes_per_ind == MAGNIFY_PAIRS) return launch_pairs<MODE>(a, s);
     if (a.lanes_per_ind > 64 && a.lanes_per_ind % 64 == 0)
       return launch_gg<MODE, CHI2, WIDE>(a, s, wpb);
   }

@@ -98,6 +98,10 @@ inline int default_lanes(int64_t n_ind) {
   return 64;
 }
 
+// In FitArgs::lanes_per_ind: magnifications with no chains of epochs, every pair
+// (individual, epoch) by itself.
+constexpr int MAGNIFY_PAIRS = 0;
+
 // Lanes per individual for the magnifications of n individuals at n_t shared
 // epochs, where no sum over the epochs ties the lanes together: the number of
 // lowest modelled time, the fewest among equals.  A lane's chain of C epochs
@@ -111,7 +115,12 @@ inline int default_lanes(int64_t n_ind) {
 // curve of 1000 epochs 18 (256), 11 (1024); 256 x 1000 46 (512), 41 (256);
 // 16384 x 256 470 (8), 345 (32); 4096 x 1000 238 (32), 229 (64); 10^5 x 4 135
 // (8), 85 (4); 16 x 5000 72 (256), 31 (8192); 65536 x 256 1191 (64), 980 (16).
+//   Few epochs (taken as spread out, as above) and enough pairs: no chains at
+// all (magnify_pairs_kernel).  In us by the rule below and so: 2^18 single
+// epochs 60 and 68, 2^19 109 and 95, 2^20 204 and 147; 2^20 x 2 335 and 215,
+// 2^19 x 4 339 and 232, 2^18 x 12 498 and 343, 2^20 x 16 2505 and 1562.
 inline int64_t magnify_lanes(int64_t n, int64_t n_t) {
+  if (n_t <= 16 && n * n_t >= 4 * RESIDENT_LANES) return MAGNIFY_PAIRS;
   const double w_solved = 1.0 + fmin(1.5, 12.0 / (double)n_t);
   int64_t best = 1;
   double best_cost = 0.0;

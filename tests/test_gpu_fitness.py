@@ -147,6 +147,41 @@ def test_magnify_chains_of_a_full_chip(hip, monkeypatch, n_t, tracked):
             assert ambiguous_count(zeta[i, k], theta[1, i], 10 ** theta[0, i]), (i, k)
 
 
+@pytest.mark.parametrize("n,n_t,heavy", [(524287, 1, False), (524288, 1, False), (600001, 1, True),
+                                         (190003, 3, False), (32768, 16, False)])
+def test_magnify_pairs(hip, n, n_t, heavy):
+    # launches of many pairs without chains (the first just below their range):
+    # the first and last pairs and some between are the oracle's, also where
+    # every solve is left for the end (q > 2) and in part-filled blocks
+    rng = np.random.default_rng(n)
+    theta = inputs.draw_theta(rng, n)
+    if heavy:
+        theta[0] = rng.uniform(0.31, 1.0, n)
+    theta[5] = -rng.uniform(-2, 2, n) * theta[4]
+    t = np.linspace(0.0, 30.0, n_t)
+    some = np.unique(np.concatenate([np.arange(400), n - 1 - np.arange(400),
+                                     rng.integers(0, n, 800)]))
+    for mode, floor in ((0, 1e-10), (1, 1e-6)):
+        st = hip.new_stats()
+        n_img = torch.zeros((n, n_t), dtype=torch.int8, device=DEV)
+        A = hip.sblm_magnify(_cuda(theta), _cuda(t), mode=mode, n_img=n_img, stats=st)
+        s = hip.stats_dict(st)
+        assert s["n_solves"] == n * n_t and s["n_unsettled"] == 0
+        assert not bool(torch.isnan(A).any()) and bool(((n_img == 3) | (n_img == 5)).all())
+        A, n_img = A.cpu().numpy()[some], n_img.cpu().numpy()[some]
+        th = theta[:, some]
+        Ao, no = O.magnify(th, t)
+        err = rel_err(A, Ao)
+        zeta = source_positions(th, t)
+        tau = (t[None, :] - th[5][:, None]) / th[4][:, None]
+        for i, k in np.argwhere(err > floor):
+            q, d = 10 ** th[0, i], th[1, i]
+            kappa = magnification_condition(zeta[i, k], d, q, tau[i, k], th[2, i])
+            assert err[i, k] <= max(floor, kappa), (i, k, err[i, k], kappa, A[i, k])
+        for i, k in np.argwhere(n_img != no):
+            assert ambiguous_count(zeta[i, k], th[1, i], 10 ** th[0, i]), (i, k)
+
+
 def test_magnify_cold_starts_on_symmetry_axes(hip):
     # sources on the lens axis and on the axis perpendicular to it (u0 = 0,
     # alpha a multiple of pi/2), single epochs, so that every solve starts
