@@ -83,8 +83,7 @@ typedef struct {
   unsigned long long n_fallback;   /* MIXED: solves whose FP32 roots were not
                                       polished to the FP64 tolerance by two
                                       Newton steps and went on to FP64
-                                      simultaneous-iteration sweeps, and warm
-                                      solves, which start with those          */
+                                      simultaneous-iteration sweeps           */
   unsigned long long n_degree4;    /* leading coefficient negligible          */
   unsigned long long n_degenerate; /* chi^2 fits with a singular 2x2 system   */
   unsigned long long n_wave_iter;  /* sweeps the wavefront executed, summed

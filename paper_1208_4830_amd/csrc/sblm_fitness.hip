@@ -263,15 +263,14 @@ __device__ __forceinline__ double magnification(const cx<double> z[5],
 // The tracked form of an epoch: the three images predicted in z, stepped
 // twice on the lens equation (a Newton step, then one that is judged), a lane's
 // images that are not final yet one per pass after that; their velocities v
-// for the source's vz; the other two roots in z3, z4.  True with A and the
+// for the source's vz; the other two roots from those.  True with A and the
 // image count when every check holds (see sblm_math.h): the images final and
 // apart, the other two roots clearly both images or clearly neither.
 //   Over the batched set 98.4% of the epochs end here (1.6% are the first of
 // a chain); in 95% of a wave's steps no lane is left for the iteration.
 __device__ __forceinline__ bool track_images(cx<double> z[3], cx<double> v[3], cx<double> zeta,
                                              cx<double> vz, double d, double q, double& A,
-                                             int& nimg, cx<double>& z3, cx<double>& z4,
-                                             int passes = SBLM_TRACK_PASSES) {
+                                             int& nimg, int passes = SBLM_TRACK_PASSES) {
   double ai[3];
   unsigned int todo = 0u;
 #pragma unroll
@@ -307,6 +306,7 @@ __device__ __forceinline__ bool track_images(cx<double> z[3], cx<double> v[3], c
   apart = vmin(c_norm(c_sub(z[0], z[2])), apart);
   apart = vmin(c_norm(c_sub(z[1], z[2])), apart);
   bool ok = todo == 0u && apart > SBLM_TRACK_APART2;
+  cx<double> z3, z4;
   ok = other_roots(zeta, d, q, z, z3, z4) && ok;
   const double r3 = lens_residual2(z3, zeta, d, q), r4 = lens_residual2(z4, zeta, d, q);
   const bool spurious = r3 > SBLM_TRACK_SPURIOUS2 && r4 > SBLM_TRACK_SPURIOUS2;
@@ -367,13 +367,12 @@ __device__ __forceinline__ void add_stats(LaneStats& a, const LaneStats& b) {
 // ok = converged to finite roots; settled = ok, or capped with finite roots
 // that no longer move (see SBLM_SETTLED_STEP2).  `retry` marks a second,
 // cold attempt at an epoch whose warm-started solve failed (not counted as
-// another solve); `direct` sends a warm MIXED solve straight to FP64 sweeps.
+// another solve).
 template <int MODE>
 __device__ __forceinline__ void solve_roots(const cx<double> c[6], cx<double> zeta, double d,
                                             double q, bool deg4, bool warm, bool active,
                                             cx<double> z[5], LaneStats& st,
-                                            bool& ok, bool& settled, bool retry = false,
-                                            bool direct = false) {
+                                            bool& ok, bool& settled, bool retry = false) {
   constexpr int MAXIT64 = 60, MAXIT32 = 30;
   // estimated relative error left after the last step
   const double tau64 = SBLM_ROOT_TAU;
@@ -388,15 +387,13 @@ __device__ __forceinline__ void solve_roots(const cx<double> c[6], cx<double> ze
     // and the fit in FP64.  A polish that has not converged after two steps
     // falls back to FP64 Aberth sweeps from the polished roots (counted).
     // A warm start (the previous epochs' roots, extrapolated) is already as
-    // close as FP32 can resolve and goes straight to the polish (or to FP64
-    // sweeps: a solve for what track_images did not settle has had its FP64
-    // steps there); degree-4 polynomials (parked root out of FP32 range) and
-    // those with a far root (its powers overflow FP32) straight to FP64 sweeps.
-    // The FP32 iteration ends at its own convergence test, or, after its first
-    // few sweeps (the global phase, where steps need not shrink), when its
-    // steps stop shrinking (the FP32 rounding floor next to clustered roots).
-    const bool use32 = !deg4 && !far && !(warm && direct);
-    fell_back = active && warm && direct;
+    // close as FP32 can resolve and goes straight to the polish; degree-4
+    // polynomials (parked root out of FP32 range) and those with a far root
+    // (its powers overflow FP32) straight to FP64 sweeps.  The FP32
+    // iteration ends at its own convergence test, or, after its first few
+    // sweeps (the global phase, where steps need not shrink), when its steps
+    // stop shrinking (the FP32 rounding floor next to clustered roots).
+    const bool use32 = !deg4 && !far;
     cx<float> cf[6];
 #pragma unroll
     for (int j = 0; j < 6; ++j) cf[j] = {(float)c[j].re, (float)c[j].im};
@@ -705,75 +702,50 @@ __device__ __forceinline__ void put_epoch(const FitArgs& a, const Item& x, int64
   }
 }
 
-// The solve of an epoch whose images cannot be tracked, by the whole wave when
-// any lane needs it (the others only follow along): the five roots by
-// simultaneous iteration from z (three predicted images and two other roots,
-// warm) or from a cold start, the retry of a warm solve that failed, the
-// images and, where an epoch follows, which of them are tracked.  With
-// SOLVE_RETRY the cold second attempt of a chain that is not tracked.  Out of
-// line: few steps come here, and inlined it costs the tracked form registers
-// (64 x 1000 x 256 FP64: 838 us inlined, 751 so).  Everything travels through
-// memory: io[0..9] the roots (in and out; SOLVE_NEXT: the images to track come
-// first), [10, 11] zeta, [12] d, [13] q, [14] A (out); flags in: SOLVE_ACTIVE,
-// _WARM, _NEXT, _RETRY, and _FOLLOW for a lane with an epoch that needs no
-// solve; flags out: SOLVE_OK, the image count from bit 4; cnt: the lane's
-// counters (added to).
+// The cold solve of an epoch whose images cannot be tracked, by the whole wave
+// when any lane needs it (the others only follow along): the five roots by
+// simultaneous iteration, the images and, where an epoch follows, which of
+// them are tracked.  With SOLVE_RETRY the second attempt of a chain that is not
+// tracked.  (A start from the images predicted and the two other roots they
+// give takes more sweeps where those were no images: in simplex rounds, whose
+// chains start from other parameters' images, 5.3 a solve against 2.3 cold, 18.8
+// ms against 17.6 for 64 x 1000 epochs and 300 steps.)  Out of line: few steps
+// come here, and inlined it costs the tracked form registers (64 x 1000 x 256
+// FP64: 838 us inlined, 751 so).  out[0..9] receives the roots (SOLVE_NEXT: the
+// images to track come first), out[10] A; flags in: SOLVE_ACTIVE, _NEXT, _RETRY,
+// and _FOLLOW for a lane with an epoch that needs no solve; flags out: SOLVE_OK,
+// the image count from bit 4; cnt: the lane's counters (added to).
 enum {
   SOLVE_ACTIVE = 1,
-  SOLVE_WARM = 2,
-  SOLVE_NEXT = 4,
-  SOLVE_FOLLOW = 8,
-  SOLVE_RETRY = 16,
+  SOLVE_NEXT = 2,
+  SOLVE_FOLLOW = 4,
+  SOLVE_RETRY = 8,
   SOLVE_OK = 1
 };
 template <int MODE>
-__device__ __noinline__ int solve_epoch(double* io, int flags, LaneStats* cnt) {
+__device__ __noinline__ int solve_epoch(double zeta_re, double zeta_im, double d, double q,
+                                        int flags, double* out, LaneStats* cnt) {
   const bool active = (flags & SOLVE_ACTIVE) != 0;
-  const cx<double> zeta = {io[10], io[11]};
-  const double d = io[12], q = io[13];
+  const cx<double> zeta = {zeta_re, zeta_im};
   cx<double> z[5], c[6];
-  bool fin = true;
 #pragma unroll
-  for (int i = 0; i < 5; ++i) {
-    z[i] = {io[2 * i], io[2 * i + 1]};
-    fin = fin && isfinite(z[i].re) && isfinite(z[i].im);
-  }
+  for (int i = 0; i < 5; ++i) z[i] = {0.0, 0.0};
   lens_coeffs(zeta, d, q, c);
   const bool deg4 = drop_to_degree4(c);
-  const bool warm = (flags & SOLVE_WARM) != 0 && !deg4 && fin;
   LaneStats st = {};
   bool ok, settled;
-  solve_roots<MODE>(c, zeta, d, q, deg4, warm, active, z, st, ok, settled,
-                    (flags & SOLVE_RETRY) != 0, true);
-  // a warm start that did not converge: solve again from the cold start;
-  // roots that still have not settled poison the result (A and with it chi^2
-  // become NaN, which ranks last)
-  const bool again = active && !ok && warm;
-  if (__any(again)) {
-    bool ok2, settled2;
-    LaneStats st2 = {};
-    solve_roots<MODE>(c, zeta, d, q, deg4, false, again, z, st2, ok2, settled2, true);
-    if (again) {
-      ok = ok2;
-      settled = settled2;
-      st.iters += st2.iters;
-      st.iters32 += st2.iters32;
-      st.newton += st2.newton;
-      st.fallback += st2.fallback;
-      st.retried += 1;
-      st.wave_iters += st2.wave_iters;
-    }
-  }
-  int out = 0;
+  solve_roots<MODE>(c, zeta, d, q, deg4, false, active, z, st, ok, settled,
+                    (flags & SOLVE_RETRY) != 0);
+  int r = 0;
   if (active) {
     int npol = 0, order[5], nimg;
     const bool next = (flags & SOLVE_NEXT) != 0;
     double A = magnification(z, zeta, d, q, deg4, nimg, npol, next, order);
-    if (!settled) {
+    if (!settled) {  // (A and with it chi^2 become NaN, which ranks last)
       A = NAN;
       nimg = 0;
     }
-    io[14] = A;
+    out[10] = A;
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
       cx<double> zk = z[k];
@@ -782,10 +754,10 @@ __device__ __noinline__ int solve_epoch(double* io, int flags, LaneStats* cnt) {
         for (int i = 0; i < 5; ++i)
           if (order[i] == k) zk = z[i];
       }
-      io[2 * k] = zk.re;
-      io[2 * k + 1] = zk.im;
+      out[2 * k] = zk.re;
+      out[2 * k + 1] = zk.im;
     }
-    out = (ok ? SOLVE_OK : 0) | (nimg << 4);
+    r = (ok ? SOLVE_OK : 0) | (nimg << 4);
     cnt->solves += st.solves;
     cnt->iters += st.iters;
     cnt->capped += ok ? 0 : 1;
@@ -793,12 +765,11 @@ __device__ __noinline__ int solve_epoch(double* io, int flags, LaneStats* cnt) {
     cnt->deg4 += st.deg4;
     cnt->iters32 += st.iters32;
     cnt->polished += npol;
-    cnt->retried += st.retried;
     cnt->unsettled += settled ? 0 : 1;
     cnt->newton += st.newton;
   }
   if (flags & (SOLVE_ACTIVE | SOLVE_FOLLOW)) cnt->wave_iters += st.wave_iters;
-  return out;
+  return r;
 }
 
 // Chains that are solved at every epoch, Cg of them in this lane and at most C
@@ -878,21 +849,14 @@ __device__ __forceinline__ void solve_chain(const FitArgs& a, const Item& x, int
     double A = 0.0;
     int nimg = 0;
     if (__any(again)) {
-      double io[15];
+      double io[11];
       LaneStats rs = {};
-#pragma unroll
-      for (int i = 0; i < 5; ++i) {
-        io[2 * i] = z[i].re;
-        io[2 * i + 1] = z[i].im;
-      }
-      io[10] = zeta.re;
-      io[11] = zeta.im;
-      io[12] = d;
-      io[13] = q;
-      const int out = solve_epoch<MODE>(
-          io, again ? SOLVE_ACTIVE | SOLVE_RETRY : active ? SOLVE_FOLLOW : 0, &rs);
+      const int out =
+          solve_epoch<MODE>(zeta.re, zeta.im, d, q,
+                            again ? SOLVE_ACTIVE | SOLVE_RETRY : active ? SOLVE_FOLLOW : 0, io,
+                            &rs);
       if (again) {
-        A = io[14];
+        A = io[10];
         nimg = out >> 4;
         ok = (out & SOLVE_OK) != 0;
 #pragma unroll
@@ -936,7 +900,7 @@ __device__ __forceinline__ void solve_chain(const FitArgs& a, const Item& x, int
 // the sweeps a wave takes in lockstep).  Solved at every epoch, 256 x 1000
 // epochs x 256 individuals took 4.23 ms FP64 over the prior and 3.23 ms for an
 // evolved population, tracked 2.43 and 2.05; 256 x 200-5000 x 128 5.03 and 3.07
-// ms; 64 x 1000 x 256 MIXED 1.58 and 1.02 ms.
+// ms; 64 x 1000 x 256 MIXED 1.58 and 0.83 ms.
 template <int MODE, bool CHI2, int G>
 __device__ __forceinline__ void track_chain(const FitArgs& a, const Item& x, int64_t Cg, int64_t C,
                                             LaneStats& st, Lsq& ls) {
@@ -978,14 +942,14 @@ __device__ __forceinline__ void track_chain(const FitArgs& a, const Item& x, int
     }
     // prediction of every image (track_weights); the history shifts as it is
     // used
-    cx<double> z[5];
     {
       double wd, w1, w2;
       track_weights(t, t1, t2, wd, w1, w2);
 #pragma unroll
       for (int i = 0; i < 3; ++i) {
-        z[i] = predict(zt[i], hist.get(0, i), vt[i], hist.get(1, i), wd, w1, w2);
-        hist.set(0, i, zt[i]);
+        const cx<double> z1 = zt[i];
+        zt[i] = predict(z1, hist.get(0, i), vt[i], hist.get(1, i), wd, w1, w2);
+        hist.set(0, i, z1);
         hist.set(1, i, vt[i]);
       }
     }
@@ -993,29 +957,17 @@ __device__ __forceinline__ void track_chain(const FitArgs& a, const Item& x, int
     int nimg = 3;
     bool ok = true, need = active;
     if (active && warm) {
-#pragma unroll
-      for (int i = 0; i < 3; ++i) zt[i] = z[i];
-      need = !track_images(zt, vt, zeta, vz, d, q, A, nimg, z[3], z[4]);
+      need = !track_images(zt, vt, zeta, vz, d, q, A, nimg);
       tracked += need ? 0u : 1u;
     }
     const bool any_need = __any(need);
     if (any_need) {
-      double io[15];
-      if (need && warm) (void)other_roots(zeta, d, q, z, z[3], z[4]);
-#pragma unroll
-      for (int i = 0; i < 5; ++i) {
-        io[2 * i] = z[i].re;
-        io[2 * i + 1] = z[i].im;
-      }
-      io[10] = zeta.re;
-      io[11] = zeta.im;
-      io[12] = d;
-      io[13] = q;
-      const int in = need ? SOLVE_ACTIVE | SOLVE_NEXT | (warm ? SOLVE_WARM : 0)
-                          : (active ? SOLVE_FOLLOW : 0);
-      const int out = solve_epoch<MODE>(io, in, &slow);
+      double io[11];
+      const int out = solve_epoch<MODE>(
+          zeta.re, zeta.im, d, q, need ? SOLVE_ACTIVE | SOLVE_NEXT : active ? SOLVE_FOLLOW : 0,
+          io, &slow);
       if (need) {
-        A = io[14];
+        A = io[10];
         nimg = out >> 4;
         ok = (out & SOLVE_OK) != 0;
 #pragma unroll
@@ -1188,17 +1140,12 @@ __device__ __noinline__ void solve_pairs(const double* theta, const double* t, i
                                          int64_t n_t, int64_t p, int active, double* A,
                                          int8_t* n_img, LaneStats* cnt) {
   cx<double> zeta;
-  double io[15], d, q;
+  double io[11], d, q;
   pair_setup(theta, t, n_ind, n_t, p, zeta, d, q);
-#pragma unroll
-  for (int i = 0; i < 10; ++i) io[i] = 0.0;
-  io[10] = zeta.re;
-  io[11] = zeta.im;
-  io[12] = d;
-  io[13] = q;
-  const int out = solve_epoch<MODE>(io, active ? SOLVE_ACTIVE : 0, cnt);
+  const int out =
+      solve_epoch<MODE>(zeta.re, zeta.im, d, q, active ? SOLVE_ACTIVE : 0, io, cnt);
   if (active) {
-    A[p] = io[14];
+    A[p] = io[10];
     if (n_img) n_img[p] = (int8_t)(out >> 4);
   }
 }
@@ -1246,7 +1193,7 @@ __global__ __launch_bounds__(256, 2) void magnify_pairs_kernel(FitArgs a, int ba
       double r2[5];
 #pragma unroll
       for (int i = 0; i < 5; ++i) r2[i] = lens_residual2(z[i], zeta, d, q);
-      cx<double> zt[3] = {z[0], z[1], z[2]}, vt[3], z3, z4;
+      cx<double> zt[3] = {z[0], z[1], z[2]}, vt[3];
 #pragma unroll
       for (int i = 0; i < 5; ++i) {
         int rank = 0;
@@ -1257,7 +1204,7 @@ __global__ __launch_bounds__(256, 2) void magnify_pairs_kernel(FitArgs a, int ba
         for (int k = 0; k < 3; ++k)
           if (rank == k) zt[k] = z[i];
       }
-      ok = track_images(zt, vt, zeta, {0.0, 0.0}, d, q, A, nimg, z3, z4, SBLM_PAIR_PASSES);
+      ok = track_images(zt, vt, zeta, {0.0, 0.0}, d, q, A, nimg, SBLM_PAIR_PASSES);
       tracked += ok ? 1u : 0u;
     }
     if (ok) {
