@@ -464,10 +464,10 @@ void nm_default_config(nm_config* cfg);
  * simplices run, else all four points of a step at once; either way the
  * simplices are those of the sequential method.
  * Allocates and frees a workspace of ~1 KB per simplex, a work order of
- * 32 B per simplex, and saved images of 48 B per lane: the trial points of a
+ * 32 B per simplex, and saved roots of 80 B per lane: the trial points of a
  * round are spread over 64, 128 or 256 lanes each, the fewest that give
- * 2^19 lanes for the round's trial points (read every 16 rounds), each
- * width with its own saved images (84 KB per simplex for the three; where
+ * 2^18 lanes for the round's trial points (read every 16 rounds), each
+ * width with its own saved roots (140 KB per simplex for the three; where
  * they would pass 1 GiB, one width: 256 lanes, else 128, else 64 without
  * saved roots).  The widths and the form of a round change results at the
  * rounding level only, and are a function of the simplices, so calls are

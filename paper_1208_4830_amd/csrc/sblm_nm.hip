@@ -882,9 +882,11 @@ int nm_run(const sblm_lcs& lcs, int32_t reps, const double* lo, const double* sp
   // their longest lightcurve, which 128 or 256 lanes (several waves per
   // trial point) shorten.  So the lanes follow the number of simplices that
   // ran in the last round (read every 16 rounds): the fewest of 64, 128, 256
-  // that give the round's trial points 2^19 lanes, else 256.  Every width
-  // keeps three images of each lane's first epoch (48 B per lane and trial
-  // slot) and starts there in its next round (the simplex moves little
+  // that give the round's trial points 2^18 lanes (a run of 60 steps of 2048
+  // simplices on 300 epochs 22.4 ms at 2^19, 16.2 so; 40 of 4096 on 1000 epochs
+  // 27.9 and 25.1; 60 of 1024 on 1000 16.0 and 16.1, at 2^17 16.8), else 256.
+  // Every width keeps the roots of each lane's first epoch (80 B per lane and
+  // trial slot) and starts there in its next round (the simplex moves little
   // between rounds; a cache of a width not used for a while is only a
   // poorer start).  The choice depends on the simplices alone, so results
   // are deterministic.  Without room for the three caches (1 GiB) a fixed
@@ -1011,7 +1013,7 @@ int nm_run(const sblm_lcs& lcs, int32_t reps, const double* lo, const double* sp
     w.spec = (int64_t)active <= spec_max ? 1 : 0;
     if (!fixed_g) {
       // trial points of a round: four per simplex, or about one
-      const int64_t want = (int64_t)1 << 19;
+      const int64_t want = (int64_t)1 << 18;
       const int64_t tp = (int64_t)active * (w.spec ? NS : 1);
       set_lanes(tp * 64 >= want ? 64 : tp * 128 >= want ? 128 : 256);
     }
