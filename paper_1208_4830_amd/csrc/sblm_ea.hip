@@ -1213,10 +1213,20 @@ extern "C" int ea_fit(ea_state* st, int32_t n_gen, sblm_stats* stats, void* stre
   int rc;
   if (!s.graph || s.graph_stats != stats)
     if ((rc = capture_graph(s, stats))) return rc;
-  if (!s.graph_n && (n_gen == 0 || n_gen >= 4 * GRAPH_GENS))
-    if ((rc = capture_generations(s, stats, GRAPH_GENS, &s.graph_n))) return rc;
-  if (n_gen == 0) return SBLM_OK;
   hipStream_t caller = (hipStream_t)stream;
+  if (!s.graph_n && (n_gen == 0 || n_gen >= 4 * GRAPH_GENS)) {
+    // (not inside a capture of the caller's: its one-generation launches are
+    // recorded there as ever)
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(caller, &cap) != hipSuccess) {
+      (void)hipGetLastError();
+      cap = hipStreamCaptureStatusActive;
+    }
+    if (cap == hipStreamCaptureStatusNone &&
+        (rc = capture_generations(s, stats, GRAPH_GENS, &s.graph_n)))
+      return rc;
+  }
+  if (n_gen == 0) return SBLM_OK;
   if ((rc = check_hip(hipEventRecord(s.ev_in, caller), "ea_fit event")) ||
       (rc = check_hip(hipStreamWaitEvent(s.work, s.ev_in, 0), "ea_fit wait")))
     return rc;

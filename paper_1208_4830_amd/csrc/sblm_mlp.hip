@@ -1495,6 +1495,7 @@ extern "C" int mlp_train(mlp_net* n, const uint16_t* x, const float* y, int64_t 
       n->sched = nullptr;
       n->losses = nullptr;
       n->sched_cap = 0;
+      n->train_key[0] = 0;  // (also where the new buffers take the old addresses)
       if (hipMalloc(&n->sched, (size_t)total * 3 * sizeof(float)) != hipSuccess ||
           hipMalloc(&n->losses, (size_t)total * sizeof(float)) != hipSuccess) {
         (void)hipGetLastError();
