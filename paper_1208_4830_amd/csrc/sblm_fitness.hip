@@ -896,7 +896,7 @@ __device__ __forceinline__ void solve_chain(const FitArgs& a, const Item& x, int
 // before and tracked (track_images); the lanes that fail a check solve for all
 // five roots (solve_epoch), which a wave goes through when any of its lanes
 // does.
-//   Bound by FP64 arithmetic (893 FLOPs per tracked epoch, 1920 of a solve with
+//   Bound by FP64 arithmetic (899 FLOPs per tracked epoch, 1920 of a solve with
 // the sweeps a wave takes in lockstep).  Solved at every epoch, 256 x 1000
 // epochs x 256 individuals took 4.23 ms FP64 over the prior and 3.23 ms for an
 // evolved population, tracked 2.43 and 2.05; 256 x 200-5000 x 128 5.03 and 3.07

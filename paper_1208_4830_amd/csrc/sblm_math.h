@@ -362,9 +362,9 @@ SBLM_FN R refine_image(cx<R> zi, cx<R> zeta, R d, R q) {
 // in closed form, from the sum and the product of all five, and with them
 // the image count: no simultaneous iteration.  Any three distinct solutions of
 // the lens equation will do -- they are roots of the polynomial -- so a step
-// only has to show that it has arrived at one; where it cannot (next to a
-// caustic, after a long gap, a source on a lens) the five roots are solved
-// for.
+// only has to show that it has arrived at one (image_close, whose two bounds
+// together prove it); where it cannot (next to a caustic, after a long gap, a
+// source on a lens) the five roots are solved for.
 
 // Square root to about 1 ulp from the hardware estimate of 1/sqrt(x) (x > 0).
 template <typename R>
@@ -378,6 +378,7 @@ SBLM_FN R sqrt_acc(R x) {
 }
 
 #define SBLM_TRACK_EST 1e-12 /* relative error of an image's A after its last step */
+#define SBLM_TRACK_STEP 1e-2 /* that step against the distance to a lens at most */
 #define SBLM_TRACK_SPURIOUS2 1e-8 /* |residual|^2 above which a root is no image */
 #define SBLM_TRACK_IMAGE2 1e-16   /* ... and below which it is one */
 #define SBLM_TRACK_APART2 1e-10   /* |z_i - z_j|^2 of two images at least */
@@ -432,11 +433,19 @@ SBLM_FN void image_newton(cx<R>& z, cx<R> zeta, R d, R q) {
 
 // A Newton step that is meant to be the last: *g is g after it to first order
 // in dz, g + h conj(dz) with h = dg/dconj(z) = 2 q b^3 - 2 a^3, *inv the
-// reciprocal of det J = 1 - |g|^2.  Returns whether A_i = |1/det J| is final:
-// what is neglected (|dz|^2 dg''/2 in g, and the position's remaining error K
-// |dz|^2, K = |h| (1 + |g|)/(2 |det|)) moves it by at most SBLM_TRACK_EST
-// relative.  (|g| <= (1 + |g|^2)/2 keeps square roots out of the bound; false
-// for NaN.)
+// reciprocal of det J = 1 - |g|^2.  Returns whether z is an image and A_i =
+// |1/det J| final:
+//   - the step is at most SBLM_TRACK_STEP of the distance to either lens, so
+//     that over all of it g's derivatives are those at its start to a few
+//     percent.  Without this the next bound says nothing: a step taken at
+//     |det J| = 0 throws z far out, where g = 0 and the step after it, z -> zeta,
+//     passes it with no image there;
+//   - what is neglected (|dz|^2 dg''/2 in g, and the position's remaining error
+//     K |dz|^2, K = |h| (1 + |g|)/(2 |det|)) moves A_i by at most SBLM_TRACK_EST
+//     relative.  K |dz| is then below 1e-6, so (Newton-Kantorovich) there is one
+//     solution of the lens equation within two steps of the start, and z is
+//     K |dz|^2 from it.
+// (|g| <= (1 + |g|^2)/2 keeps square roots out of the bound; false for NaN.)
 template <typename R>
 SBLM_FN bool image_close(cx<R>& z, cx<R> zeta, R d, R q, cx<R>* g, R* inv) {
   const LensAt<R> e = lens_at<true>(z, zeta, d, q);
@@ -452,9 +461,11 @@ SBLM_FN bool image_close(cx<R>& z, cx<R> zeta, R d, R q, cx<R>* g, R* inv) {
   *inv = rcp_acc(R(1.0) - c_norm(*g));
   z = {z.re + dz.re, z.im + dz.im};
   const R dn = c_norm(dz), hn = c_norm(hh);
-  return (R(1.0) + gn) * dn *
-             fma(R(3.0) * fma(e.iz, e.iz, q * e.ie * e.ie), fabs(det), hn * (R(3.0) + gn)) <=
-         R(SBLM_TRACK_EST) * (det * det);
+  const bool small = (R(1.0) + gn) * dn *
+                         fma(R(3.0) * fma(e.iz, e.iz, q * e.ie * e.ie), fabs(det),
+                             hn * (R(3.0) + gn)) <=
+                     R(SBLM_TRACK_EST) * (det * det);
+  return dn * (e.iz + e.ie) <= R(SBLM_TRACK_STEP * SBLM_TRACK_STEP) && small;
 }
 
 // The other two roots (z3, z4) of the lens polynomial from three of them, by
@@ -624,7 +635,7 @@ SBLM_FN void image_history(cx<R> z, cx<R> zeta, cx<R> vz, R d, R q, R h, cx<R>& 
 // (s + 2h) z^(3)/6 for the parabola through three positions; it carries
 // across a gap in the cadence (a night between two runs of epochs minutes
 // apart) up to a thousand spacings, where rounding (about 2 (s/h)^3 ulp) takes
-// over.  A poor start costs steps, never a wrong image.
+// over.  A poor start costs steps: what image_close accepts is an image.
 template <typename R>
 SBLM_FN void track_weights(R t, R t1, R t2, R& wd, R& w1, R& w2) {
   const R s = t - t1, h = t1 - t2;

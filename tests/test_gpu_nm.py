@@ -347,3 +347,64 @@ def test_work_order_packing_beyond_one_block(hip, monkeypatch):
                                       cfg.tol_x, cfg.tol_f, cfg.max_iter)
     assert big[4][j] == steps
     assert np.array_equal(big[0][:, j], xr)
+
+
+@pytest.mark.parametrize("lanes", ["64", "128", "256"])
+def test_tracked_simplex_matches_oracle(hip, lanes, monkeypatch):
+    # lightcurves long enough for chains along which images are tracked, whose
+    # first epochs start (128 and 256 lanes) from another trial point's images:
+    # the simplices are the oracle's
+    monkeypatch.setenv("SBLM_NM_LANES", lanes)
+    lengths = [2000, 330, 1300, 1100]
+    wl = inputs.uniform_workload(48, len(lengths), 2000)
+    ts, off = [], [0]
+    for k, L in enumerate(lengths):
+        ts.append(wl.t[k * 2000:(k + 1) * 2000][np.linspace(0, 1999, L).astype(int)])
+        off.append(off[-1] + L)
+    wl.t, wl.off = np.concatenate(ts), np.array(off, np.int64)
+    wl.sfrac, wl.noise = wl.sfrac[:wl.t.size], wl.noise[:wl.t.size]
+    y, w = oracle_lightcurves(wl)
+    lcs = device_lcs(hip, wl, y, w)
+    rng = np.random.default_rng(15)
+    x0 = np.clip((wl.theta - LO[:, None]) / (HI - LO)[:, None]
+                 + rng.normal(scale=0.03, size=wl.theta.shape), 0, 1)
+    cfg = hip.nm_default_config()
+    cfg.max_iter = 150
+    st = hip.new_stats()
+    x, c, fs, fb, it = (a.cpu().numpy() for a in
+                        hip.nm_refine(lcs, LO, HI, torch.tensor(x0, device="cuda"), cfg,
+                                      stats=st))
+    s = hip.stats_dict(st)
+    assert s["n_newton"] > 0.5 * s["n_solves"] and s["n_unsettled"] == 0, s
+    for k in range(len(lengths)):
+        sl = slice(off[k], off[k + 1])
+        xr, fr, steps, _, _ = _oracle_minimise(("tracked", k), oracle_f(wl.t[sl], y[sl], w[sl]),
+                                               x0[:, k], cfg)
+        assert it[k] == steps, (k, it[k], steps)
+        assert np.array_equal(x[:, k], xr), (k, x[:, k] - xr)
+        assert abs(c[k] - fr) <= 1e-8 * fr
+
+
+def test_tracked_simplices_return_their_points_values(hip):
+    # 64 simplices x 1000 epochs x 300 steps, a start now and then far from the
+    # data: the chi^2 of every returned point is the oracle's, and sampled
+    # simplices are its simplices
+    wl = inputs.uniform_workload(49, 64, 1000)
+    y, w = oracle_lightcurves(wl)
+    lcs = device_lcs(hip, wl, y, w)
+    rng = np.random.default_rng(16)
+    x0 = np.clip((wl.theta - LO[:, None]) / (HI - LO)[:, None]
+                 + rng.normal(scale=0.03, size=wl.theta.shape), 0, 1)
+    x0[:, ::9] = rng.uniform(0.05, 0.95, x0[:, ::9].shape)
+    cfg = hip.nm_default_config()
+    cfg.max_iter = 300
+    x, c, fs, fb, it = (a.cpu().numpy() for a in
+                        hip.nm_refine(lcs, LO, HI, torch.tensor(x0, device="cuda"), cfg))
+    cr, fsr, fbr = O.chi2(wl.off, wl.t, y, w, O.decode(x, LO, HI), 1)
+    assert np.all(np.abs(c - cr) <= 1e-8 * cr), np.abs(c / cr - 1).max()
+    for k in (7, 30, 52):
+        sl = slice(wl.off[k], wl.off[k + 1])
+        xr, fr, steps, _, _ = NM.minimise(oracle_f(wl.t[sl], y[sl], w[sl]), x0[:, k],
+                                          cfg.tol_x, cfg.tol_f, cfg.max_iter)
+        assert it[k] == steps, (k, it[k], steps)
+        assert np.array_equal(x[:, k], xr), k
