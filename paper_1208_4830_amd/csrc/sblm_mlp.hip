@@ -388,6 +388,10 @@ struct RowArgs {
 constexpr int RB = 32;                       // rows of a block
 constexpr int SX = NB + 8, SH = NH + 8, SD = NOP + 8, SO = NOP + 4;  // padded LDS rows
 constexpr int PF = 8;                        // fragments in flight
+constexpr int ROW_THREADS = 1024;            // threads of a block
+// Rows of a launch at most (2^31 threads; a grid must stay below 2^32).
+constexpr int64_t ROWS_MAX = (int64_t)1 << 26;
+static_assert(ROWS_MAX % RB == 0 && ROWS_MAX / RB * ROW_THREADS < (int64_t)1 << 32, "grid");
 
 __device__ __forceinline__ void frag_load(uint4* pre, const uint4* __restrict__ f) {
 #pragma unroll
@@ -422,7 +426,7 @@ __device__ __forceinline__ void store_t(uint16_t* T, int64_t ldt, int n, int64_t
 }
 
 template <bool TRAIN>
-__global__ __launch_bounds__(1024) void net_rows_kernel(RowArgs a) {
+__global__ __launch_bounds__(ROW_THREADS) void net_rows_kernel(RowArgs a) {
   __shared__ __attribute__((aligned(16))) uint16_t sX[RB * SX], sH1[RB * SH], sH2[RB * SH];
   __shared__ __attribute__((aligned(16))) float sO[TRAIN ? RB * SO : 4];
   __shared__ __attribute__((aligned(16))) uint16_t sD[TRAIN ? RB * SD : 8];
@@ -1264,9 +1268,9 @@ static hipError_t launch_rows(mlp_net* n, RowArgs& a, bool train, hipStream_t st
   a.p = n->p;
   const dim3 grid((unsigned)((a.rows + RB - 1) / RB));
   if (train)
-    hipLaunchKernelGGL((net_rows_kernel<true>), grid, dim3(1024), 0, st, a);
+    hipLaunchKernelGGL((net_rows_kernel<true>), grid, dim3(ROW_THREADS), 0, st, a);
   else
-    hipLaunchKernelGGL((net_rows_kernel<false>), grid, dim3(1024), 0, st, a);
+    hipLaunchKernelGGL((net_rows_kernel<false>), grid, dim3(ROW_THREADS), 0, st, a);
   return hipGetLastError();
 }
 
@@ -1279,10 +1283,10 @@ extern "C" int mlp_forward(mlp_net* n, const uint16_t* x, int64_t rows, float* o
   hipStream_t st = (hipStream_t)stream;
   RowArgs a;
   memset(&a, 0, sizeof(a));
-  // the kernel reads the caller's rows in 16-byte pieces: all of them in one
-  // launch where their address allows it, else chunks of batch_max from a copy
+  // the kernel reads the caller's rows in 16-byte pieces: as many as a launch
+  // takes where their address allows it, else chunks of batch_max from a copy
   const bool aligned = ((uintptr_t)x & 15) == 0;
-  const int64_t chunk = aligned ? (int64_t)1 << 30 : n->batch_max;
+  const int64_t chunk = aligned ? ROWS_MAX : n->batch_max;
   for (int64_t r0 = 0; r0 < rows; r0 += chunk) {
     a.rows = std::min<int64_t>(chunk, rows - r0);
     a.x = x + r0 * NB;

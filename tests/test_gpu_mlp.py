@@ -553,3 +553,27 @@ def test_trained_network_improves_the_ea(hip):
     assert success["learned"] >= success["plain"] + 0.05
     assert success["learned"] >= success["window"] + 0.03
     net.close()
+
+
+def test_forward_of_more_rows_than_a_grid_holds(hip):
+    # 2^27 rows and a few (64 GiB in, 64 GiB out): 32 threads a row would pass the
+    # 2^32 threads of a grid, so the rows go in several launches.  Groups of rows at
+    # the ends and around the launches' bounds are those of calls of their own
+    rows = (1 << 27) + 33
+    if torch.cuda.mem_get_info()[0] < 160 << 30:
+        pytest.skip("needs 160 GiB of free GPU memory")
+    net = hip.MLP(batch_max=64, seed=6)
+    x = torch.zeros((rows, 256), dtype=torch.bfloat16, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(3)
+    some = [slice(0, 65), slice((1 << 26) - 40, (1 << 26) + 40), slice(rows - 70, rows)]
+    for s in some:
+        x[s] = torch.randn(x[s].shape, generator=g, device="cuda").to(torch.bfloat16)
+    out = net.forward(x)
+    for s in some:
+        assert torch.equal(out[s], net.forward(x[s].clone())), s
+    zero = net.forward(x[100:101].clone())
+    for r0 in range(1 << 20, rows - (1 << 20), (1 << 25) - 12345):
+        assert torch.equal(out[r0:r0 + 1000], zero.expand(1000, -1)), r0
+    net.close()
+    del x, out
+    torch.cuda.empty_cache()
