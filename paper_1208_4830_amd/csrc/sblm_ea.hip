@@ -218,6 +218,9 @@ __global__ void ea_seed_kernel(EaParams p, double* P, const EaLc* lcs, Proposals
   seed_row(p, P, pr, lc, (int)(idx % pr.n_seed), lcs[lc].gen);
 }
 
+// The largest population.
+#define EA_POP_MAX 1024
+
 // Populations up to this size are ranked by counting, larger ones sorted.
 #define EA_COUNT_RANK 256
 
@@ -624,7 +627,7 @@ static size_t gen_smem(int pop) {
 
 // Threads of a generation's block: one per (offspring, two genes) task up to
 // 256, where several blocks share a compute unit; 512 and 1024 for the
-// populations whose LDS (45 KB at 512, 90 KB at 1024) leaves room for two
+// populations whose LDS (44 KB at 512, 88 KB at 1024) leaves room for three
 // blocks or one.
 static int gen_block(int pop) {
   int b = 64;
@@ -734,8 +737,8 @@ extern "C" void ea_default_config(ea_config* c) {
 }
 
 static int validate(const ea_config* c) {
-  if (c->pop < 2 || c->pop > 1024)
-    return set_error(SBLM_ERANGE, "ea_config: pop = %d outside [2, 1024]", c->pop);
+  if (c->pop < 2 || c->pop > EA_POP_MAX)
+    return set_error(SBLM_ERANGE, "ea_config: pop = %d outside [2, %d]", c->pop, EA_POP_MAX);
   if (c->n_tourn < 0 || c->n_tourn > c->pop)
     return set_error(SBLM_EINVAL, "ea_config: n_tourn = %d", c->n_tourn);
   if (!(c->p_mut0 >= 0.0 && c->p_mut0 <= 1.0) || !(c->p_mut_min >= 0.0) ||
@@ -838,15 +841,15 @@ extern "C" int ea_create(const ea_config* cfg, const sblm_lcs* lcs, uint64_t see
   // the four waves of a block on the one-shot grid.
   s.lanes = default_lanes(p.n_ind);
   if (s.lanes > 64) s.persistent = 0;
-  if (gen_smem(p.pop) > (64u << 10)) {
-    rc = check_hip(hipFuncSetAttribute((const void*)ea_generation_kernel,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)gen_smem(p.pop)),
-                   "ea_create: LDS");
-    if (rc) {
-      ea_destroy(st);
-      return rc;
-    }
+  // (the limit belongs to the kernel, which all states share: always the same,
+  // that of the largest population)
+  rc = check_hip(hipFuncSetAttribute((const void*)ea_generation_kernel,
+                                     hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     (int)gen_smem(EA_POP_MAX)),
+                 "ea_create: LDS");
+  if (rc) {
+    ea_destroy(st);
+    return rc;
   }
   const size_t nb = (size_t)p.n_ind * sizeof(double);
   // longest-processing-time order of the work items: lightcurves by length,

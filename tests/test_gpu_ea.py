@@ -463,3 +463,34 @@ def test_fitness_timer_leaves_the_fit_unchanged(hip):
     assert hip.stats_dict(stats)["n_solves"] > 0
     st_a.close()
     st_b.close()
+
+
+def test_states_of_several_population_sizes(hip):
+    # states whose generation kernels take more than the default 64 KB of LDS
+    # (1000 rows: 86 KB, 750: 68) beside each other and one that does not: a state
+    # created later changes nothing for the ones before, called or replayed
+    wl = csr_workload(12, [2, 2])
+    rng = np.random.default_rng(31)
+    pops = (1000, 750, 48)
+    states = [_make_state(hip, wl, pop, seed=41)[0] for pop in pops]
+    eas = [_oracle_eas(2, pop, 41) for pop in pops]
+    for _ in range(2):
+        for pop, st, ea in zip(pops, states, eas):
+            chi2 = rng.uniform(10, 1000, 2 * pop)
+            Fs, Fb = rng.uniform(0.5, 1.5, 2 * pop), rng.uniform(0, 0.5, 2 * pop)
+            st.generation(_cuda(chi2), _cuda(Fs), _cuda(Fb))
+            for lc, e in enumerate(ea):
+                sl = slice(lc * pop, (lc + 1) * pop)
+                e.generation(chi2[sl], Fs[sl], Fb[sl])
+            _compare(hip, st, ea, pop)
+    alone = _make_state(hip, wl, 1000, seed=43)[0]
+    alone.fit(5)
+    want = alone.save()
+    first = _make_state(hip, wl, 1000, seed=43)[0]
+    first.fit(2)
+    second = _make_state(hip, wl, 750, seed=44)[0]
+    second.fit(2)
+    first.fit(3)
+    assert first.save() == want
+    for st in states + [alone, first, second]:
+        st.close()
