@@ -1211,10 +1211,13 @@ __global__ __launch_bounds__(256, 2) void magnify_pairs_kernel(FitArgs a, int ba
       a.A[p] = A;
       if (a.n_img) a.n_img[p] = (int8_t)nimg;
     }
-    // those left, in order; solved as soon as they fill a wave
+    // those left, in order; solved as soon as they fill a wave (by other lanes:
+    // a fence between their reads and the writes on either side)
     const unsigned long long m = __ballot(active && !ok);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     if (active && !ok)
       left[w][n_left + __popcll(m & ((1ull << lane) - 1ull))] = b * 64 + lane;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     n_left += __popcll(m);
     if (n_left >= 64) {
       n_left -= 64;

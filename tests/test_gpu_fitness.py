@@ -350,3 +350,38 @@ def test_chi2_full_size_sampled(hip, mode):
         Ao, _ = O.magnify(th[:, i:i + 1], wl.t[sl])
         co, _, _ = O.lsq_chi2(Ao[0], y[sl], w[sl])
         assert rel_err(c[i], co) < 1e-8, (i, c[i], co)
+
+
+@pytest.mark.parametrize("n,n_t,planet", [(1 << 20, 1, False), (1 << 20, 1, True),
+                                          (100003, 7, False)])
+def test_magnify_pairs_all_of_a_launch(hip, monkeypatch, n, n_t, planet):
+    # every pair of a launch, those put aside and solved by other lanes among them,
+    # against the same pairs solved one by one along chains.  Image counts differ
+    # at most next to a caustic, where the oracle calls them ambiguous, and values
+    # beyond 1e-9 only where rounding alone can move them so far
+    rng = np.random.default_rng(n + n_t)
+    theta = inputs.draw_theta(rng, n)
+    if planet:
+        theta[0] = rng.uniform(-3.0, -2.0, n)
+        theta[2] *= 0.1
+    theta[5] = -rng.uniform(-2, 2, n) * theta[4]
+    t = np.linspace(0.0, 30.0, n_t)
+    th, td = _cuda(theta), _cuda(t)
+    n_img = torch.zeros((n, n_t), dtype=torch.int8, device=DEV)
+    n_one = torch.zeros_like(n_img)
+    A = hip.sblm_magnify(th, td, n_img=n_img)
+    monkeypatch.setenv("SBLM_LANES", "1")
+    B = hip.sblm_magnify(th, td, n_img=n_one)
+    err = ((A - B) / B).abs()
+    assert not bool(torch.isnan(err).any())
+    off = torch.nonzero((err > 1e-9) | (n_img != n_one)).cpu().numpy()
+    assert len(off) < 1e-3 * n * n_t, len(off)
+    zeta = source_positions(theta, t)
+    for i, k in off:
+        q, d = 10 ** theta[0, i], theta[1, i]
+        if int(n_img[i, k]) != int(n_one[i, k]):
+            assert ambiguous_count(zeta[i, k], d, q), (i, k)
+            continue
+        tau = (t[k] - theta[5, i]) / theta[4, i]
+        kappa = magnification_condition(zeta[i, k], d, q, tau, theta[2, i])
+        assert float(err[i, k]) <= 2 * max(1e-9, kappa), (i, k, float(err[i, k]), kappa)
