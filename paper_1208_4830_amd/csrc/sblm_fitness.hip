@@ -1170,7 +1170,7 @@ __global__ __launch_bounds__(256, 2) void magnify_pairs_kernel(FitArgs a, int ba
   const int64_t n = a.n_ind * a.n_t;
   const int64_t p0 = ((int64_t)blockIdx.x * 4 + w) * batches * 64;
   int n_left = 0;
-  unsigned int tracked = 0;
+  unsigned int tracked = 0, tried = 0;
   LaneStats slow = {};
   for (int b = 0; b < batches && p0 + b * 64 < n; ++b) {
     const int64_t p = p0 + b * 64 + lane;
@@ -1184,6 +1184,7 @@ __global__ __launch_bounds__(256, 2) void magnify_pairs_kernel(FitArgs a, int ba
     double A = 0.0;
     int nimg = 3;
     if (ok) {
+      ++tried;
 #pragma unroll
       for (int i = 0; i < 5; ++i) z[i] = {(double)zf[i].re, (double)zf[i].im};
 #pragma unroll 1
@@ -1238,8 +1239,8 @@ __global__ __launch_bounds__(256, 2) void magnify_pairs_kernel(FitArgs a, int ba
   if (a.stats) {
     slow.solves += tracked;
     slow.newton += tracked;
-    slow.iters += tracked * SBLM_PAIR_SWEEPS;
-    slow.wave_iters += tracked * SBLM_PAIR_SWEEPS;
+    slow.iters += tried * SBLM_PAIR_SWEEPS;
+    slow.wave_iters += tried * SBLM_PAIR_SWEEPS;
     put_stats(a.stats, slow, lane);
   }
 }

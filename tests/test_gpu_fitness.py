@@ -385,3 +385,28 @@ def test_magnify_pairs_all_of_a_launch(hip, monkeypatch, n, n_t, planet):
         tau = (t[k] - theta[5, i]) / theta[4, i]
         kappa = magnification_condition(zeta[i, k], d, q, tau, theta[2, i])
         assert float(err[i, k]) <= 2 * max(1e-9, kappa), (i, k, float(err[i, k]), kappa)
+
+
+@pytest.mark.parametrize("on_caustic", [True, False])
+def test_magnify_pairs_counts_every_sweep(hip, on_caustic):
+    # n copies of one pair, so that the counts are n times a pair's: a source on a
+    # caustic, whose images no lane can follow, costs the first sweep and then the
+    # whole solve; an ordinary one the first sweep alone
+    q, d = 0.1, 1.1
+    z = 1.6 + 0.4j
+    if on_caustic:  # 1/zb^2 + q/(d - zb)^2 = exp(i)
+        e = np.exp(1j)
+        zb = np.roots([e, -2 * d * e, d * d * e - 1 - q, 2 * d, -d * d])[0]
+        z = np.conj(zb)
+    zeta = z - 1 / np.conj(z) + q / (d - np.conj(z))
+    one = np.array([[np.log10(q)], [d], [abs(zeta)], [np.angle(zeta) % (2 * np.pi)], [30.0], [0.0]])
+    st = hip.new_stats()
+    hip.sblm_magnify(_cuda(one), _cuda(np.zeros(1)), stats=st)
+    alone = hip.stats_dict(st)
+    n = 1 << 19
+    st = hip.new_stats()
+    hip.sblm_magnify(_cuda(np.repeat(one, n, axis=1)), _cuda(np.zeros(1)), stats=st)
+    s = hip.stats_dict(st)
+    assert s["n_solves"] == n and alone["n_solves"] == 1 and alone["n_iter"] > 1
+    assert s["n_newton"] == (0 if on_caustic else n)
+    assert s["n_iter"] == (n * (1 + alone["n_iter"]) if on_caustic else n)
