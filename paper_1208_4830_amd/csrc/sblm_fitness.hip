@@ -1015,13 +1015,14 @@ __device__ __forceinline__ int64_t wave_longest(int64_t c) {
 
 // One wave's share of the work: 64/G individuals (items wave_item*64/G ...);
 // every lane takes its s-th epoch at the same time.  Where a wave holds chains
-// of both kinds (tracked_chains) it goes through both loops.
+// of both kinds (tracked_chains, simplex_tracked) it goes through both loops.
 template <int MODE, bool CHI2, int G>
 __device__ __forceinline__ void fit_wave(const FitArgs& a, int64_t wave_item, LaneStats& st) {
   const Item x = item_setup<G>(a, wave_item);
   Lsq ls = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
   const int64_t lanes = G == WIDE ? a.lanes_per_ind : G;
-  const bool track = tracked_chains(a.n_ind, lanes, x.L, x.Cg);
+  const bool track =
+      a.by_chain ? simplex_tracked(x.Cg) : tracked_chains(a.n_ind, lanes, x.L, x.Cg);
   const int64_t Cs = track ? 0 : x.Cg, Ct = track ? x.Cg : 0;
   const int64_t ws = wave_longest<G>(Cs), wt = wave_longest<G>(Ct);
   if (ws > 0) solve_chain<MODE, CHI2, G>(a, x, Cs, ws, st, ls);

@@ -59,6 +59,8 @@ struct FitArgs {
                           // (must read 0 when the kernel starts)
   const int32_t* skip;    // nullable (CSR only): individual i is evaluated
   int32_t skip_per;       // as empty when skip[i / skip_per] != 0
+  int32_t by_chain;       // 1: whether images are tracked follows from the chain
+                          // alone (simplex_tracked), not from how many run
 };
 
 // Lanes of one residency of the chip: 256 compute units x 8 waves.
@@ -78,6 +80,13 @@ constexpr int64_t RESIDENT_LANES = 2048 * 64;
 inline __host__ __device__ bool tracked_chains(int64_t n_ind, int64_t G, int64_t L, int64_t C) {
   return n_ind * G >= 4 * RESIDENT_LANES ? L > 112 && C > 2 : L > 320 && C > 3;
 }
+
+// The same for the trial points of simplices, whose values depend on the points
+// and the lanes, not on how many simplices a call has: by the chain alone.
+// Times of 60 steps, solved and tracked ms, on 64 lanes: 64 simplices of 130
+// epochs (chains of 3) 5.3 and 5.9, of 200 5.8 and 5.8, of 300 6.3 and 6.0; 4096
+// of 130 26.5 and 24.8, of 200 32.6 and 28.1, of 300 38.1 and 30.4.
+inline __host__ __device__ bool simplex_tracked(int64_t C) { return C > 3; }
 
 // Launch the FP64 or mixed fitness kernel; chi2 = false writes A/n_img.
 // Lanes per individual for a launch of n_ind individuals: the fewest of 8,

@@ -875,6 +875,7 @@ int nm_run(const sblm_lcs& lcs, int32_t reps, const double* lo, const double* sp
   a.skip = w.skipT;  // trial slots this round does not need
   a.skip_per = 1;
   a.cold_per = NS;
+  a.by_chain = 1;
   // Lanes per trial point.  While most simplices are still running a
   // round is bound by its work, and 64 lanes (long chains of warm-started
   // epochs per lane, one wave per trial point) do it fastest; later rounds

@@ -408,3 +408,44 @@ def test_tracked_simplices_return_their_points_values(hip):
                                           cfg.tol_x, cfg.tol_f, cfg.max_iter)
         assert it[k] == steps, (k, it[k], steps)
         assert np.array_equal(x[:, k], xr), k
+
+
+@pytest.mark.parametrize("L", [130, 192, 193, 300])
+def test_simplices_do_not_depend_on_the_size_of_the_call(hip, L, monkeypatch):
+    # at 64 lanes without saved roots a simplex's values follow from its points
+    # alone: the simplices of a call that fills the chip (2100 lightcurves, 8400
+    # trial slots) are, bit for bit, those of calls of three lightcurves, and the
+    # iterated simplex is the same with 1 and with 8 slots
+    n_lc = 2100
+    wl = inputs.uniform_workload(53, n_lc, L)
+    y, w = oracle_lightcurves(wl)
+    lcs = device_lcs(hip, wl, y, w)
+    rng = np.random.default_rng(17)
+    x0 = np.clip((wl.theta - LO[:, None]) / (HI - LO)[:, None]
+                 + rng.normal(scale=0.05, size=(6, n_lc)), 0, 1)
+    cfg = hip.nm_default_config()
+    cfg.max_iter = 40
+    big = [a.cpu().numpy() for a in
+           hip.nm_refine_noalloc(lcs, LO, HI, torch.tensor(x0, device="cuda"), cfg)]
+    for k in (0, 1001, n_lc - 3):
+        sl = slice(wl.off[k], wl.off[k + 3])
+        part = hip.Lightcurves(torch.arange(4, dtype=torch.int64, device="cuda") * L,
+                               torch.tensor(wl.t[sl], device="cuda"),
+                               torch.tensor(y[sl], device="cuda"),
+                               torch.tensor(w[sl], device="cuda"))
+        small = [a.cpu().numpy() for a in
+                 hip.nm_refine_noalloc(part, LO, HI,
+                                       torch.tensor(x0[:, k:k + 3].copy(), device="cuda"), cfg)]
+        for u, v in zip(big, small):
+            assert np.array_equal(np.ascontiguousarray(u[..., k:k + 3]).view(np.uint8),
+                                  np.ascontiguousarray(v).view(np.uint8)), k
+    monkeypatch.setenv("SBLM_NM_LANES", "64")
+    cfg.max_iter = 20
+    sl = slice(0, wl.off[300])
+    part = hip.Lightcurves(torch.arange(301, dtype=torch.int64, device="cuda") * L,
+                           torch.tensor(wl.t[sl], device="cuda"),
+                           torch.tensor(y[sl], device="cuda"), torch.tensor(w[sl], device="cuda"))
+    one, eight = ([a.cpu().numpy() for a in hip.nm_iterated(part, LO, HI, reps, 8 // reps, 5, cfg)]
+                  for reps in (1, 8))
+    for u, v in zip(one, eight):
+        assert np.array_equal(u.view(np.uint8), v.view(np.uint8))
