@@ -685,12 +685,13 @@ int mlp_adam_step(mlp_net* net, float lr, void* stream);
  * [epochs*floor(rows/batch)]) receives the loss of every step.  The steps
  * are the ones that mlp_loss_grad and mlp_adam_step would take one call at
  * a time, bit for bit; here one step (and, for a call of 32 or more, eight
- * in a row) is captured as a HIP graph (batch gather, forward, likelihood,
- * backward, Adam, all reading the step index from device memory) and
+ * in a row) is captured as a HIP graph (forward, likelihood, backward, Adam,
+ * all reading the step index, and with it the batch, from device memory) and
  * replayed on the net's own stream, which follows `stream` and which
  * `stream` then waits for.  The graphs are kept with the net for later calls
- * of the same shape and data; step buffers of 16 B per step grow as needed
- * (with a synchronisation of the net's stream).
+ * of the same shape and data; step buffers of 16 B per step grow as needed.
+ * The call returns when its steps are queued; it first waits for those of
+ * the net's call before.
  * Errors: SBLM_EINVAL, SBLM_ERANGE (more than 2^31 steps), SBLM_ENOMEM,
  * SBLM_EDEVICE.
  */

@@ -1232,7 +1232,10 @@ static int copy_canonical(mlp_net* n, float* dev, float* host, bool to_host,
 
 extern "C" int mlp_set_params(mlp_net* n, const float* params) {
   if (!n || !params) return set_error(SBLM_EINVAL, "mlp_set_params: null argument");
-  int rc = copy_canonical(n, n->p, (float*)params, false, "mlp_set_params");
+  // (queued steps and forward passes read and write what is replaced here)
+  int rc = check_hip(hipDeviceSynchronize(), "mlp_set_params");
+  if (rc != SBLM_OK) return rc;
+  rc = copy_canonical(n, n->p, (float*)params, false, "mlp_set_params");
   if (rc != SBLM_OK) return rc;
   rc = check_hip(shadow(n), "mlp_set_params: launch");
   if (rc == SBLM_OK) rc = check_hip(hipMemset(n->m, 0, NP_DEV * 4), "mlp_set_params");
@@ -1486,27 +1489,26 @@ extern "C" int mlp_train(mlp_net* n, const uint16_t* x, const float* y, int64_t 
     sched_h[3 * k + 1] = (float)(1.0 / (1.0 - pow(b1, t)));
     sched_h[3 * k + 2] = (float)(1.0 / (1.0 - pow(b2, t)));
   }
-  int rc = SBLM_OK;
+  // The steps of the call before, which may still be queued on the net's own
+  // stream, read the schedule and run the graphs that this call replaces.
+  int rc = check_hip(hipStreamSynchronize(n->work), "mlp_train: synchronise");
   // the net's work stream follows the caller's
-  rc = check_hip(hipEventRecord(n->ev_in, st), "mlp_train: event");
+  if (!rc) rc = check_hip(hipEventRecord(n->ev_in, st), "mlp_train: event");
   if (!rc) rc = check_hip(hipStreamWaitEvent(n->work, n->ev_in, 0), "mlp_train: wait");
   if (!rc && total > n->sched_cap) {
     // larger step buffers: the graph holds the old ones, so it is captured again
-    rc = check_hip(hipStreamSynchronize(n->work), "mlp_train: synchronise");
-    if (!rc) {
-      if (n->sched) (void)hipFree(n->sched);
-      if (n->losses) (void)hipFree(n->losses);
-      n->sched = nullptr;
-      n->losses = nullptr;
-      n->sched_cap = 0;
-      n->train_key[0] = 0;  // (also where the new buffers take the old addresses)
-      if (hipMalloc(&n->sched, (size_t)total * 3 * sizeof(float)) != hipSuccess ||
-          hipMalloc(&n->losses, (size_t)total * sizeof(float)) != hipSuccess) {
-        (void)hipGetLastError();
-        rc = set_error(SBLM_ENOMEM, "mlp_train: device allocation");
-      } else {
-        n->sched_cap = total;
-      }
+    if (n->sched) (void)hipFree(n->sched);
+    if (n->losses) (void)hipFree(n->losses);
+    n->sched = nullptr;
+    n->losses = nullptr;
+    n->sched_cap = 0;
+    n->train_key[0] = 0;  // (also where the new buffers take the old addresses)
+    if (hipMalloc(&n->sched, (size_t)total * 3 * sizeof(float)) != hipSuccess ||
+        hipMalloc(&n->losses, (size_t)total * sizeof(float)) != hipSuccess) {
+      (void)hipGetLastError();
+      rc = set_error(SBLM_ENOMEM, "mlp_train: device allocation");
+    } else {
+      n->sched_cap = total;
     }
   }
   if (!rc)

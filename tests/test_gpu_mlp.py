@@ -577,3 +577,39 @@ def test_forward_of_more_rows_than_a_grid_holds(hip):
     net.close()
     del x, out
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("batch", [128, 256])
+def test_training_calls_queued_one_after_another(hip, batch):
+    # three calls on a stream of the caller's with nothing waited for between them
+    # -- other learning rates, then other data, whose steps are captured anew --
+    # and parameters set at once after them, against calls waited for one by one
+    rng = np.random.default_rng(21)
+    x = torch.tensor(rng.normal(size=(2048, 256)), device="cuda").to(torch.bfloat16)
+    y = torch.tensor(rng.random((2048, 7)), dtype=torch.float32, device="cuda")
+    x2, y2 = x.flip(0).contiguous(), y.flip(0).contiguous()
+    torch.cuda.synchronize()
+
+    def calls(wait):
+        net = hip.MLP(batch_max=256, seed=9)
+        p0 = net.get_params()
+        st = torch.cuda.Stream()
+        loss = []
+        with torch.cuda.stream(st):
+            for xs, ys, lr in ((x, y, 2e-3), (x, y, 1e-5), (x2, y2, 1e-3)):
+                loss.append(net.train(xs, ys, batch=batch, epochs=40, lr0=lr, lr1=0.1 * lr,
+                                      stream=st))
+                if wait:
+                    torch.cuda.synchronize()
+        p = net.get_params()
+        net.train(x, y, batch=batch, epochs=40, lr0=1e-3, stream=st)
+        net.set_params(p0)
+        back = net.get_params()
+        net.close()
+        return [v.cpu().numpy() for v in loss], np.asarray(p), np.asarray(p0), np.asarray(back)
+
+    queued, waited = calls(False), calls(True)
+    for a, b in zip(queued[0], waited[0]):
+        assert np.array_equal(a, b)
+    assert np.array_equal(queued[1], waited[1])
+    assert np.array_equal(queued[3], queued[2])
