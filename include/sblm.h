@@ -331,14 +331,14 @@ int ea_fitness_time(ea_state* st, double* ms, int64_t* launches);
 /*
  * ea_autotune -- choose the fitness schedule of this state by timing it on
  * the state's own population and lightcurves (coordinate descent over the
- * epoch stepping {asynchronous, lockstep: one kernel serves both, whose
- * lanes step together}, waves per block {1, 2, 4} and a
- * persistent work-counter launch vs a one-shot grid; with 128 or 256 lanes
- * per individual only the waves per block that hold whole individuals, the
- * one-shot grid and lockstep stepping), starting from the current schedule
- * and moving only to a candidate more than 2% faster (so that repeated tuning
- * settles on the same choice despite timing jitter), then re-capture the
- * generation graph.  None of these knobs changes a result bit, so a tuned fit
+ * waves per block {1, 2, 4} and a persistent work-counter launch vs a
+ * one-shot grid; with 128 or 256 lanes per individual only the waves per
+ * block that hold whole individuals and the one-shot grid), starting from
+ * the current schedule and moving only to a candidate more than 2% faster
+ * (so that repeated tuning settles on the same choice despite timing
+ * jitter), then re-capture the generation graph.  The epoch stepping is
+ * kept: asynchronous or lockstep, one kernel serves both, and the report
+ * has its time under either name.  None of these knobs changes a result bit, so a tuned fit
  * is bit-identical to the untuned one.  The lanes per individual are not
  * tuned: each lane warm-starts the root solves along its own chunk of a
  * lightcurve's epochs, so their number decides where the chains of warm

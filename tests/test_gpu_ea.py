@@ -494,3 +494,18 @@ def test_states_of_several_population_sizes(hip):
     assert first.save() == want
     for st in states + [alone, first, second]:
         st.close()
+
+
+@pytest.mark.parametrize("asy", [0, 1])
+def test_autotune_does_not_time_one_kernel_twice(hip, asy):
+    # both steppings run one kernel: the report has its time under either name,
+    # and the setting stays whatever the timings are
+    wl = csr_workload(9, [5, 201, 777, 1500])
+    st, _, _ = _make_state(hip, wl, 32, seed=21)
+    st.set_schedule(16, 2, 1, asy)
+    lines = st.autotune().splitlines()
+    first = [ln.split(": ")[-1] for ln in lines[:3]]
+    assert len(set(first)) == 1 and first[0].endswith("ms"), lines
+    assert {ln.split(":")[0].split("async=")[1] for ln in lines[1:3]} == {"0", "1"}
+    assert st.schedule()[0] == 16 and st.schedule()[3] == asy
+    st.close()
