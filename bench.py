@@ -74,7 +74,7 @@ N_GEN_FIT = 500
 # copy kernel of known size (profiles/fitness_kernel_fp64_256lc_1000ep_pop256_
 # traffic.md).  Valid only for the kernel sources it was taken on (the kernel
 # file and the arithmetic it shares).
-FITNESS_TRAFFIC = dict(source_sha256_16="a3b87db78e9edbd1", bytes_per_launch=204.0e6,
+FITNESS_TRAFFIC = dict(source_sha256_16="b592783d3a009cc2", bytes_per_launch=204.6e6,
                        algorithmic_bytes_per_launch=10.86e6)
 FITNESS_SOURCES = ("sblm_fitness.hip", "sblm_math.h", "sblm_internal.h")
 
@@ -234,13 +234,10 @@ def run_form(sblm, torch, lcs, wl, chi2_true, pop, steps, args, mode, tune=True)
     sweeps = s["n_iter"] / n
     n32 = s["n_iter_fp32"] / n
     refined = s["n_polished"] / n
-    tracked, newton = s["n_newton"] / n, 0.0
-    # MIXED, where n_newton holds the polish passes as well: the first epoch of
-    # every lane's chunk is solved and polished, the others tracked (but for
-    # some 0.5%)
-    if mode == sblm.MIXED:
-        newton, tracked = tracked, 1.0 - min(1.0, sched[0] * n_lc / int(wl.off[-1]))
-        newton -= tracked
+    tracked = s["n_tracked"] / n
+    newton = (s["n_newton"] - s["n_tracked"]) / n
+    # MIXED: every epoch that is not tracked is polished (all but degree-4
+    # polynomials and far roots, a few in 10^6)
     polishes = (1.0 - tracked) if mode == sblm.MIXED else 0.0
     flop = flop_per_magnification(sweeps - n32, n32, refined, newton, polishes, tracked)
     # what the wavefronts executed: lockstep sweeps (n_wave_iter) instead of
@@ -748,7 +745,8 @@ def precision_forms(sblm, torch, lcs, n_lc, args):
         out["single_epoch_magnify"][name] = dict(
             pairs=n, ms=ms, mags_per_s=n / (ms / 1e3),
             sweeps_per_solve=s["n_iter"] / n, fp32_sweeps_per_solve=s["n_iter_fp32"] / n,
-            newton_passes_per_solve=s["n_newton"] / n, fallback_per_solve=s["n_fallback"] / n)
+            newton_passes_per_solve=(s["n_newton"] - s["n_tracked"]) / n,
+            tracked_per_solve=s["n_tracked"] / n, fallback_per_solve=s["n_fallback"] / n)
     lo, hi = inputs.PRIOR_LO, inputs.PRIOR_HI
     x0 = torch.as_tensor(np.clip(rng.random((6, n_lc)), 0, 1), device="cuda")
     for name, mode in (("fp64", sblm.FP64), ("mixed", sblm.MIXED)):

@@ -75,7 +75,7 @@ typedef enum {
  * call that receives a non-NULL pointer.  64-bit device integers. */
 typedef struct {
   unsigned long long n_solves;     /* epochs solved for, by the simultaneous
-                                      iteration or by tracked images (n_newton) */
+                                      iteration or by tracked images (n_tracked) */
   unsigned long long n_iter;       /* simultaneous-iteration sweeps, summed   */
   unsigned long long n_capped;     /* solves that reached the iteration cap,
                                       also after the cold retry (see
@@ -103,11 +103,13 @@ typedef struct {
                                       images (a fold or a cusp of the
                                       caustic), and their images are refined
                                       on the lens equation                    */
-  unsigned long long n_newton;     /* epochs whose images were followed from the
-                                      epoch before by Newton steps on the lens
-                                      equation, with no simultaneous iteration;
-                                      MIXED: also FP64 Newton polish passes over
-                                      the five roots, summed                  */
+  unsigned long long n_newton;     /* n_tracked; MIXED: plus the FP64 Newton polish
+                                      passes over the five roots, summed      */
+  unsigned long long n_tracked;    /* epochs whose images were followed from the
+                                      epoch before (single epochs: from their
+                                      start) by Newton steps on the lens
+                                      equation, with no solve by the
+                                      simultaneous iteration                  */
 } sblm_stats;
 
 /* Ragged batch of lightcurves in CSR form.  Lightcurve k owns epochs

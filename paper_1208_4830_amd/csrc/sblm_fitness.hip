@@ -352,6 +352,11 @@ __device__ __forceinline__ void add_stats(LaneStats& a, const LaneStats& b) {
   a.unsettled += b.unsettled;
   a.newton += b.newton;
 }
+// ... and, in MIXED, the epochs tracked (in FP64, which has no polish passes,
+// those are `newton`: one more register through the loops costs spills).
+struct WaveStats : LaneStats {
+  unsigned int tracked;
+};
 
 // A solve that reaches the iteration cap has settled when its roots are
 // finite and its last sweep moved them by less than this much relative
@@ -903,7 +908,7 @@ __device__ __forceinline__ void solve_chain(const FitArgs& a, const Item& x, int
 // ms; 64 x 1000 x 256 MIXED 1.58 and 0.83 ms.
 template <int MODE, bool CHI2, int G>
 __device__ __forceinline__ void track_chain(const FitArgs& a, const Item& x, int64_t Cg, int64_t C,
-                                            LaneStats& st, Lsq& ls) {
+                                            WaveStats& st, Lsq& ls) {
   const int64_t k0 = x.k0, k1 = x.k1;
   const double q = x.q, d = x.d, t0 = x.t0;
   cx<double> zt[3], vt[3];  // the images at the epoch before, their velocities
@@ -999,6 +1004,7 @@ __device__ __forceinline__ void track_chain(const FitArgs& a, const Item& x, int
   }
   slow.solves += tracked;
   slow.newton += tracked;
+  if (MODE == SBLM_MIXED) st.tracked += tracked;
   add_stats(st, slow);
 }
 
@@ -1017,7 +1023,7 @@ __device__ __forceinline__ int64_t wave_longest(int64_t c) {
 // every lane takes its s-th epoch at the same time.  Where a wave holds chains
 // of both kinds (tracked_chains, simplex_tracked) it goes through both loops.
 template <int MODE, bool CHI2, int G>
-__device__ __forceinline__ void fit_wave(const FitArgs& a, int64_t wave_item, LaneStats& st) {
+__device__ __forceinline__ void fit_wave(const FitArgs& a, int64_t wave_item, WaveStats& st) {
   const Item x = item_setup<G>(a, wave_item);
   Lsq ls = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
   const int64_t lanes = G == WIDE ? a.lanes_per_ind : G;
@@ -1031,24 +1037,27 @@ __device__ __forceinline__ void fit_wave(const FitArgs& a, int64_t wave_item, La
 }
 
 // Adds the wave's counters.
-__device__ __forceinline__ void put_stats(sblm_stats* stats, const LaneStats& st, int lane) {
+template <int MODE>
+__device__ __forceinline__ void put_stats(sblm_stats* stats, const WaveStats& st, int lane) {
   // wave sums in 64 bits
-  unsigned long long v[11] = {st.solves,     st.iters,   st.capped,   st.fallback,
+  unsigned long long v[12] = {st.solves,     st.iters,   st.capped,   st.fallback,
                               st.deg4,       st.wave_iters, st.iters32, st.polished,
-                              st.retried,    st.unsettled, st.newton};
+                              st.retried,    st.unsettled, st.newton,
+                              MODE == SBLM_MIXED ? st.tracked : 0u};
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1)
 #pragma unroll
-    for (int k = 0; k < 11; ++k) v[k] += __shfl_down(v[k], off, 64);
+    for (int k = 0; k < 12; ++k) v[k] += __shfl_down(v[k], off, 64);
+  if (MODE != SBLM_MIXED) v[11] = v[10];
   if (lane == 0 && v[0]) {
-    unsigned long long* dst[11] = {&stats->n_solves,    &stats->n_iter,
+    unsigned long long* dst[12] = {&stats->n_solves,    &stats->n_iter,
                                    &stats->n_capped,    &stats->n_fallback,
                                    &stats->n_degree4,   &stats->n_wave_iter,
                                    &stats->n_iter_fp32, &stats->n_polished,
                                    &stats->n_retried,   &stats->n_unsettled,
-                                   &stats->n_newton};
+                                   &stats->n_newton,    &stats->n_tracked};
 #pragma unroll
-    for (int k = 0; k < 11; ++k)
+    for (int k = 0; k < 12; ++k)
       if (v[k]) atomicAdd(dst[k], v[k]);
   }
 }
@@ -1063,7 +1072,7 @@ __global__ __launch_bounds__(256, 2) void fitness_kernel(
   // (blocks of at most 256 threads: launch_gg refuses larger ones)
   constexpr int GPW = G > 64 ? 1 : 64 / G;  // individuals per wave
   const int lane = threadIdx.x & 63;
-  LaneStats st = {};
+  WaveStats st = {};
   // One-shot grid: wave w takes wave item w (blocks remapped so that
   // consecutive logical blocks sit on one XCD, unless a work order is
   // given).  Persistent grid: waves take items from a shared counter until
@@ -1112,7 +1121,7 @@ __global__ __launch_bounds__(256, 2) void fitness_kernel(
     fit_wave<MODE, CHI2, G>(a, wi, st);
   }
   if (a.stats) {
-    put_stats(a.stats, st, lane);
+    put_stats<MODE>(a.stats, st, lane);
   }
 }
 
@@ -1172,7 +1181,7 @@ __global__ __launch_bounds__(256, 2) void magnify_pairs_kernel(FitArgs a, int ba
   const int64_t p0 = ((int64_t)blockIdx.x * 4 + w) * batches * 64;
   int n_left = 0;
   unsigned int tracked = 0, tried = 0;
-  LaneStats slow = {};
+  WaveStats slow = {};
   for (int b = 0; b < batches && p0 + b * 64 < n; ++b) {
     const int64_t p = p0 + b * 64 + lane;
     const bool active = p < n;
@@ -1240,9 +1249,10 @@ __global__ __launch_bounds__(256, 2) void magnify_pairs_kernel(FitArgs a, int ba
   if (a.stats) {
     slow.solves += tracked;
     slow.newton += tracked;
+    slow.tracked = tracked;
     slow.iters += tried * SBLM_PAIR_SWEEPS;
     slow.wave_iters += tried * SBLM_PAIR_SWEEPS;
-    put_stats(a.stats, slow, lane);
+    put_stats<MODE>(a.stats, slow, lane);
   }
 }
 

@@ -57,7 +57,7 @@ class ea_lc_summary(ctypes.Structure):
 
 STATS_FIELDS = ("n_solves", "n_iter", "n_capped", "n_fallback", "n_degree4", "n_degenerate",
                 "n_wave_iter", "n_iter_fp32", "n_polished", "n_retried",
-                "n_unsettled", "n_newton")
+                "n_unsettled", "n_newton", "n_tracked")
 
 _SIGS = {
     "sblm_magnify": [ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p, ctypes.c_int64,

@@ -410,3 +410,35 @@ def test_magnify_pairs_counts_every_sweep(hip, on_caustic):
     assert s["n_solves"] == n and alone["n_solves"] == 1 and alone["n_iter"] > 1
     assert s["n_newton"] == (0 if on_caustic else n)
     assert s["n_iter"] == (n * (1 + alone["n_iter"]) if on_caustic else n)
+
+
+@pytest.mark.parametrize("mode,tol", [(0, 1e-8), (1, 1e-6)])
+@pytest.mark.parametrize("lanes", ["8", "16", "32"])
+def test_chi2_waves_of_both_kinds_of_chains(hip, monkeypatch, lanes, mode, tol):
+    # individuals of one wave on lightcurves on either side of the length from
+    # which images are tracked (populations of 5 share no wave's bounds with the
+    # lightcurves): the wave goes through both kinds of chains, and its counters
+    # tell them apart
+    monkeypatch.setenv("SBLM_LANES", lanes)
+    lengths, pop = [0, 64, 300, 320, 321, 1000, 30, 1500], 5
+    wl = csr_workload(33, lengths)
+    y, w = oracle_lightcurves(wl)
+    lcs = hip.Lightcurves(_cuda(wl.off, torch.int64), _cuda(wl.t), _cuda(y), _cuda(w))
+    rng = np.random.default_rng(34)
+    theta = inputs.draw_theta(rng, len(lengths) * pop)
+    theta[:, ::pop] = wl.theta
+    st = hip.new_stats()
+    c, fs, fb = (a.cpu().numpy() for a in hip.sblm_chi2(lcs, _cuda(theta), pop, mode=mode, stats=st))
+    co, fso, fbo = O.chi2(wl.off, wl.t, y, w, theta, pop)
+    scale = np.array([np.sum(w[wl.off[k]:wl.off[k + 1]] * y[wl.off[k]:wl.off[k + 1]] ** 2)
+                      for k in range(len(lengths))]).repeat(pop)
+    assert np.all(np.abs(c - co) <= tol * co + 1e-14 * scale)
+    assert np.all(np.abs(fs - fso) <= 1e-5 * (np.abs(fso) + np.abs(fbo)))
+    assert np.all(np.abs(fb - fbo) <= 1e-5 * (np.abs(fso) + np.abs(fbo)))
+    s = hip.stats_dict(st)
+    assert s["n_solves"] == pop * sum(lengths) and s["n_unsettled"] == 0
+    long = pop * sum(L for L in lengths if L > 320)
+    assert 0.5 * long < s["n_tracked"] < long, s
+    # FP64: no polish passes; MIXED: one or two of every solve
+    passes, solved = s["n_newton"] - s["n_tracked"], s["n_solves"] - s["n_tracked"]
+    assert passes == 0 if mode == 0 else 0.9 * solved < passes <= 2 * solved + s["n_retried"], s
