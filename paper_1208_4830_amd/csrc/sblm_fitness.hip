@@ -197,8 +197,9 @@ __device__ __forceinline__ void cold_start(const cx<T> c[6], cx<double> zeta, do
   }
 }
 
-// Images, det J and the magnification from five FP64 roots.  The image
-// count and the choice of images use the roots' residuals (image_score); an
+// Images, det J and the magnification from five FP64 roots.  The image count
+// and the choice of images use the roots' residuals (image_score), or where those
+// tell no three images apart the distances that they stand for; an
 // accepted image that needs it is refined on the lens equation
 // (refine_image).  If next, *order receives, per root, its place when the three
 // images to be tracked from here come first: with three images those, with five the
@@ -216,6 +217,15 @@ __device__ __forceinline__ double magnification(const cx<double> z[5],
 #pragma unroll
   for (int i = 0; i < 5; ++i) below += (r2[i] < SBLM_IMAGE_TOL2) ? 1 : 0;
   const bool five = !deg4 && below >= 4;
+  // Fewer than three roots that solve the lens equation to its tolerance: next to
+  // a lens, in a cluster of roots (a separation below 3e-3, a mass ratio below
+  // 1e-6), a root's rounding is a large residual, |g| times its distance to the
+  // image.  There the distances are what is compared (not for a heavy secondary,
+  // in whose units the clusters are the smaller and the other images the wider).
+  if (below < 3 && q <= 2.0) {
+#pragma unroll
+    for (int i = 0; i < 5; ++i) r2[i] *= rcp_fast(1.0 + adet[i]);
+  }
   // accepted images: sum those that need no refinement, list the others
   double A = 0.0;
   unsigned int todo = 0u;

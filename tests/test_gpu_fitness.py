@@ -442,3 +442,20 @@ def test_chi2_waves_of_both_kinds_of_chains(hip, monkeypatch, lanes, mode, tol):
     # FP64: no polish passes; MIXED: one or two of every solve
     passes, solved = s["n_newton"] - s["n_tracked"], s["n_solves"] - s["n_tracked"]
     assert passes == 0 if mode == 0 else 0.9 * solved < passes <= 2 * solved + s["n_retried"], s
+
+
+@pytest.mark.parametrize("n,lanes", [(3000, None), (200, "1"), (200, "8"), (200, "64")])
+def test_magnify_close_binaries(hip, monkeypatch, n, lanes):
+    # separations of 1e-4 to 3e-3, where three roots of the polynomial crowd about
+    # the lenses and the residual of the image among them is mostly rounding: single
+    # epochs and chains, against the oracle
+    if lanes:
+        monkeypatch.setenv("SBLM_LANES", lanes)
+    rng = np.random.default_rng(110)
+    theta = inputs.draw_theta(rng, n)
+    theta[1] = 10 ** rng.uniform(-4.0, -2.5, n)
+    t = np.linspace(-80.0, 80.0, 700) if lanes else np.array([3.7])
+    for mode in (0, 1):
+        A = hip.sblm_magnify(_cuda(theta), _cuda(t), mode=mode).cpu().numpy()
+        Ao, _ = O.magnify(theta, t)
+        assert np.all(rel_err(A, Ao) < 1e-6), (mode, int(np.sum(rel_err(A, Ao) >= 1e-6)))
