@@ -915,7 +915,8 @@ __device__ __forceinline__ void solve_chain(const FitArgs& a, const Item& x, int
 // the sweeps a wave takes in lockstep).  Solved at every epoch, 256 x 1000
 // epochs x 256 individuals took 4.23 ms FP64 over the prior and 3.23 ms for an
 // evolved population, tracked 2.43 and 2.05; 256 x 200-5000 x 128 5.03 and 3.07
-// ms; 64 x 1000 x 256 MIXED 1.58 and 0.83 ms.
+// ms; 64 x 1000 x 256 MIXED 1.58 and 0.83 ms.  The bound on the length of a judged
+// step (image_close), not yet in these, costs 1.5%: 1.97 and 2.00 ms, 0.83 and 0.84.
 template <int MODE, bool CHI2, int G>
 __device__ __forceinline__ void track_chain(const FitArgs& a, const Item& x, int64_t Cg, int64_t C,
                                             WaveStats& st, Lsq& ls) {
